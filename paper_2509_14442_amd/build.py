@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librbos.so")
-SOURCES = ["abi.hip", "field_pack.hip", "trace_fwd.hip", "render.hip", "trace_adj.hip", "mlp.hip"]
+SOURCES = ["abi.hip", "field_pack.hip", "trace_fwd.hip", "render.hip", "trace_adj.hip", "trace_adj_queue.hip", "mlp.hip"]
 # measurement microbenchmarks (gather, FMA, FP64 atomic and stream ceilings), a library of their own
 CEIL_LIB = os.path.join(HERE, "librbos_ceilings.so")
 CEIL_SOURCES = ["ceilings.hip"]

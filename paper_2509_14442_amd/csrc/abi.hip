@@ -381,7 +381,27 @@ int compute_units() {
   return v;
 }
 
-int finish_launch(Prepared& P, void* workspace, hipStream_t stream, rbos::LaunchPlan& plan) {
+// Rays of one tile that share an interpolation cell, from the scene's geometry: a cell's
+// cross-section seen along the viewing direction over the area of a pixel, both at the
+// middle of the box. The rays of a pixel list are taken as evenly spread in the image: a
+// wavefront then holds a stretch of image rows, thinned out by the list's density.
+double rays_per_cell(const rbos_scene& S) {
+  double vox[3], area = 0.0, depth = 0.0;
+  const int n[3] = {S.nx, S.ny, S.nz};
+  for (int a = 0; a < 3; ++a) vox[a] = (S.box_hi[a] - S.box_lo[a]) / n[a];
+  for (int a = 0; a < 3; ++a) {
+    area += std::fabs(S.cam_fwd[a]) * vox[(a + 1) % 3] * vox[(a + 2) % 3];
+    depth += S.cam_fwd[a] * (0.5 * (S.box_lo[a] + S.box_hi[a]) - S.cam_pos[a]);
+  }
+  const double diag = std::hypot(S.box_hi[0] - S.box_lo[0], S.box_hi[1] - S.box_lo[1], S.box_hi[2] - S.box_lo[2]);
+  const double pitch = 2.0 * std::tan(0.5 * S.cam_fov_x_deg * M_PI / 180.0) / S.width * std::fmax(depth, 0.25 * diag);
+  const double per_cell = area / (pitch * pitch);
+  if (!S.pixel_ids) return per_cell;
+  const double density = (double)S.n_pixels / ((double)S.width * S.height);
+  return std::fmin(per_cell, std::sqrt(per_cell) * density);
+}
+
+int finish_launch(Prepared& P, const rbos_scene* scenes, void* workspace, hipStream_t stream, rbos::LaunchPlan& plan) {
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   hipError_t e = rbos::launch_upload(ws + P.Y.table, P.table.data(), sizeof(SceneDev) * P.table.size(), stream);
   if (e != hipSuccess) return fail(RBOS_E_HIP, "scene table upload failed: %s", hipGetErrorString(e));
@@ -404,6 +424,16 @@ int finish_launch(Prepared& P, void* workspace, hipStream_t stream, rbos::Launch
   while ((longest >> plan.order_shift) >= 1024) ++plan.order_shift;
   plan.ckpt_k = P.table.empty() ? 0 : P.table[0].ckpt_k;
   plan.tracer = P.table.empty() ? 0 : P.table[0].tracer;
+  double weight = 0.0, logs = 0.0;  // geometric mean over the tiles of all scenes
+  for (size_t i = 0; i < P.table.size(); ++i) {
+    if (P.table[i].n_tiles == 0) continue;
+    weight += P.table[i].n_tiles;
+    logs += P.table[i].n_tiles * std::log(rays_per_cell(scenes[i]));
+  }
+  plan.rays_per_cell = weight > 0.0 ? (float)std::exp(logs / weight) : 1.0f;
+  plan.view_axis = 0;
+  for (int a = 1; a < 3 && !P.table.empty(); ++a)
+    if (std::fabs(scenes[0].cam_fwd[a]) > std::fabs(scenes[0].cam_fwd[plan.view_axis])) plan.view_axis = a;
   if (P.L.persistent) {
     e = rbos::launch_fill_u32(plan.queues, 0u, 16, stream);
     if (e != hipSuccess) return fail(RBOS_E_HIP, "queue reset failed: %s", hipGetErrorString(e));
@@ -438,12 +468,17 @@ int adjoint_bind(Prepared& P, const rbos_scene* scenes, int32_t n_scenes, const 
 
 // Enqueue the adjoint: scene table upload into `ws` (the caller's workspace or the
 // static scratch), tile order, adjoint kernel.
-int adjoint_enqueue(Prepared& P, int32_t n_scenes, void* ws, hipStream_t stream_h) {
+int adjoint_enqueue(Prepared& P, const rbos_scene* scenes, int32_t n_scenes, void* ws, hipStream_t stream_h) {
   if (n_scenes == 0 || P.Y.total_tiles == 0) return RBOS_OK;
   rbos::LaunchPlan plan{};
-  int rc = finish_launch(P, ws, stream_h, plan);
+  int rc = finish_launch(P, scenes, ws, stream_h, plan);
   if (rc) return rc;
   hipError_t e = hipSuccess;
+  if (rbos::adjoint_by_queue(plan)) {
+    e = rbos::launch_trace_adj_queue(plan, stream_h);
+    if (e != hipSuccess) return fail(RBOS_E_HIP, "adjoint launch failed: %s", hipGetErrorString(e));
+    return RBOS_OK;
+  }
   if (plan.persistent) {
     e = rbos::launch_tile_order(plan, stream_h);
     if (e != hipSuccess) return fail(RBOS_E_HIP, "tile order launch failed: %s", hipGetErrorString(e));
@@ -600,7 +635,7 @@ int rbos_trace_forward(const rbos_scene* scenes, int32_t n_scenes, const rbos_tr
   if (n_scenes == 0 || P.Y.total_tiles == 0) return RBOS_OK;
   rbos::LaunchPlan plan{};
   hipStream_t stream_h = static_cast<hipStream_t>(stream);
-  rc = finish_launch(P, workspace, stream_h, plan);
+  rc = finish_launch(P, scenes, workspace, stream_h, plan);
   if (rc) return rc;
   hipError_t e = rbos::launch_trace_fwd(plan, stream_h);
   if (e != hipSuccess) return fail(RBOS_E_HIP, "forward launch failed: %s", hipGetErrorString(e));
@@ -639,7 +674,7 @@ int rbos_render(const rbos_scene* scenes, int32_t n_scenes, const rbos_trace_out
   if (n_scenes == 0) return RBOS_OK;
   rbos::LaunchPlan plan{};
   hipStream_t stream_h = static_cast<hipStream_t>(stream);
-  rc = finish_launch(P, workspace, stream_h, plan);
+  rc = finish_launch(P, scenes, workspace, stream_h, plan);
   if (rc) return rc;
   hipError_t e = rbos::launch_render(plan, stream_h);
   if (e != hipSuccess) return fail(RBOS_E_HIP, "render launch failed: %s", hipGetErrorString(e));
@@ -655,7 +690,7 @@ int rbos_trace_adjoint(const rbos_scene* scenes, int32_t n_scenes, const rbos_tr
   if (rc) return rc;
   rc = adjoint_bind(P, scenes, n_scenes, outs, io);
   if (rc) return rc;
-  return adjoint_enqueue(P, n_scenes, workspace, static_cast<hipStream_t>(stream));
+  return adjoint_enqueue(P, scenes, n_scenes, workspace, static_cast<hipStream_t>(stream));
 }
 
 int rbos_trace_adjoint_noalloc(const rbos_scene* scenes, int32_t n_scenes, const rbos_trace_out* outs,
@@ -677,7 +712,7 @@ int rbos_trace_adjoint_noalloc(const rbos_scene* scenes, int32_t n_scenes, const
   void* scratch_dev = nullptr;
   rc = noalloc_scratch(&scratch_dev);
   if (rc) return rc;
-  return adjoint_enqueue(P, n_scenes, scratch_dev, static_cast<hipStream_t>(stream));
+  return adjoint_enqueue(P, scenes, n_scenes, scratch_dev, static_cast<hipStream_t>(stream));
 }
 
 size_t rbos_mlp_param_count(int32_t width, int32_t depth) {

@@ -629,10 +629,10 @@ __device__ __forceinline__ void force_at(const SceneDev& S, const Cell& C, float
 }
 
 // Sample recorder of sharma_step: called with the stage (0, 1, 2 for P1, P2, P3), the
-// record index and the located cell of each of a step's three samples. The forward pass
+// record index and the fractions of each of a step's three samples. The forward pass
 // records nothing; the adjoint's replay keeps them for the reverse sweep.
 struct NoRecord {
-  __device__ __forceinline__ void operator()(int, unsigned, const Cell&) const {}
+  __device__ __forceinline__ void operator()(int, unsigned, const float*) const {}
 };
 
 // Work issued by sharma_step right after the gather of its first sample (the forward's
@@ -729,7 +729,7 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
                                             const Record& record = Record(), const Issue& issue = Issue()) {
   float G1[3], G2[3], G3[3], bh2[3], bh3[3], sm[3], base3[3];
   unsigned rec = cell_index(S, C);
-  record(0, rec, C);
+  record(0, rec, C.f);
   {
     float c[8];
     fetch_cell<DT>(S, rec, c);
@@ -745,7 +745,7 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
   }
   locate3(S, bh2, sm, C);
   rec = cell_index(S, C);
-  record(1, rec, C);
+  record(1, rec, C.f);
   {
     float c[8];
     fetch_cell<DT>(S, rec, c);
@@ -759,7 +759,7 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
   }
   locate3(S, bh3, sm, C);
   rec = cell_index(S, C);
-  record(2, rec, C);
+  record(2, rec, C.f);
   if constexpr (!FULL) return;
   {
     float c[8];
@@ -778,6 +778,164 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
 #pragma unroll
   for (int a = 0; a < 3; ++a)
     locate_floor(st.bh[a], small_part(B, a, st.jf, st.d[a]), S.n_f[a], C.p[a], C.f[a], st.pu[a]);
+}
+
+// Gathers issued ahead of the arithmetic that needs them (sharma_step_ahead). A stage point
+// is the straight base plus a deviation that the step's forces move by ~1e-7 cell, so its
+// cell is known well before its exact position: a Fetched holds, per axis, the base's
+// fraction r = base - floor(base), the line's small part lo and the floor t predicted for
+// r + lo + dev, and the predicted cell's record index and coefficients. The exact point has
+// the fraction f = (r + small) - t, by the operations of `locate`, whenever its floor is t
+// too (0 <= f < 1); else it is located and fetched afresh.
+struct Fetched {
+  float r[3], lo[3], t[3];
+  float pu[3];  // floor(base) + t, the unclamped floor of u
+  unsigned rec;
+  float c[8];
+};
+
+// Fetch the predicted cell of the point `half` half steps on from the state st, with the
+// deviation dev = d + half h/2 e.
+template <int DT>
+__device__ __forceinline__ void fetch_ahead(const SceneDev& S, const RayBase& B, const State& st, float half,
+                                            float h_half, Fetched& F) {
+  int p[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float bh = fmaf(half, B.g2hi[a], st.bh[a]);  // exact: multiples of 2^-14 below 512
+    const float fl = floorf(bh);
+    F.r[a] = bh - fl;
+    F.lo[a] = fmaf(st.jf + half, B.g2lo[a], B.U0lo[a]);
+    F.t[a] = floorf(F.r[a] + (F.lo[a] + fmaf(h_half, st.e[a], st.d[a])));
+    F.pu[a] = fl + F.t[a];
+    p[a] = (int)__builtin_amdgcn_fmed3f(F.pu[a], 0.0f, S.n_f[a]);
+  }
+  F.rec = (unsigned)p[0] + __umul24((unsigned)p[1], (unsigned)S.P0) + __umul24((unsigned)p[2], (unsigned)S.P01);
+  fetch_cell<DT>(S, F.rec, F.c);
+}
+
+// Fractions in the predicted cell of the point with deviation dev; false when it lies in
+// another cell (or at a fraction that rounds to 1).
+__device__ __forceinline__ bool in_fetched(const Fetched& F, const float dev[3], float f[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) f[a] = (F.r[a] + (F.lo[a] + dev[a])) - F.t[a];
+  return fminf(fminf(f[0], f[1]), f[2]) >= 0.0f && fmaxf(fmaxf(f[0], f[1]), f[2]) < 1.0f;
+}
+
+// The point of F with deviation dev, located afresh.
+__device__ __forceinline__ unsigned relocate(const SceneDev& S, const Fetched& F, const float dev[3], float f[3],
+                                             float pu[3]) {
+  int p[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float fl = F.pu[a] - F.t[a];  // floor(base): integers, exact
+    const float ff = F.r[a] + (F.lo[a] + dev[a]);
+    const float t = floorf(ff);
+    f[a] = ff - t;
+    pu[a] = fl + t;
+    p[a] = (int)__builtin_amdgcn_fmed3f(pu[a], 0.0f, S.n_f[a]);
+  }
+  return (unsigned)p[0] + __umul24((unsigned)p[1], (unsigned)S.P0) + __umul24((unsigned)p[2], (unsigned)S.P01);
+}
+
+// The samples a step needs, fetched: the state's own (located, with its fractions) and the
+// predicted second and third ones.
+struct Ahead {
+  unsigned rec;
+  float f[3], c[8];
+  Fetched P2, P3;
+};
+
+template <int DT>
+__device__ __forceinline__ void start_ahead(const SceneDev& S, const RayBase& B, const State& st, Ahead& A) {
+  float sm[3];
+  Cell C;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) sm[a] = small_part(B, a, st.jf, st.d[a]);
+  locate3(S, st.bh, sm, C);
+  A.rec = cell_index(S, C);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) A.f[a] = C.f[a];
+  fetch_cell<DT>(S, A.rec, A.c);
+  fetch_ahead<DT>(S, B, st, 1.0f, S.h_2, A.P2);
+  fetch_ahead<DT>(S, B, st, 2.0f, S.hf, A.P3);
+}
+
+// sharma_step with its gathers ahead: the same arithmetic and the same results. The next
+// step's second and third samples are fetched, from their predicted cells, as soon as this
+// step has used its own (into the same registers: a copy of a load in flight would wait for
+// it), and the new state's own sample lies in the third sample's cell, so a step waits for
+// no gather it has just issued while the predictions hold. For kernels with few wavefronts
+// per SIMD and registers to spare: a step then takes little more than its arithmetic.
+template <int DT, class Record = NoRecord, class Issue = NoIssue, bool FULL = true>
+__device__ __forceinline__ void sharma_step_ahead(const SceneDev& S, const RayBase& B, State& st, Ahead& A,
+                                                  const Record& record = Record(), const Issue& issue = Issue()) {
+  float base3[3], dev[3], f[3], pu[3], G1[3], G2[3], G3[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) base3[a] = stage3_base(S, st, a);
+  record(0, A.rec, A.f);
+  force_code(S, A.c, A.f, G1);
+  // P2
+#pragma unroll
+  for (int a = 0; a < 3; ++a) dev[a] = stage2_dev(S, st, a, G1[a]);
+  const bool ok2 = in_fetched(A.P2, dev, f);
+  force_code(S, A.P2.c, f, G2);
+  unsigned rec = A.P2.rec;
+  if (!ok2) {
+    float c[8];
+    rec = relocate(S, A.P2, dev, f, pu);
+    fetch_cell<DT>(S, rec, c);
+    force_code(S, c, f, G2);
+  }
+  record(1, rec, f);
+  if constexpr (FULL) {
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_ahead<DT>(S, B, st, 3.0f, 3.0f * S.h_2, A.P2);
+    __builtin_amdgcn_sched_barrier(0);
+    issue();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // P3
+#pragma unroll
+  for (int a = 0; a < 3; ++a) dev[a] = stage3_dev(S, a, base3[a], G2[a]);
+  const bool ok3 = in_fetched(A.P3, dev, f);
+  if constexpr (FULL) force_code(S, A.P3.c, f, G3);
+  rec = A.P3.rec;
+  if (!ok3) {
+    rec = relocate(S, A.P3, dev, f, pu);
+    if constexpr (FULL) {
+      float c[8];
+      fetch_cell<DT>(S, rec, c);
+      force_code(S, c, f, G3);
+    }
+  }
+  record(2, rec, f);
+  if constexpr (!FULL) return;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    float dn = fmaf(S.c_x[a], fmaf(2.0f, G2[a], G1[a]), base3[a]);
+    float en = fmaf(S.c_v[a], fmaf(4.0f, G2[a], G1[a]) + G3[a], st.e[a]);
+    st.d[a] = dn;
+    st.e[a] = en;
+    st.bh[a] = fmaf(2.0f, B.g2hi[a], st.bh[a]);  // exact
+  }
+  st.jf += 2.0f;
+  // the new state's sample, in P3's predicted cell
+  const bool ok = in_fetched(A.P3, st.d, A.f);
+  A.rec = A.P3.rec;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) st.pu[a] = A.P3.pu[a];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) A.c[k] = A.P3.c[k];
+  if (!ok) {
+    A.rec = relocate(S, A.P3, st.d, A.f, st.pu);
+    fetch_cell<DT>(S, A.rec, A.c);
+    // complete the fetch here: left pending, it would make the common path wait for every
+    // gather in flight at the join
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  }
+  fetch_ahead<DT>(S, B, st, 2.0f, S.hf, A.P3);
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // One quasi-linear step (Sec. 2.B): the forces are taken on the straight entry line, at
@@ -827,14 +985,14 @@ __device__ __forceinline__ bool outside_box(const SceneDev& S, const RayBase& B,
   return !inside;
 }
 
-// The same test after a sharma_step, from its last locate (C, st.pu): u = pu + f lies in
+// The same test after a sharma_step, from its last locate (f, st.pu): u = pu + f lies in
 // [1/2, n + 1/2] iff -pu <= f - 1/2 <= n - pu, where both bounds are exact integers and
 // f - 1/2 has the sign of the exact difference; NaN (a non-finite position) is outside.
-__device__ __forceinline__ bool outside_located(const SceneDev& S, const State& st, const Cell& C) {
+__device__ __forceinline__ bool outside_located(const SceneDev& S, const State& st, const float f[3]) {
   bool inside = true;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float g = C.f[a] - 0.5f;
+    const float g = f[a] - 0.5f;
     inside = inside & (g >= -st.pu[a]) & (g <= S.n_f[a] - st.pu[a]);
   }
   return !inside;
@@ -900,6 +1058,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_f<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// the same over ints
+__device__ __forceinline__ int wave_sum_int(int v) {
+  v += dpp_i<0xb1>(v);
+  v += dpp_i<0x4e>(v);
+  v += dpp_i<0x141>(v);
+  v += dpp_i<0x140>(v);
+  v += dpp_i<0x142, 0xa>(v);
+  v += dpp_i<0x143, 0xc>(v);
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // max over lanes of a non-negative int

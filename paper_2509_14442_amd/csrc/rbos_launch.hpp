@@ -25,6 +25,8 @@ struct LaunchPlan {
   int* tile_cost;           // adjoint, persistent: longest ray of each tile (steps)
   int* tile_order;          // adjoint, persistent: processing order of the tiles
   int order_shift;          // cost >> order_shift is the sort key (< 1024)
+  float rays_per_cell;      // rays of one tile that share a cell, estimated from the geometry
+  int view_axis;            // axis the (first) camera looks along most
 };
 
 // Grid of a persistent kernel: blocks_per_cu blocks on every compute unit, or as many as
@@ -45,6 +47,9 @@ inline int persistent_grid(Kernel kernel, const LaunchPlan& P, size_t lds_bytes)
 hipError_t launch_trace_fwd(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_render(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_trace_adj(const LaunchPlan& P, hipStream_t stream);
+// the adjoint for few rays per cell or few wavefronts, and whether this call is one
+hipError_t launch_trace_adj_queue(const LaunchPlan& P, hipStream_t stream);
+bool adjoint_by_queue(const LaunchPlan& P);
 // persistent adjoint: fill P.tile_order from the forward's step counts
 hipError_t launch_tile_order(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_field_pack(int nx, int ny, int nz, const float* src, int from_temperature, float rho0G, float T0,

@@ -1,0 +1,481 @@
+// trace_adj_queue.hip -- the adjoint of scenes with few rays per cell or few wavefronts.
+//
+// The coherent kernels (trace_adj.hip) sum the rays of a tile that leave one cell across
+// the wavefront, cell by cell. With about two rays per cell, or a random pixel list, that
+// is a serial reduction for nearly every lane (8192 random pixels of a 512 x 512 camera in
+// the 128^3 room: 7553 us, against 490 us for their forward). Here a lane that leaves a cell
+// puts its sums into a queue in LDS (lanes that leave one cell together and are many are
+// summed first). The queue is turned, 64 entries at a time and one lane per entry, into
+// corner values, which collect per voxel in a table in LDS: the chip takes 2.4e10 FP64
+// atomic requests a second, of one 64-byte line each, and eight of them for every cell that
+// every ray crosses would bound these scenes (256 x 256 rays in that room: 3588 us without
+// the table, 1209 with).
+//
+// What bounds it then is the instruction stream of one wavefront (4.5 to 6 cycles per
+// instruction when alone on its SIMD), so gathers are issued ahead (sharma_step_ahead, the
+// rows of the next step) and the registers for it are taken: one wavefront per SIMD.
+#include <algorithm>
+
+#include "rbos_adjoint.hpp"
+#include "rbos_launch.hpp"
+
+namespace rbos {
+
+// Lanes leaving one cell at a sample are summed across the wavefront from this many on.
+constexpr int QUEUE_GROUP = 8;
+constexpr int QUEUE_MISSES = 3;
+
+// Voxel sums a wavefront keeps in LDS on their way to the gradient: voxel (x, y, z) has the
+// slot of its low coordinate bits, so a compact bundle of rays meets no collision; what
+// does collide goes straight to the gradient. A slot that no entry touched between two
+// sweeps is written out.
+struct VoxelTable {
+  int bits[3];  // slot bits per axis
+  __host__ __device__ int slots() const { return 1 << (bits[0] + bits[1] + bits[2]); }
+};
+
+struct QueuePlan {
+  int entries;  // queue entries (>= 128)
+  VoxelTable table;
+  __host__ __device__ size_t bytes() const { return (size_t)entries * 36 + (size_t)table.slots() * 12; }
+};
+
+constexpr unsigned SLOT_FREE = 0x7fffffffu, SLOT_TOUCHED = 0x80000000u;  // voxel indices are < 2^27
+
+struct QueueMerge {
+  float acc[8];
+  int key;         // record index of the lane's cell, CELL_NONE when empty
+  f32x4* vals;     // LDS: 8 monomial totals per entry
+  int* keys;       // LDS: the entry's cell
+  double* sums;    // LDS: the table's voxel sums
+  unsigned* tags;  // LDS: the slot's voxel, SLOT_FREE when free, with SLOT_TOUCHED since the last sweep
+  QueuePlan Q;
+  int count;       // wave-uniform: queue entries
+  int claims;      // wave-uniform: slots taken since the last sweep
+
+  __device__ __forceinline__ QueueMerge(float* lds, const QueuePlan& plan, int lane)
+      : key(CELL_NONE), Q(plan), count(0), claims(0) {
+    vals = reinterpret_cast<f32x4*>(lds);
+    keys = reinterpret_cast<int*>(lds + 8 * plan.entries);
+    sums = reinterpret_cast<double*>(lds + 9 * plan.entries);
+    tags = reinterpret_cast<unsigned*>(sums + plan.table.slots());
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+    for (int i = lane; i < plan.table.slots(); i += 64) {
+      sums[i] = 0.0;
+      tags[i] = SLOT_FREE;
+    }
+    wave_lds_order();
+  }
+
+  // The last `n` (<= 64) queue entries into the table, one lane per entry: the corner values
+  // of an entry's monomial totals in binary64 (one difference per axis and pair: corner 0
+  // of an axis is m0 - m1, corner 1 is m1).
+  __device__ __forceinline__ void insert(const SceneDev& S, int n, int lane) {
+    wave_lds_order();
+    count -= n;
+    const bool on = lane < n;
+    int took = 0;
+    if (on) {
+      const int i = count + lane;
+      const f32x4 lo = vals[2 * i], hi = vals[2 * i + 1];
+      double g[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int ax = 1; ax < 8; ax <<= 1) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          if (!(c & ax)) g[c] -= g[c | ax];
+      }
+      int p[3];
+      cell_of_record(S, (unsigned)keys[i], p);
+      // the two clamped corners per axis (apron corners repeat the edge voxel): their share
+      // of the voxel index and of the slot
+      unsigned v[3][2], s[3][2];
+      unsigned stride = 1u;
+      int shift = 0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const unsigned c0 = (unsigned)max(p[a] - 1, 0), c1 = (unsigned)min(p[a], S.n[a] - 1);
+        const unsigned mask = (1u << Q.table.bits[a]) - 1u;
+        v[a][0] = c0 * stride;
+        v[a][1] = c1 * stride;
+        s[a][0] = (c0 & mask) << shift;
+        s[a][1] = (c1 & mask) << shift;
+        stride *= (unsigned)S.n[a];
+        shift += Q.table.bits[a];
+      }
+      // claim or find the slots: all eight exchanges in flight together
+      unsigned t[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const unsigned vox = v[0][c & 1] + v[1][(c >> 1) & 1] + v[2][c >> 2];
+        t[c] = SLOT_FREE;
+        __hip_atomic_compare_exchange_strong(&tags[s[0][c & 1] + s[1][(c >> 1) & 1] + s[2][c >> 2]], &t[c],
+                                             vox | SLOT_TOUCHED, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const unsigned vox = v[0][c & 1] + v[1][(c >> 1) & 1] + v[2][c >> 2];
+        const unsigned slot = s[0][c & 1] + s[1][(c >> 1) & 1] + s[2][c >> 2];
+        const double x = g[c] * S.inv_dec_d;
+        const bool taken = t[c] == SLOT_FREE;
+        took += taken ? 1 : 0;
+        if (taken || (t[c] & ~SLOT_TOUCHED) == vox) {
+          __hip_atomic_fetch_add(&sums[slot], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (t[c] == vox) tags[slot] = vox | SLOT_TOUCHED;
+        } else {
+          gatomic_add(S.grad + vox, x);
+        }
+      }
+    }
+    claims += wave_sum_int(took);
+    wave_lds_order();
+  }
+
+  // Write out the slots that were not touched since the last sweep (all with `every`).
+  __device__ __forceinline__ void sweep(const SceneDev& S, bool every, int lane) {
+    wave_lds_order();
+    const int n = Q.table.slots();
+#pragma unroll 2
+    for (int i = lane; i < n; i += 64) {
+      const unsigned t = tags[i];
+      if (t == SLOT_FREE) continue;
+      if (every || !(t & SLOT_TOUCHED)) {
+        gatomic_add(S.grad + (t & ~SLOT_TOUCHED), sums[i]);
+        sums[i] = 0.0;
+        tags[i] = SLOT_FREE;
+      } else {
+        tags[i] = t & ~SLOT_TOUCHED;
+      }
+    }
+    claims = 0;
+    wave_lds_order();
+  }
+
+  // The sums of the lanes in out_m (those lanes have out) become entries, and restart.
+  __device__ __forceinline__ void push(const SceneDev& S, bool out, unsigned long long out_m, int lane) {
+    if (count + 64 > Q.entries) insert(S, 64, lane);
+    // cells with many leaving lanes are summed first; the scan ends with the lanes left too
+    // few, or after QUEUE_MISSES cells of few lanes
+    unsigned long long pend = out_m, few = 0;
+    int misses = 0;
+    while (__popcll(pend) >= QUEUE_GROUP && misses < QUEUE_MISSES) {
+      const int leader = __ffsll((long long)pend) - 1;
+      const int cell = __builtin_amdgcn_readlane(key, leader);
+      const unsigned long long group = pend & __ballot(key == cell);
+      if (__popcll(group) < QUEUE_GROUP) {
+        ++misses;
+        few |= group;
+        pend &= ~group;
+        continue;
+      }
+      const bool mine = out && key == cell;
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = mine ? acc[k] : 0.0f;
+      const float total = wave_sum8(v);
+      if ((lane & 7) == 0) reinterpret_cast<float*>(vals)[8 * count + group_corner(lane)] = total;
+      if (lane == 0) keys[count] = cell;
+      ++count;
+      pend &= ~group;
+    }
+    pend |= few;
+    if (pend) {
+      if ((pend >> lane) & 1) {
+        const int i = count + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(pend >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((unsigned)pend, 0u));
+        vals[2 * i] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+        vals[2 * i + 1] = f32x4{acc[4], acc[5], acc[6], acc[7]};
+        keys[i] = key;
+      }
+      count += __popcll(pend);
+    }
+    if (out) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+    }
+  }
+
+  __device__ __forceinline__ void enter(const SceneDev& S, bool act, unsigned long long act_m, int k, int lane) {
+    const bool out = act && k != key && key != CELL_NONE;
+    const unsigned long long out_m = act_m & __ballot(k != key) & __ballot(key != CELL_NONE);
+    if (out_m) push(S, out, out_m, lane);
+    if (act) key = k;
+  }
+
+  // Entries and slots go out where the caller has its next gathers issued, so that the
+  // atomics' latency runs beside the arithmetic of a step.
+  __device__ __forceinline__ void ease(const SceneDev& S, int lane) {
+    if (count >= 64) insert(S, 64, lane);
+    if (claims >= Q.table.slots() / 4) sweep(S, false, lane);
+  }
+
+  __device__ __forceinline__ void drain(const SceneDev& S, int lane) {
+    push(S, key != CELL_NONE, __ballot(key != CELL_NONE), lane);
+    while (count > 0) insert(S, min(count, 64), lane);
+    sweep(S, true, lane);
+  }
+};
+
+// The three samples of a step as the replay recorded them, with their cells' coefficients.
+struct StepRows {
+  unsigned rec[3];
+  float f[3][3], c[3][8];
+};
+
+template <int DT>
+__device__ __forceinline__ void load_rows(const SceneDev& S, const f32x4* row, StepRows& W) {
+#pragma unroll
+  for (int s = 2; s >= 0; --s) {
+    const f32x4 v = row[s * 64];
+    W.rec[s] = __float_as_uint(v.x);
+    W.f[s][0] = v.y;
+    W.f[s][1] = v.z;
+    W.f[s][2] = v.w;
+  }
+#pragma unroll
+  for (int s = 2; s >= 0; --s) fetch_cell<DT>(S, W.rec[s], W.c[s]);
+}
+
+// Nonlinear tracer, every checkpoint stride: chunks of KS steps replayed into LDS as
+// recorded samples (record index and fractions), then reversed, the rows and cells of a
+// step loaded one step ahead.
+template <int DT, int KS>
+__device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, int lane, float* lds,
+                                                   const QueuePlan& plan) {
+  AdjRay R;
+  adjoint_ray_setup(S, tile, lane, R);
+  const int q = R.q, n = R.n;
+  const bool active = R.active;
+  const RayBase& B = R.B;
+  const bool stored = S.ckpt_k == 1;  // every step's start state is a checkpoint
+  const int K = stored ? KS : S.ckpt_k;
+  const int m_chunks = K / KS;
+  const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
+  f32x4* rows = reinterpret_cast<f32x4*>(lds) + lane;
+  QueueMerge M(lds + KS * 3 * 64 * 4, plan, lane);
+
+  // The state a chunk's replay starts from and its first samples, loaded while the chunk
+  // before it (the one after it on the ray) is reversed.
+  State st;
+  Ahead P;
+  auto load_start = [&](int step) {  // a multiple of the stride
+    state_at_step(B, step, st);
+    if (step == 0) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
+    } else {
+      load_ckpt(S, q, step / S.ckpt_k - 1, st);
+    }
+  };
+  int c0 = (nseg - 1) * K + (m_chunks - 1) * KS;  // first step of the chunk
+  if (active && c0 < n && c0 >= 0 && !stored) {
+    load_start(c0 / K * K);
+    start_ahead<DT>(S, B, st, P);
+  }
+  for (; c0 >= 0; c0 -= KS) {
+    const bool lane_chunk = active && c0 < n;
+    if (lane_chunk) {
+      const int cnt = min(KS, n - c0);
+      if (stored) {
+#pragma unroll 1
+        for (int i = 0; i < cnt; ++i) {
+          load_start(c0 + i);
+          start_ahead<DT>(S, B, st, P);
+          sharma_step_ahead<DT, SampleRow, NoIssue, false>(S, B, st, P, SampleRow{rows + i * 3 * 64});
+        }
+      } else {
+#pragma unroll 1
+        for (int i = c0 % K; i > 0; --i) sharma_step_ahead<DT>(S, B, st, P);
+#pragma unroll 1
+        for (int i = 0; i < cnt - 1; ++i) sharma_step_ahead<DT>(S, B, st, P, SampleRow{rows + i * 3 * 64});
+        sharma_step_ahead<DT, SampleRow, NoIssue, false>(S, B, st, P, SampleRow{rows + (cnt - 1) * 3 * 64});
+      }
+    }
+    const bool next = active && !stored && c0 > 0 && c0 - KS < n;
+    if (next) load_start((c0 - KS) / K * K);
+    StepRows cur;
+    if (lane_chunk && c0 + KS - 1 < n) load_rows<DT>(S, rows + (KS - 1) * 3 * 64, cur);
+#pragma unroll 1
+    for (int i = KS - 1; i >= 0; --i) {
+      const bool act = lane_chunk && c0 + i < n;
+      SampleRev R1, R2, R3;
+      float wA[3], wB[3];
+      if (act) {
+        sample_rev_at(S, cur.c[2], cur.rec[2], cur.f[2], R3);
+        sample_rev_at(S, cur.c[1], cur.rec[1], cur.f[1], R2);
+        sample_rev_at(S, cur.c[0], cur.rec[0], cur.f[0], R1);
+        stage_weights(S, R.rb, R.tb, wA, wB);
+      }
+      if (i > 0 && lane_chunk && c0 + i - 1 < n) load_rows<DT>(S, rows + (i - 1) * 3 * 64, cur);
+      if (i == 0 && next) start_ahead<DT>(S, B, st, P);
+      M.ease(S, lane);
+      reverse_stages(S, M, act, R1, R2, R3, wA, wB, R.rb, R.tb, lane);
+    }
+  }
+  entry_term(S, B, B.V, active, R.tb, M, lane);
+  M.drain(S, lane);
+}
+
+template <int DT, int KS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_queue(
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+  extern __shared__ float lds[];
+  const int gtile = xcd_remap(blockIdx.x, total_tiles);
+  const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
+  adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds, plan);
+}
+
+// A located sample with its cell's coefficients.
+struct Sample {
+  unsigned rec;
+  float f[3], c[8];
+};
+
+// Quasi-linear tracer: the line points j = 0 .. 2n are independent of each other, so a
+// tile's range of them is shared out over `parts` wavefronts. The entry term is linear in
+// the adjoint of the entry velocity: each part adds its own share.
+template <int DT>
+__device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int tile, int part, int parts, int lane,
+                                                      float* lds, const QueuePlan& plan) {
+  AdjRay R;
+  adjoint_ray_setup(S, tile, lane, R);
+  const int n = R.n;
+  const bool active = R.active;
+  const RayBase& B = R.B;
+  const int npts = wave_max_nonneg(active ? 2 * n + 1 : 0);
+  const int j0 = (int)((long long)npts * part / parts), j1 = (int)((long long)npts * (part + 1) / parts);
+  const float h = S.hf;
+  QueueMerge M(lds, plan, lane);
+  float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
+  auto sample_point_j = [&](int j, Sample& P) {
+    const float jf = (float)j;
+    float bh[3], sm[3];
+    Cell C;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      bh[a] = fmaf(jf, B.g2hi[a], B.U0hi[a]);
+      sm[a] = small_part(B, a, jf, 0.0f);
+    }
+    locate3(S, bh, sm, C);
+    P.rec = cell_index(S, C);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) P.f[a] = C.f[a];
+    fetch_cell<DT>(S, P.rec, P.c);
+  };
+  // samples are fetched two points ahead
+  Sample P0, P1;
+  if (active && j0 < j1 && j0 <= 2 * n) sample_point_j(j0, P0);
+  if (active && j0 + 1 < j1 && j0 + 1 <= 2 * n) sample_point_j(j0 + 1, P1);
+#pragma unroll 1
+  for (int j = j0; j < j1; ++j) {
+    const bool act = active && j <= 2 * n;
+    SampleRev Rs;
+    float w[3];
+    if (act) {
+      sample_rev_at(S, P0.c, P0.rec, P0.f, Rs);
+      ql_force_adjoint(S, R, j, w);
+    }
+    P0 = P1;
+    if (active && j + 2 < j1 && j + 2 <= 2 * n) sample_point_j(j + 2, P1);
+    M.ease(S, lane);
+    M.enter(S, act, __ballot(act), act ? Rs.key : 0, lane);
+    if (act) {
+      float p[3];
+      force_rev(S, Rs, w, p, M.acc);
+      const float tj = (float)j * (0.5f * h);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) pv[a] = fmaf(tj, p[a], pv[a]);
+    }
+  }
+  float tb0[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) tb0[a] = part == 0 ? fmaf((float)n * h, R.rb[a], R.tb[a]) + pv[a] : pv[a];
+  entry_term(S, B, B.V, active, tb0, M, lane);
+  M.drain(S, lane);
+}
+
+template <int DT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_trace_adj_ql_queue(
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int parts, QueuePlan plan) {
+  extern __shared__ float lds[];
+  const int gtile = xcd_remap(blockIdx.x, total_tiles);
+  const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
+  adjoint_tile_ql_queue<DT>(S, gtile - S.tile_begin, blockIdx.y, parts, threadIdx.x, lds, plan);
+}
+
+// Steps per recorded chunk for a checkpoint stride.
+static int queue_chunk(const LaunchPlan& P) {
+  return P.ckpt_k == 3 || P.ckpt_k == 4 || P.ckpt_k == 6 ? P.ckpt_k : 8;
+}
+
+// 8 slots per axis hold a tile's cells across the view down to one ray per cell; along the
+// view, 16: the slots the bundle has left wait there for the sweep (8: 1776 against 1223 us
+// on the 128^3 room with 256 x 256 rays).
+static QueuePlan queue_plan(const LaunchPlan& P) {
+  QueuePlan q{128, VoxelTable{{3, 3, 3}}};
+  q.table.bits[P.view_axis] = 4;
+  return q;
+}
+
+static size_t queue_lds(const LaunchPlan& P) {
+  return (P.tracer == 1 ? 0 : (size_t)queue_chunk(P) * 3 * 64 * 16) + queue_plan(P).bytes();
+}
+
+// With every wavefront resident at once (4 per compute unit by registers, fewer by LDS), the
+// nonlinear form is never slower than the coherent kernel, and the fewer rays share a cell
+// the faster: 128^3 room, stride 3, adjoint coherent / queue in us: 48 x 48 rays 7938 /
+// 1105, 256 x 256 (7 rays per cell) 2464 / 1209; 32^3, 160 x 160 (46) 280 / 251. Beyond
+// that the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3, 384 x 384
+// (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. The quasi-linear form shares a tile
+// out over wavefronts while there are few: 64^3, 160 x 160 (12) 773 / 135, 256 x 256 (30)
+// 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 / 2839, 512 x 512 (13)
+// 2974 / 5041.
+bool adjoint_by_queue(const LaunchPlan& P) {
+  if (P.tracer == 1) {
+    const bool few = P.total_tiles <= 4 * P.n_cus;
+    return P.rays_per_cell < (P.total_tiles <= 2 * P.n_cus ? 64.0f : few ? 40.0f : 8.0f);
+  }
+  const int per_cu = std::min(4, (int)(160 * 1024 / queue_lds(P)));
+  return P.total_tiles <= per_cu * P.n_cus || P.rays_per_cell < 6.0f;
+}
+
+template <int DT, int KS>
+static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
+  const QueuePlan plan = queue_plan(P);
+  hipLaunchKernelGGL((k_trace_adj_queue<DT, KS>), dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
+                     P.total_tiles, plan);
+  return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t launch_queue_dt(const LaunchPlan& P, hipStream_t stream) {
+  if (P.tracer == 1) {
+    const int parts = std::max(1, std::min(16, 8 * P.n_cus / P.total_tiles));
+    const QueuePlan plan = queue_plan(P);
+    hipLaunchKernelGGL(k_trace_adj_ql_queue<DT>, dim3(P.total_tiles, parts), dim3(64), queue_lds(P), stream, P.scenes,
+                       P.n_scenes, P.total_tiles, parts, plan);
+    return hipGetLastError();
+  }
+  switch (queue_chunk(P)) {
+    case 3: return launch_queue_t<DT, 3>(P, stream);
+    case 4: return launch_queue_t<DT, 4>(P, stream);
+    case 6: return launch_queue_t<DT, 6>(P, stream);
+    default: return launch_queue_t<DT, 8>(P, stream);
+  }
+}
+
+hipError_t launch_trace_adj_queue(const LaunchPlan& P, hipStream_t stream) {
+  if (P.total_tiles == 0) return hipSuccess;
+  switch (P.dtype) {
+    case DT_F32: return launch_queue_dt<DT_F32>(P, stream);
+    case DT_F16: return launch_queue_dt<DT_F16>(P, stream);
+    case DT_BF16: return launch_queue_dt<DT_BF16>(P, stream);
+    case DT_F32_XPAIR: return launch_queue_dt<DT_F32_XPAIR>(P, stream);
+    case DT_F16_XPAIR: return launch_queue_dt<DT_F16_XPAIR>(P, stream);
+    default: return launch_queue_dt<DT_BF16_XPAIR>(P, stream);
+  }
+}
+
+}  // namespace rbos

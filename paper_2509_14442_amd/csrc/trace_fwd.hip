@@ -50,7 +50,7 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
     // tested every step and the whole state once the ray stops.
     auto stop = [&]() {
       ++n;
-      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, C)) {
+      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, C.f)) {
         exited = true;
         if (!state_finite(st)) status |= RAY_NONFINITE;
       }
