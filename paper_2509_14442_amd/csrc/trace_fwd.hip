@@ -9,7 +9,7 @@ namespace rbos {
 // (component c of the ray at [c * ckpt_pad + ckpt_entry]): the ray header (see
 // store_ray_header), then the states (d, e) before steps k, 2k, ... (6 components per
 // slot).
-template <int DT, bool QL>
+template <int DT, bool QL, bool AHEAD>
 __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int smp) {
   int n = 0;
   unsigned char status = 0;
@@ -45,12 +45,20 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
     float* ck = S.ckpt ? S.ckpt + (size_t)RAY_HEADER * S.ckpt_pad + (size_t)q : nullptr;
     const size_t slot_stride = 6 * (size_t)S.ckpt_pad;
     bool exited = false;
+    Ahead P;  // AHEAD: the next step's samples
+    if constexpr (AHEAD && !QL) start_ahead<DT>(S, B, st, P);
+    auto step = [&](auto issue) {
+      if constexpr (AHEAD)
+        sharma_step_ahead<DT>(S, B, st, P, NoRecord(), issue);
+      else
+        sharma_step<DT>(S, B, st, C, NoRecord(), issue);
+    };
     // after each step: count it, stop on a non-finite state or outside the box. After a
     // Sharma step a non-finite position locates as NaN (outside), so only the velocity is
     // tested every step and the whole state once the ray stops.
     auto stop = [&]() {
       ++n;
-      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, C.f)) {
+      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, AHEAD ? P.f : C.f)) {
         exited = true;
         if (!state_finite(st)) status |= RAY_NONFINITE;
       }
@@ -72,7 +80,7 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
       }
     } else if (!ck) {
       while (n < S.max_steps) {
-        sharma_step<DT>(S, B, st, C);
+        step(NoIssue());
         if (stop()) break;
       }
     } else {
@@ -84,11 +92,11 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
       int until = min(K, S.max_steps);
       while (!exited) {
         while (n < until) {
-          sharma_step<DT>(S, B, st, C);
+          step(NoIssue());
           if (stop()) break;
         }
         if (exited || n >= S.max_steps) break;
-        sharma_step<DT>(S, B, st, C, NoRecord(), [&]() {
+        step([&]() {
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
             gst_stream(ck + (size_t)a * S.ckpt_pad, st.d[a]);
@@ -169,9 +177,9 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
 }
 
 // Held to 64 registers for 8 wavefronts per SIMD (68 would allow 7): the trace without
-// checkpoints runs 3 % faster; with checkpoints it is unchanged.
-template <int DT, bool QL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_trace_fwd(
+// checkpoints runs 3 % faster; with checkpoints it is unchanged. AHEAD: for few wavefronts.
+template <int DT, bool QL, bool AHEAD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AHEAD ? 2 : 8))) void k_trace_fwd(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -181,7 +189,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   const int tile = gtile - S.tile_begin;
   int r, pix, smp;
   if (!tile_ray(S, tile, lane, r, pix, smp)) return;
-  trace_one<DT, QL>(S, r, pix, smp);
+  trace_one<DT, QL, AHEAD>(S, r, pix, smp);
 }
 
 // Persistent form: blocks pull tiles from per-XCD queues (every 8th run of tiles), and
@@ -205,13 +213,24 @@ __global__ __launch_bounds__(256) void k_trace_fwd_persistent(const SceneDev* __
       const SceneDev& S = scenes[si];
       const int tile = t - S.tile_begin;
       int r, pix, smp;
-      if (tile_ray(S, tile, lane, r, pix, smp)) trace_one<DT, QL>(S, r, pix, smp);
+      if (tile_ray(S, tile, lane, r, pix, smp)) trace_one<DT, QL, false>(S, r, pix, smp);
     }
   }
 }
 
+// Few wavefronts leave a step's gathers exposed: up to 9 tiles per compute unit the kernel
+// that issues them ahead runs, one wavefront per block so that they spread over the chip.
+// 192^3 room, stride 16, 160 x 160 rays: 628 -> 378 us, 384 x 384 (9 tiles per unit) 668 ->
+// 511; 128^3, 160 x 160: 388 -> 261 us, 768 x 768 895 -> 1038. The quasi-linear gathers do
+// not wait for each other; more registers alone let two run together: 192^3, 160 x 160 rays
+// 504 -> 354 us, 512 x 512 (16 per unit) 621 -> 561.
 template <int DT, bool QL>
 static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
+  if (P.total_tiles <= (QL ? 16 : 9) * P.n_cus) {
+    hipLaunchKernelGGL((k_trace_fwd<DT, QL, true>), dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes,
+                       P.total_tiles, 1, P.total_tiles);
+    return hipGetLastError();
+  }
   const dim3 block(64 * P.wpb);
   if (P.persistent) {
     const dim3 grid(persistent_grid(k_trace_fwd_persistent<DT, QL>, P, 0));
@@ -219,8 +238,8 @@ static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
                        P.total_tiles, P.queues);
   } else {
     const int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_fwd<DT, QL>), dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes, P.total_tiles,
-                       P.wpb, nblocks);
+    hipLaunchKernelGGL((k_trace_fwd<DT, QL, false>), dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes,
+                       P.total_tiles, P.wpb, nblocks);
   }
   return hipGetLastError();
 }
