@@ -5,11 +5,11 @@
 //
 // The 64 x 64 layers are v_mfma_f32_32x32x2f32 products (FP32 inputs and accumulation).
 // The forward runs all layers of 32 points in one wavefront, the activations staying in
-// registers between layers (k_mlp_forward_fused). The parameter gradient, a sum over
-// points of outer products, runs on the same instruction with the points as K; each
-// block reduces a fixed range of points and a second kernel sums the blocks in order,
-// so the result does not depend on scheduling. The gradient one layer down is computed
-// from the same chunk of points staged in LDS (k_mlp_wgrad with a product).
+// registers between layers (k_mlp_forward_fused), the backward all layers of 128 points in one
+// block, delta and the parameter gradient staying in registers (k_mlp_backward_fused). The
+// jets of the PDE loss run layer by layer (k_jet_*, k_mlp_wgrad). Every sum over points runs
+// over a fixed range per block, and a second kernel adds the blocks in order, so results do
+// not depend on scheduling.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -70,10 +70,15 @@ __host__ __device__ constexpr int fused_lds_floats(int depth) {
 }
 
 __global__ __launch_bounds__(256) void k_mlp_forward_fused(MlpDev M, float* __restrict__ act, float* __restrict__ xh,
-                                                           float* __restrict__ out, float* __restrict__ T, float T0,
-                                                           float dT) {
+                                                           float* __restrict__ wt, float* __restrict__ out,
+                                                           float* __restrict__ T, float T0, float dT) {
   extern __shared__ float lds[];
   const int D = M.depth;
+  // W_l^T of the hidden layers for the backward pass, a layer per block
+  for (int l = 1 + blockIdx.x; l < D; l += gridDim.x)
+    for (int e = threadIdx.x; e < MLP_WIDTH * MLP_WIDTH; e += 256)
+      wt[(l - 1) * MLP_WIDTH * MLP_WIDTH + e] =
+          M.params[M.off_w[l] + (e & (MLP_WIDTH - 1)) * MLP_WIDTH + (e / MLP_WIDTH)];
   float* Wh = lds;                                         // W_1 .. W_{D-1}, rows padded
   float* bh = Wh + (D - 1) * MLP_WIDTH * FUSED_PITCH;      // b_0 .. b_{D-1}
   float* W0 = bh + D * MLP_WIDTH;                          // [3][64]
@@ -159,17 +164,13 @@ __global__ __launch_bounds__(256) void k_mlp_forward_fused(MlpDev M, float* __re
   }
 }
 
-// WT_l = W_l^T for the hidden layers l = 1 .. depth - 1, then the output layer's W_D^T
-// (5 x 64) padded with zero rows to 64 x 64, so that its product runs like the others
+// WT_l = W_l^T for the hidden layers l = 1 .. depth - 1
 __global__ __launch_bounds__(256) void k_mlp_transpose(MlpDev M, float* __restrict__ wt) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   const int l = 1 + idx / (MLP_WIDTH * MLP_WIDTH);
-  if (l > M.depth) return;
+  if (l >= M.depth) return;
   const int e = idx % (MLP_WIDTH * MLP_WIDTH), k = e / MLP_WIDTH, j = e % MLP_WIDTH;
-  float v;
-  if (l < M.depth) v = M.params[M.off_w[l] + k * MLP_WIDTH + j];
-  else v = j < MLP_OUT ? M.params[M.off_w[l] + k * MLP_OUT + j] : 0.0f;
-  wt[(l - 1) * MLP_WIDTH * MLP_WIDTH + j * MLP_WIDTH + k] = v;
+  wt[(l - 1) * MLP_WIDTH * MLP_WIDTH + j * MLP_WIDTH + k] = M.params[M.off_w[l] + k * MLP_WIDTH + j];
 }
 
 // Partial parameter gradient of one layer over this block's rows:
@@ -181,11 +182,9 @@ __global__ __launch_bounds__(256) void k_mlp_transpose(MlpDev M, float* __restri
 // is staged in LDS with coalesced loads, and wavefront (mt, nt) accumulates the 32 x 32
 // tile P[32 mt ..][32 nt ..] with the rows along K.
 // With PROD, the same staged chunk also gives the gradient one layer down, written to
-// Cout [nrows][64]: Cout = B WT (WT = W^T as 64 x 64, zero rows past B's nb columns), times 1 - A^2
-// for PROD_DTANH. Wavefront (mt, nt) computes its rows 32 mt .. and units 32 nt .., so
-// A and B are read from HBM once for both products.
-enum { PROD_NONE = 0, PROD_DTANH = 1, PROD_PLAIN = 2 };
-template <bool XHAT, int PROD = PROD_NONE>
+// Cout [nrows][64]: Cout = B WT (WT = W^T as 64 x 64). Wavefront (mt, nt) computes its rows
+// 32 mt .. and units 32 nt .., so A and B are read from HBM once for both products.
+template <bool XHAT, bool PROD>
 __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpDev M, const float* __restrict__ A, const float* __restrict__ B,
                                                    int ldb, int nb, float* __restrict__ partial,
                                                    long long rows_per_block, long long nrows, long long bias_rows,
@@ -193,9 +192,9 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpDev M, const float* __rest
                                                    float* __restrict__ Cout = nullptr) {
   __shared__ float As[64 * 65];
   __shared__ float Bs[64 * 65];
-  __shared__ float Ws[PROD != PROD_NONE ? 64 * 65 : 1];
+  __shared__ float Ws[PROD ? 64 * 65 : 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if constexpr (PROD != PROD_NONE) {
+  if constexpr (PROD) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int e = t + 256 * i;
@@ -244,7 +243,7 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpDev M, const float* __rest
       acc = mfma32(As[rr * 65 + 32 * mt + c], bvv, acc);
       if (mt == 0 && base + rr < bias_rows) bsum += bvv;
     }
-    if constexpr (PROD != PROD_NONE) {
+    if constexpr (PROD) {
       // rows 32 mt + acc_row(r, h), units 32 nt + c of B WT; K = the 64 columns of B,
       // lane half h supplying k = 32 h + s at step s
       f32x16 d = {};
@@ -257,12 +256,7 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpDev M, const float* __rest
       for (int r = 0; r < 16; ++r) {
         const int rr = 32 * mt + acc_row(r, h);
         if (base + rr < r1) {
-          float v = d[r];
-          if constexpr (PROD == PROD_DTANH) {
-            const float y = As[rr * 65 + 32 * nt + c];
-            v *= 1.0f - y * y;
-          }
-          Cout[(base + rr) * MLP_WIDTH + 32 * nt + c] = v;
+          Cout[(base + rr) * MLP_WIDTH + 32 * nt + c] = d[r];
         }
       }
     }
@@ -275,29 +269,412 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpDev M, const float* __rest
   if (mt == 0 && h == 0) P[MLP_WIDTH * MLP_WIDTH + 32 * nt + c] = bsum + other;
 }
 
-// dparams[layer] += sum over blocks of the partials: W [fi][fo], b [fo]. A block takes 16
-// elements; its 16 thread groups sum the blocks b = g, g + 16, ..., and the groups are
-// added in a fixed order, so the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, int nblk, int fi, int fo,
-                                                    float* __restrict__ dW, float* __restrict__ db) {
+// Fused backward: every layer of a chunk of 128 points in one block, the parameter gradient
+// of every layer accumulated in registers over the block's chunks, so that the activations
+// are read once and nothing else of the size of the point set is touched (a kernel per layer
+// also wrote and read back each delta, 2 x 512 MB per layer at 2M points, and ran the output
+// layer's 5 columns as 64).
+//
+// Four wavefronts carry delta_l = (delta_{l+1} W_l^T)(1 - a_l^2) down the layers, 32 points
+// each, transposed as in the forward (units as rows, points as columns: the accumulators of
+// one product are the B operand of the next; the rows of W_l^T, read through the vector L1,
+// which holds a layer's 16 KB, are the A operand). Four others form dW_l = a_l^T delta_{l+1},
+// the points along K: delta passes through LDS, [point][unit], and wavefront (mt, nt)
+// accumulates the 32 x 32 tile dW_l[32 mt ..][32 nt ..] over all 128 points, a_l's rows read
+// straight from memory as the A operand. Both sides take 64 products of 64 cycles per layer
+// and chunk, and each SIMD holds one of each, so that one side's loads, tanh derivatives and
+// LDS traffic run beside the other's products (with both products in four wavefronts of 512
+// registers: 1873 us at 2M points and depth 4). The output layer (5 columns) and the first
+// one (3 rows and the bias) take 16 x 16 x 4 tiles, 16 units per wavefront.
+//
+// Bound: the products, 0.66 ms at 2M points and depth 4; measured 1.34 ms there (a kernel per
+// layer: 2.18 ms), 34 us at 4096 points (66 us), 2.60 ms at depth 8 (3.98 ms).
+constexpr int BWD_POINTS = 128;  // points per chunk
+constexpr int BWD_PITCH = 68;    // LDS row pitch of a delta chunk
+
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// *(base + imm bytes) at a lane's byte offset, in the form the load instruction takes: a
+// uniform base, one offset register for every load, and an immediate.
+__device__ __forceinline__ float load_at(const float* base, unsigned lane_bytes, int imm) {
+  return *(const __attribute__((address_space(1))) float*)(reinterpret_cast<const char*>(base) + (size_t)lane_bytes +
+                                                           imm);
+}
+
+// 0, as a value the compiler cannot see through: loads addressed with it stay where they are
+// written. Moved up to the layers before, or (the weights) out of the chunk loop, they took
+// several times the registers there are.
+__device__ __forceinline__ int here() {
+  int zero = 0;
+  asm volatile("" : "+s"(zero));
+  return zero;
+}
+
+// What both sides know of the point set and of the chunk at hand.
+struct BackwardSet {
+  const MlpDev& M;
+  const float *act, *xh, *dL, *wt;
+  float* Ds;       // LDS: two delta chunks, taken in turn
+  float* Xs;       // LDS: two chunks of [point][8], dL (5) and the normalised input (3), taken in turn
+  int lane, wave;  // wave 0 .. 3 of its side
+  long long base;  // first point of the chunk
+  int rows;        // its points
+
+  __device__ __forceinline__ const float* layer(int l) const {  // a_l of the chunk
+    return act + ((size_t)(l - 1) * (size_t)M.n + (size_t)base) * MLP_WIDTH;
+  }
+  __device__ __forceinline__ float* delta(int buf) const { return Ds + (buf & 1) * (BWD_POINTS * BWD_PITCH); }
+  __device__ __forceinline__ float* ends(int chunk) const { return Xs + (chunk & 1) * (BWD_POINTS * 8); }
+};
+
+// The side that carries delta down the layers.
+template <int D>
+struct DeltaSide : BackwardSet {
+  int c, h;
+  float wD[2][3];  // the output layer's weights as A operand: row (unit) 32 u + c, K = 2 s + h
+  float dl[32];    // delta_{l+1}: unit 32 t + acc_row(r, h) of point 32 wave + c at [16 t + r]
+  // Loaded ahead, past the barrier between two layers: loads return in order, and the first of
+  // a layer to come from HBM would hold up all its products.
+  f32x4 y[2][8];   // a_l of the lane's point, in dl's order, at [(D - l) & 1]
+  float vw[3][8];  // weights of a layer's step groups, see slot
+  float seed[3];   // dL of the lane's point, outputs 2 s + h
+  f32x4 x;         // its normalised input
+
+  __device__ __forceinline__ explicit DeltaSide(const BackwardSet& s) : BackwardSet(s), c(s.lane & 31), h(s.lane >> 5) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        wD[u][k] = 2 * k + h < MLP_OUT ? M.params[M.off_w[D] + (32 * u + c) * MLP_OUT + 2 * k + h] : 0.0f;
+  }
+
+  // a_l of the lane's point of a chunk (the chunk's last point past its end)
+  template <int l>
+  __device__ __forceinline__ void load_own(const float* a, int n_rows) {
+    const float* q = a + here() + (min(32 * wave + c, n_rows - 1) * MLP_WIDTH + 4 * h);
+    const f32x4* v = reinterpret_cast<const f32x4*>(q);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[(D - l) & 1][i] = v[8 * (i >> 2) + 2 * (i & 3)];
+  }
+
+  // dL and the input of the lane's point of a chunk
+  __device__ __forceinline__ void load_ends(long long chunk, int n_rows) {
+    const long long p = chunk + min(32 * wave + c, n_rows - 1);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) seed[s] = dL[p * MLP_OUT + (2 * s + h < MLP_OUT ? 2 * s + h : 0)];
+    x = *reinterpret_cast<const f32x4*>(xh + p * 4);
+  }
+
+  // Buffer of step group g (0 .. 7) of layer l: the groups take the three in turn, through the
+  // layers.
+  template <int l>
+  static constexpr __device__ int slot(int g) { return (2 * (D - 1 - l) + g) % 3; }
+
+  // step group g of layer l: rows acc_row(s & 15, h) of W_l^T for the steps s = 4 g ..
+  template <int l>
+  __device__ __forceinline__ void load_group(int g) {
+    const float* w = wt + (size_t)(l - 1) * MLP_WIDTH * MLP_WIDTH + here();
+    unsigned ow = 4u * (unsigned)((32 * (g >> 2) + 8 * (g & 3) + 4 * h) * MLP_WIDTH + c);
+    asm volatile("" : "+v"(ow));  // one register, not an address per load
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      vw[slot<l>(g)][2 * i] = load_at(w, ow, 256 * i);
+      vw[slot<l>(g)][2 * i + 1] = load_at(w, ow, 256 * i + 128);
+    }
+  }
+
+  template <int l>
+  __device__ __forceinline__ void times_dtanh(const f32x16& acc0, const f32x16& acc1) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      const float v = y[(D - l) & 1][i >> 2][i & 3], d = i < 16 ? acc0[i & 15] : acc1[i & 15];
+      dl[i] = d * (1.0f - v * v);
+    }
+  }
+
+  // delta_D, and dL and the input to the other side (0 past the end)
+  __device__ __forceinline__ void output_layer(int chunk) {
+    const bool in = 32 * wave + c < rows;
+    float* X = ends(chunk) + (32 * wave + c) * 8;
+    f32x16 acc0 = {}, acc1 = {};
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const float g = in && 2 * s + h < MLP_OUT ? seed[s] : 0.0f;
+      acc0 = mfma32(wD[0][s], g, acc0);
+      acc1 = mfma32(wD[1][s], g, acc1);
+      if (2 * s + h < MLP_OUT) X[2 * s + h] = g;
+    }
+    if (h == 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) X[MLP_OUT + a] = in ? x[a] : 0.0f;
+    }
+    if constexpr (D > 1) {
+      load_own<D - 1>(layer(D - 1), rows);
+      load_group<D - 1>(0);
+      load_group<D - 1>(1);
+    }
+    times_dtanh<D>(acc0, acc1);
+  }
+
+  // Layers l .. 1, then the next chunk's loads. A buffer of the delta is written again two
+  // barriers on, when the other side has read it.
+  template <int l>
+  __device__ __forceinline__ void layers_from(int buf, long long next, int next_rows) {
+    float* Dc = delta(buf);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      *reinterpret_cast<f32x4*>(Dc + (32 * wave + c) * BWD_PITCH + 32 * (q >> 2) + 8 * (q & 3) + 4 * h) =
+          f32x4{dl[4 * q], dl[4 * q + 1], dl[4 * q + 2], dl[4 * q + 3]};
+    if constexpr (l == 0) {
+      base = next;
+      rows = next_rows;
+      if (rows > 0) {
+        load_own<D>(layer(D), rows);
+        if (D == 1) load_ends(base, rows);
+      }
+      __syncthreads();
+    } else {
+      constexpr int below = l > 1 ? l - 1 : 1;
+      __syncthreads();
+      f32x16 acc0 = {}, acc1 = {};
+#pragma unroll
+      for (int g = 0; g < 8; ++g) {
+        __builtin_amdgcn_sched_barrier(0);  // no loads from further ahead
+        if (g + 2 < 8) load_group<l>(g + 2);
+        else if (l > 1) load_group<below>(g - 6);
+        if (g == 5 && l > 1) load_own<below>(layer(below), rows);
+        if (g == 5 && l == 1 && next_rows > 0) load_ends(next, next_rows);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc0 = mfma32(vw[slot<l>(g)][2 * i], dl[4 * g + i], acc0);
+          acc1 = mfma32(vw[slot<l>(g)][2 * i + 1], dl[4 * g + i], acc1);
+        }
+      }
+      times_dtanh<l>(acc0, acc1);
+      layers_from<l - 1>(buf + 1, next, next_rows);
+    }
+  }
+};
+
+// The side that forms the parameter gradient. Operands over the points are 0 past the end.
+// (The loads behind them still lie inside the workspace: up to 127 rows past a layer, 32 KB,
+// are the next layers, then weights and partials.)
+template <int D>
+struct GradSide : BackwardSet {
+  int c, h, c4, k4, mt, nt;
+  f32x16 dW[D > 1 ? D - 1 : 1] = {};  // hidden layers l = 1 .. D - 1 at [l - 1]
+  float db[D > 1 ? D - 1 : 1] = {};
+  f32x4 dWout = {}, dWin = {};
+  float dbout = 0.0f;
+  float va[3][8];  // rows of a layer's step groups, see slot
+
+  __device__ __forceinline__ explicit GradSide(const BackwardSet& s)
+      : BackwardSet(s), c(s.lane & 31), h(s.lane >> 5), c4(s.lane & 15), k4(s.lane >> 4), mt(s.wave >> 1),
+        nt(s.wave & 1) {}
+
+  // Buffer of a step group: the output layer's four, then eight per hidden layer, take the
+  // three in turn.
+  template <int l>
+  static constexpr __device__ int slot(int g) { return l == D ? g % 3 : (4 + 8 * (D - 1 - l) + g) % 3; }
+
+  // step group g of layer l: points 16 g ..
+  template <int l>
+  __device__ __forceinline__ void load_group(int g) {
+    const float* a = layer(l) + here();
+    unsigned oa = 4u * (unsigned)((16 * g + h) * MLP_WIDTH + 32 * mt + c);
+    asm volatile("" : "+v"(oa));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) va[slot<l>(g)][i] = load_at(a, oa, 512 * i);
+  }
+
+  // step group q (0 .. 3) of the output layer: points 32 q .., 4 per step
+  __device__ __forceinline__ void load_output_group(int q) {
+    const float* a = layer(D) + here();
+    unsigned oa = 4u * (unsigned)((32 * q + k4) * MLP_WIDTH + 16 * wave + c4);
+    asm volatile("" : "+v"(oa));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) va[slot<D>(q)][i] = load_at(a, oa, 1024 * i);
+  }
+
+  // Bring a chunk's 32 KB of a_l into the L2 (a line per lane), for a later layer's loads.
+  float touched = 0.0f;
+  __device__ __forceinline__ void touch(int l, long long chunk, int n_rows) {
+    asm volatile("" ::"v"(touched));  // the last one has arrived
+    const int p = min((64 * wave + lane) >> 1, n_rows - 1);
+    touched = act[((size_t)(l - 1) * (size_t)M.n + (size_t)(chunk + p)) * MLP_WIDTH + 32 * (lane & 1) + here()];
+  }
+
+  // dW_D: columns o, K = the points, units 16 wave ..
+  __device__ __forceinline__ void output_layer(int chunk) {
+    const float* X = ends(chunk) + (k4 * 8 + (c4 < MLP_OUT ? c4 : 0));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (q + 2 < 4) load_output_group(q + 2);
+      else if (D > 1) load_group<(D > 1 ? D - 1 : 1)>(q - 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float gp = X[(32 * q + 4 * i) * 8];
+        const float g = c4 < MLP_OUT ? gp : 0.0f;
+        dWout = mfma16(32 * q + 4 * i + k4 < rows ? va[slot<D>(q)][i] : 0.0f, g, dWout);
+        dbout += g;
+      }
+      asm volatile("" : "+v"(dWout), "+v"(dbout));
+    }
+  }
+
+  template <int l>
+  __device__ __forceinline__ void layers_from(int buf, int chunk, long long next, int next_rows) {
+    const float* Dc = delta(buf);
+    __syncthreads();
+    if constexpr (l == D - 1) output_layer(chunk);
+    if constexpr (l == 0) {
+      const float* X = ends(chunk) + (k4 * 8 + MLP_OUT + (c4 < 3 ? c4 : 0));
+      const float* Dp = Dc + (k4 * BWD_PITCH + 16 * wave + c4);
+      if (next_rows > 0) {
+        base = next;
+        load_output_group(0);
+        load_output_group(1);
+      }
+      // dW_0 (columns 0 .. 2) and db_0 (column 3): rows (units) 16 wave ..
+#pragma unroll
+      for (int s = 0; s < BWD_POINTS / 4; ++s) {
+        if (s % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+        const float xp = X[4 * s * 8];
+        const float v = c4 < 3 ? xp : c4 == 3 ? 1.0f : 0.0f;
+        dWin = mfma16(Dp[4 * s * BWD_PITCH], v, dWin);
+      }
+      asm volatile("" : "+v"(dWin));
+      rows = next_rows;
+    } else {
+      constexpr int below = l > 1 ? l - 1 : 1;
+      const float* Dp = Dc + h * BWD_PITCH + 32 * nt + c;
+      float vb[2][8];
+      auto load_delta = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vb[g & 1][i] = Dp[(16 * g + 2 * i) * BWD_PITCH];
+      };
+      load_delta(0);
+#pragma unroll
+      for (int g = 0; g < 8; ++g) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (g + 2 < 8) load_group<l>(g + 2);
+        else if (l > 1) load_group<below>(g - 6);
+        if (g == 5) {  // two layers on: l - 2, or the next chunk's D and D - 1
+          if (l > 2) touch(l - 2, base, rows);
+          else if (next_rows > 0 && (l == 2 || D == 2)) touch(D, next, next_rows);
+          else if (next_rows > 0) touch(D - 1, next, next_rows);
+        }
+        if (g + 1 < 8) load_delta(g + 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float b = vb[g & 1][i];
+          // past the end the delta is 0: only what is not a number has to go
+          dW[l - 1] = mfma32(__builtin_amdgcn_fmed3f(va[slot<l>(g)][i], -1.0f, 1.0f), b, dW[l - 1]);
+          db[l - 1] += b;
+        }
+      }
+      // computed here: the compiler put products and sums off to the end of the chunk, with
+      // every operand held
+      asm volatile("" : "+v"(dW[l - 1]), "+v"(db[l - 1]));
+      layers_from<l - 1>(buf + 1, chunk, next, next_rows);
+    }
+  }
+
+  __device__ __forceinline__ void store(float* partial, int nblk) {
+    auto part = [&](int l) { return partial + ((size_t)l * nblk + blockIdx.x) * MLP_PART; };
+#pragma unroll
+    for (int l = 1; l < D; ++l) {
+      float* P = part(l);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) P[(32 * mt + acc_row(r, h)) * MLP_WIDTH + 32 * nt + c] = dW[l - 1][r];
+      const float sum = db[l - 1] + __shfl_xor(db[l - 1], 32);
+      if (mt == 0 && h == 0) P[MLP_WIDTH * MLP_WIDTH + 32 * nt + c] = sum;
+    }
+    dbout += __shfl_xor(dbout, 16);
+    dbout += __shfl_xor(dbout, 32);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int u = 16 * wave + 4 * k4 + r;
+      if (c4 < MLP_OUT) part(D)[u * MLP_WIDTH + c4] = dWout[r];
+      if (c4 < 3) part(0)[c4 * MLP_WIDTH + u] = dWin[r];
+      if (c4 == 3) part(0)[MLP_WIDTH * MLP_WIDTH + u] = dWin[r];
+    }
+    if (wave == 0 && k4 == 0 && c4 < MLP_OUT) part(D)[MLP_WIDTH * MLP_WIDTH + c4] = dbout;
+  }
+};
+
+template <int D>
+__global__ __launch_bounds__(512, 2) void k_mlp_backward_fused(MlpDev M, const float* __restrict__ act,
+                                                               const float* __restrict__ xh,
+                                                               const float* __restrict__ dL,
+                                                               const float* __restrict__ wt,
+                                                               float* __restrict__ partial, int nblk,
+                                                               long long rows_per_block) {
+  __shared__ __align__(16) float Ds[2 * BWD_POINTS * BWD_PITCH];
+  __shared__ float Xs[2 * BWD_POINTS * 8];
+  // the wavefront's index as a scalar, so that the two sides are branches and not lane masks
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long r0 = (long long)blockIdx.x * rows_per_block;
+  const long long r1 = r0 + rows_per_block < M.n ? r0 + rows_per_block : M.n;
+  auto rows_at = [&](long long b) { return (int)(r1 - b < BWD_POINTS ? r1 - b : BWD_POINTS); };
+  const BackwardSet set{M, act, xh, dL, wt, Ds, Xs, (int)(threadIdx.x & 63), wave & 3, r0, rows_at(r0)};
+  // D barriers per chunk on both sides
+  int chunk = 0, buf = 0;
+  if (wave < 4) {
+    DeltaSide<D> side(set);
+    side.template load_own<D>(side.layer(D), side.rows);
+    side.load_ends(r0, side.rows);
+#pragma unroll 1
+    for (long long b = r0; b < r1; b += BWD_POINTS) {
+      side.output_layer(chunk);
+      side.template layers_from<D - 1>(buf, b + BWD_POINTS, rows_at(b + BWD_POINTS));
+      buf += D;
+      ++chunk;
+    }
+  } else {
+    GradSide<D> side(set);
+    side.load_output_group(0);
+    side.load_output_group(1);
+#pragma unroll 1
+    for (long long b = r0; b < r1; b += BWD_POINTS) {
+      side.template layers_from<D - 1>(buf, chunk, b + BWD_POINTS, rows_at(b + BWD_POINTS));
+      buf += D;
+      ++chunk;
+    }
+    side.store(partial, nblk);
+  }
+}
+
+// dparams += sum over blocks of the partials, all layers in one launch (the packed order: W
+// [fi][fo], b [fo] per layer). A block takes 16 parameters; its 16 thread groups sum the
+// blocks b = g, g + 16, ..., and the groups are added in a fixed order, so the result does
+// not depend on scheduling.
+__global__ __launch_bounds__(256) void k_mlp_reduce(MlpDev M, const float* __restrict__ partial, int nblk,
+                                                    float* __restrict__ dparams) {
   __shared__ float red[16][17];
   const int el = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int e = blockIdx.x * 16 + el;
-  const int ne = fi * fo + fo;
+  const int total = M.off_b[M.depth] + MLP_OUT;
   float s = 0.0f;
-  if (e < ne) {
-    const int src = e < fi * fo ? (e / fo) * MLP_WIDTH + e % fo : MLP_WIDTH * MLP_WIDTH + (e - fi * fo);
+  if (e < total) {
+    int l = 0;
+    while (l < M.depth && e >= M.off_w[l + 1]) ++l;
+    const int fo = l == M.depth ? MLP_OUT : MLP_WIDTH, i = e - M.off_w[l];
+    const int src = e < M.off_b[l] ? (i / fo) * MLP_WIDTH + i % fo : MLP_WIDTH * MLP_WIDTH + (e - M.off_b[l]);
+    const float* P = partial + (size_t)l * nblk * MLP_PART + src;
 #pragma unroll 8
-    for (int b = g; b < nblk; b += 16) s += partial[(long long)b * MLP_PART + src];
+    for (int b = g; b < nblk; b += 16) s += P[(size_t)b * MLP_PART];
   }
   red[g][el] = s;
   __syncthreads();
-  if (g == 0 && e < ne) {
+  if (g == 0 && e < total) {
     float t = red[0][el];
 #pragma unroll
     for (int k = 1; k < 16; ++k) t += red[k][el];
-    if (e < fi * fo) dW[e] += t;
-    else db[e - fi * fo] += t;
+    dparams[e] += t;
   }
 }
 
@@ -601,7 +978,7 @@ size_t mlp_work_bytes(int depth, long long n) {
   const long long nblk = wgrad_blocks(n);
   size_t b = 0;
   b += al256(sizeof(float) * (size_t)depth * (size_t)n * MLP_WIDTH);
-  b += 2 * al256(sizeof(float) * (size_t)n * MLP_WIDTH);
+  b += 2 * al256(sizeof(float) * (size_t)n * MLP_WIDTH);  // spare: the size callers have allocated so far
   b += al256(sizeof(float) * (size_t)depth * MLP_WIDTH * MLP_WIDTH);
   b += al256(sizeof(float) * (size_t)(depth + 1) * (size_t)nblk * MLP_PART);
   b += al256(sizeof(float) * 4 * (size_t)n);
@@ -611,15 +988,10 @@ size_t mlp_work_bytes(int depth, long long n) {
 void mlp_work_carve(void* ws, int depth, long long n, MlpWork& w) {
   const long long nblk = wgrad_blocks(n);
   w.nblk = (int)nblk;
-  long long rows = (n + nblk - 1) / nblk;
-  w.rows_per_block = (rows + 63) / 64 * 64;
   unsigned char* p = static_cast<unsigned char*>(ws);
   w.act = reinterpret_cast<float*>(p);
   p += al256(sizeof(float) * (size_t)depth * (size_t)n * MLP_WIDTH);
-  w.delta[0] = reinterpret_cast<float*>(p);
-  p += al256(sizeof(float) * (size_t)n * MLP_WIDTH);
-  w.delta[1] = reinterpret_cast<float*>(p);
-  p += al256(sizeof(float) * (size_t)n * MLP_WIDTH);
+  p += 2 * al256(sizeof(float) * (size_t)n * MLP_WIDTH);  // spare
   w.wt = reinterpret_cast<float*>(p);
   p += al256(sizeof(float) * (size_t)depth * MLP_WIDTH * MLP_WIDTH);
   w.partial = reinterpret_cast<float*>(p);
@@ -647,38 +1019,37 @@ hipError_t launch_mlp_forward(const MlpDev& M, const MlpWork& w, float* out, flo
   const long long groups = (M.n + 31) / 32;
   const long long blocks = (groups + 3) / 4;
   const int grid = (int)(blocks < 2048 ? blocks : 2048);
-  hipLaunchKernelGGL(k_mlp_forward_fused, dim3(grid), dim3(256), lds, stream, M, w.act, w.xh, out, T, T0, dT);
+  hipLaunchKernelGGL(k_mlp_forward_fused, dim3(grid), dim3(256), lds, stream, M, w.act, w.xh, w.wt, out, T,
+                     T0, dT);
   return hipGetLastError();
+}
+
+template <int D>
+static void launch_backward_depth(const MlpDev& M, const MlpWork& w, const float* dL_dout, int nblk, long long rows,
+                                  hipStream_t stream) {
+  if (M.depth == D)
+    hipLaunchKernelGGL((k_mlp_backward_fused<D>), dim3(nblk), dim3(512), 0, stream, M, w.act, w.xh, dL_dout, w.wt,
+                       w.partial, nblk, rows);
+  else if constexpr (D > 1)
+    launch_backward_depth<D - 1>(M, w, dL_dout, nblk, rows, stream);
+}
+
+static void launch_reduce(const MlpDev& M, const float* partial, int nblk, float* dparams, hipStream_t stream) {
+  const int total = M.off_b[M.depth] + MLP_OUT;
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((total + 15) / 16), dim3(256), 0, stream, M, partial, nblk, dparams);
 }
 
 hipError_t launch_mlp_backward(const MlpDev& M, const MlpWork& w, const float* dL_dout, float* dparams,
                                hipStream_t stream) {
   if (M.n == 0) return hipSuccess;
-  const long long n = M.n;
-  const int D = M.depth;
-  auto act = [&](int l) { return w.act + (size_t)(l - 1) * n * MLP_WIDTH; };  // a_l, l = 1 .. D
-  auto part = [&](int l) { return w.partial + (size_t)l * w.nblk * MLP_PART; };
-  hipLaunchKernelGGL(k_mlp_transpose, dim3(blocks_for((long long)D * MLP_WIDTH * MLP_WIDTH)), dim3(256), 0, stream, M,
-                     w.wt);
-  // output layer: dW_D = a_D^T dL, db_D = sum dL; delta_D = (dL W_D^T)(1 - a_D^2)
-  hipLaunchKernelGGL((k_mlp_wgrad<false, PROD_DTANH>), dim3(w.nblk), dim3(256), 0, stream, M, act(D), dL_dout, MLP_OUT,
-                     MLP_OUT, part(D), w.rows_per_block, n, n, w.wt + (size_t)(D - 1) * MLP_WIDTH * MLP_WIDTH,
-                     w.delta[0]);
-  int cur = 0;
-  for (int l = D - 1; l >= 1; --l) {
-    // dW_l = a_l^T delta_{l+1}; delta_l = (delta_{l+1} W_l^T)(1 - a_l^2)
-    hipLaunchKernelGGL((k_mlp_wgrad<false, PROD_DTANH>), dim3(w.nblk), dim3(256), 0, stream, M, act(l), w.delta[cur],
-                       MLP_WIDTH, MLP_WIDTH, part(l), w.rows_per_block, n, n,
-                       w.wt + (size_t)(l - 1) * MLP_WIDTH * MLP_WIDTH, w.delta[cur ^ 1]);
-    cur ^= 1;
-  }
-  hipLaunchKernelGGL((k_mlp_wgrad<true>), dim3(w.nblk), dim3(256), 0, stream, M, w.xh, w.delta[cur], MLP_WIDTH,
-                     MLP_WIDTH, part(0), w.rows_per_block, n, n);
-  for (int l = 0; l <= D; ++l) {
-    const int fi = l == 0 ? 3 : MLP_WIDTH, fo = l == D ? MLP_OUT : MLP_WIDTH;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((fi * fo + fo + 15) / 16), dim3(256), 0, stream, part(l), w.nblk, fi, fo,
-                       dparams + M.off_w[l], dparams + M.off_b[l]);
-  }
+  // whole chunks per block, on at most the blocks whose partials the workspace holds
+  const long long chunks = (M.n + BWD_POINTS - 1) / BWD_POINTS;
+  const long long per = (chunks + w.nblk - 1) / w.nblk;
+  const int nblk = (int)((chunks + per - 1) / per);
+  launch_backward_depth<MLP_MAX_DEPTH>(M, w, dL_dout, nblk, per * BWD_POINTS, stream);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  launch_reduce(M, w.partial, nblk, dparams, stream);
   return hipGetLastError();
 }
 
@@ -740,29 +1111,26 @@ hipError_t launch_mlp_pde(const MlpDev& M, void* ws, const PdeConst& P, float* l
   if (loss) hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, stream, lpart, blocks_for(n), loss);
   if (!dparams) return hipGetLastError();
   // reverse
-  hipLaunchKernelGGL(k_mlp_transpose, dim3(blocks_for((long long)D * MLP_WIDTH * MLP_WIDTH)), dim3(256), 0, stream, M,
-                     wt);
-  hipLaunchKernelGGL((k_mlp_wgrad<false>), dim3((unsigned)nblk), dim3(256), 0, stream, M, A(D), dj, MLP_OUT, MLP_OUT,
+  if (D > 1)
+    hipLaunchKernelGGL(k_mlp_transpose, dim3(blocks_for((long long)(D - 1) * MLP_WIDTH * MLP_WIDTH)), dim3(256), 0,
+                       stream, M, wt);
+  hipLaunchKernelGGL((k_mlp_wgrad<false, false>), dim3((unsigned)nblk), dim3(256), 0, stream, M, A(D), dj, MLP_OUT, MLP_OUT,
                      part(D), rpb, rows, n);
   hipLaunchKernelGGL((k_jet_act_back<true>), dim3(blocks_for(n * MLP_WIDTH)), dim3(256), 0, stream, M, dj, A(D),
                      Z(D), dz[0]);
   int cur = 0;
   for (int l = D - 1; l >= 1; --l) {
     // dW_l = sum_c a_l^c^T dz_{l+1}^c (bias: value channel); G = dz_{l+1} W_l^T; dz_l
-    hipLaunchKernelGGL((k_mlp_wgrad<false, PROD_PLAIN>), dim3((unsigned)nblk), dim3(256), 0, stream, M, A(l), dz[cur],
+    hipLaunchKernelGGL((k_mlp_wgrad<false, true>), dim3((unsigned)nblk), dim3(256), 0, stream, M, A(l), dz[cur],
                        MLP_WIDTH, MLP_WIDTH, part(l), rpb, rows, n, wt + (size_t)(l - 1) * MLP_WIDTH * MLP_WIDTH, G);
     hipLaunchKernelGGL((k_jet_act_back<false>), dim3(blocks_for(n * MLP_WIDTH)), dim3(256), 0, stream, M, G, A(l),
                        Z(l), dz[cur ^ 1]);
     cur ^= 1;
   }
   // first layer: the input jet (xhat, e_d, 0): rows 0 .. 4n of dz_1
-  hipLaunchKernelGGL((k_mlp_wgrad<true>), dim3((unsigned)nblk), dim3(256), 0, stream, M, xh, dz[cur], MLP_WIDTH,
+  hipLaunchKernelGGL((k_mlp_wgrad<true, false>), dim3((unsigned)nblk), dim3(256), 0, stream, M, xh, dz[cur], MLP_WIDTH,
                      MLP_WIDTH, part(0), rpb, 4 * n, n);
-  for (int l = 0; l <= D; ++l) {
-    const int fi = l == 0 ? 3 : MLP_WIDTH, fo = l == D ? MLP_OUT : MLP_WIDTH;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((fi * fo + fo + 15) / 16), dim3(256), 0, stream, part(l), (int)nblk, fi,
-                       fo, dparams + M.off_w[l], dparams + M.off_b[l]);
-  }
+  launch_reduce(M, partial, (int)nblk, dparams, stream);
   return hipGetLastError();
 }
 

@@ -76,6 +76,27 @@ def test_parameter_gradient_for_given_seeds(depth, n):
     assert np.allclose(_np(d2), 2 * g, rtol=1e-6, atol=1e-6 * np.abs(g).max())
 
 
+@pytest.mark.parametrize("depth", [1, 2, 3, 6, 8])
+@pytest.mark.parametrize("n", [1, 31, 127, 128, 129, 65665])
+def test_parameter_gradient_at_chunk_edges(depth, n):
+    """Point counts around the backward's chunks of 128 and its blocks (65665: the last of 257
+    blocks holds one chunk and one point), with the workspace full of NaN before the forward:
+    what lies past the points must not enter. Bar: rel-L2 < 1e-5 (FP32 sums of at most 2^17
+    products, as above)."""
+    m, th = _mlp(depth, 20 + depth)
+    rng = np.random.default_rng(n)
+    x = rng.uniform(LO, HI, (n, 3)).astype(np.float32)
+    lam = rng.standard_normal((n, 5)).astype(np.float32)
+    xt, lt = torch.from_numpy(x).to(DEV), torch.from_numpy(lam).to(DEV)
+    m.forward(xt, want_out=False)
+    for ws in m._ws.values():
+        ws[:ws.numel() // 4 * 4].view(torch.float32).fill_(float("nan"))
+    m.forward(xt, want_out=False)
+    g = _np(m.backward(lt, xt)).astype(np.float64)
+    ref = omlp.vjp_params(th, 64, depth, x.astype(np.float64), LO, HI, lam.astype(np.float64))
+    assert np.linalg.norm(g - ref) / np.linalg.norm(ref) < 1e-5
+
+
 def test_backward_is_deterministic():
     m, _ = _mlp(4, 4)
     x = torch.from_numpy(np.random.default_rng(5).uniform(LO, HI, (70000, 3)).astype(np.float32)).to(DEV)
