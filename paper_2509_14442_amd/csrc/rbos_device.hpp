@@ -635,7 +635,7 @@ struct NoRecord {
   __device__ __forceinline__ void operator()(int, unsigned, const float*) const {}
 };
 
-// Work issued by sharma_step right after the gather of its first sample (the forward's
+// Work issued by sharma_step right after the gather of its second sample (the forward's
 // checkpoint stores): gfx9 counts loads and stores in one in-order counter, so stores
 // issued before that gather would be waited for with it, while stores issued after it
 // complete in the shadow of the step's arithmetic.
@@ -715,40 +715,61 @@ __device__ __forceinline__ float stage3_dev(const SceneDev& S, int a, float base
   return fmaf(S.c_p3[a], G2, base3);
 }
 
+// A located sample with its cell's coefficients.
+struct Sample {
+  unsigned rec;
+  float f[3], c[8];
+};
+
+template <int DT>
+__device__ __forceinline__ void sample_at_state(const SceneDev& S, const RayBase& B, const State& st, Sample& P) {
+  float sm[3];
+  Cell C;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) sm[a] = small_part(B, a, st.jf, st.d[a]);
+  locate3(S, st.bh, sm, C);
+  P.rec = cell_index(S, C);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) P.f[a] = C.f[a];
+  fetch_cell<DT>(S, P.rec, P.c);
+}
+
 // One Sharma step of Eq. (1) (grid units):
 //   K1 = D(P1), P1 = x
 //   K2 = D(P2), P2 = x + h/2 v + h^2/8 K1
 //   K3 = D(P3), P3 = x + h v + h^2/2 K2
 //   x <- x + h v + h^2/6 (K1 + 2 K2),  v <- v + h/6 (K1 + 4 K2 + K3)
-// The base absorbs the h V part of every position. On return st holds the new state
-// and `C` the located cell of the new position (the next step's first sample). With
-// FULL false the step ends once its third sample is located and recorded (no force
-// there, no new state): the last step of a replayed chunk needs only its samples.
-template <int DT, class Record = NoRecord, class Issue = NoIssue, bool FULL = true>
-__device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B, State& st, Cell& C,
+// The base absorbs the h V part of every position. On entry P is the state's located
+// sample; on return st holds the new state and P its sample (the next step's first). The
+// third point and the new position differ by h^2/6 (K1 + 2 K2 - 3 K2), ~1e-7 cell, so the
+// third sample's coefficients serve the new state unless its record is another one: two
+// gathers per step instead of three (1M-ray room: forward 1480 -> 1450 us, 512 x 512 rays 534
+// -> 477, stride-3 adjoint 4570 -> 4390). A step may end early: at SAMPLES once its third
+// sample is located and recorded (no force there, no new state; the last step of a replayed
+// chunk needs only its samples), at STATE with the new state but not its sample (P and st.pu
+// are then left undefined).
+enum class StepEnd { SAMPLES, STATE, NEXT_SAMPLE };
+template <int DT, class Record = NoRecord, class Issue = NoIssue, StepEnd END = StepEnd::NEXT_SAMPLE>
+__device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B, State& st, Sample& P,
                                             const Record& record = Record(), const Issue& issue = Issue()) {
   float G1[3], G2[3], G3[3], bh2[3], bh3[3], sm[3], base3[3];
-  unsigned rec = cell_index(S, C);
-  record(0, rec, C.f);
-  {
-    float c[8];
-    fetch_cell<DT>(S, rec, c);
-    __builtin_amdgcn_sched_barrier(0);
-    issue();
-    __builtin_amdgcn_sched_barrier(0);
-    force_code(S, c, C.f, G1);
-  }
+  Cell C;
+  record(0, P.rec, P.f);
+  force_code(S, P.c, P.f, G1);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     bh2[a] = st.bh[a] + B.g2hi[a];
     sm[a] = small_part(B, a, st.jf + 1.0f, stage2_dev(S, st, a, G1[a]));
   }
   locate3(S, bh2, sm, C);
-  rec = cell_index(S, C);
+  unsigned rec = cell_index(S, C);
   record(1, rec, C.f);
   {
     float c[8];
     fetch_cell<DT>(S, rec, c);
+    __builtin_amdgcn_sched_barrier(0);
+    issue();
+    __builtin_amdgcn_sched_barrier(0);
     force_code(S, c, C.f, G2);
   }
 #pragma unroll
@@ -760,12 +781,9 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
   locate3(S, bh3, sm, C);
   rec = cell_index(S, C);
   record(2, rec, C.f);
-  if constexpr (!FULL) return;
-  {
-    float c[8];
-    fetch_cell<DT>(S, rec, c);
-    force_code(S, c, C.f, G3);
-  }
+  if constexpr (END == StepEnd::SAMPLES) return;
+  fetch_cell<DT>(S, rec, P.c);
+  force_code(S, P.c, C.f, G3);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     float dn = fmaf(S.c_x[a], fmaf(2.0f, G2[a], G1[a]), base3[a]);
@@ -775,9 +793,16 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
     st.bh[a] = bh3[a];
   }
   st.jf += 2.0f;
+  if constexpr (END == StepEnd::STATE) return;
 #pragma unroll
   for (int a = 0; a < 3; ++a)
-    locate_floor(st.bh[a], small_part(B, a, st.jf, st.d[a]), S.n_f[a], C.p[a], C.f[a], st.pu[a]);
+    locate_floor(st.bh[a], small_part(B, a, st.jf, st.d[a]), S.n_f[a], C.p[a], P.f[a], st.pu[a]);
+  P.rec = cell_index(S, C);
+  if (P.rec != rec) {
+    fetch_cell<DT>(S, P.rec, P.c);
+    // complete the fetch here: left pending, it would make the common path wait at the join
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  }
 }
 
 // Gathers issued ahead of the arithmetic that needs them (sharma_step_ahead). A stage point

@@ -327,12 +327,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds, plan);
 }
 
-// A located sample with its cell's coefficients.
-struct Sample {
-  unsigned rec;
-  float f[3], c[8];
-};
-
 // Quasi-linear tracer: the line points j = 0 .. 2n are independent of each other, so a
 // tile's range of them is shared out over `parts` wavefronts. The entry term is linear in
 // the adjoint of the entry velocity: each part adds its own share.

@@ -1,5 +1,7 @@
 // trace_fwd.hip -- forward ray tracing (Sec. 2.B, Eq. 1): one ray per lane, 64-ray
 // tiles per wavefront, every scene of a batch in one launch.
+#include <type_traits>
+
 #include "rbos_device.hpp"
 #include "rbos_launch.hpp"
 
@@ -45,20 +47,21 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
     float* ck = S.ckpt ? S.ckpt + (size_t)RAY_HEADER * S.ckpt_pad + (size_t)q : nullptr;
     const size_t slot_stride = 6 * (size_t)S.ckpt_pad;
     bool exited = false;
-    Ahead P;  // AHEAD: the next step's samples
+    std::conditional_t<AHEAD, Ahead, Sample> P;  // the next step's samples
     if constexpr (AHEAD && !QL) start_ahead<DT>(S, B, st, P);
+    if constexpr (!AHEAD && !QL) sample_at_state<DT>(S, B, st, P);
     auto step = [&](auto issue) {
       if constexpr (AHEAD)
         sharma_step_ahead<DT>(S, B, st, P, NoRecord(), issue);
       else
-        sharma_step<DT>(S, B, st, C, NoRecord(), issue);
+        sharma_step<DT>(S, B, st, P, NoRecord(), issue);
     };
     // after each step: count it, stop on a non-finite state or outside the box. After a
     // Sharma step a non-finite position locates as NaN (outside), so only the velocity is
     // tested every step and the whole state once the ray stops.
     auto stop = [&]() {
       ++n;
-      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, AHEAD ? P.f : C.f)) {
+      if (!isfinite((st.e[0] + st.e[1]) + st.e[2]) || outside_located(S, st, P.f)) {
         exited = true;
         if (!state_finite(st)) status |= RAY_NONFINITE;
       }
