@@ -145,13 +145,6 @@ __device__ __forceinline__ void load_ckpt(const SceneDev& S, int r, int slot, St
   }
 }
 
-__device__ __forceinline__ void locate_state(const SceneDev& S, const RayBase& B, const State& st, Cell& C) {
-  float sm[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) sm[a] = small_part(B, a, st.jf, st.d[a]);
-  locate3(S, st.bh, sm, C);
-}
-
 // Ray setup of the adjoint: the ray of this lane, its step count and whether it carries
 // a gradient, its straight-line base from the header, and the adjoint of the last state
 // through the wall step X = x + s v:

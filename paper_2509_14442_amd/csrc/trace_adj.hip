@@ -1,12 +1,11 @@
 // trace_adj.hip -- Sec. 2.D: exact gradient of L_BOS with respect to eta - 1 per voxel,
 // back-propagated through the wall step and every Sharma step of Eq. (1).
 //
-// Per wavefront (64 rays of one tile), segments between checkpoints are processed from
-// the last to the first, aligned on the step index so that the tile's rays move through
-// the same cells together. A segment is replayed forward from its checkpoint in chunks
-// of KS steps, keeping in LDS either each step's start state (then the reverse relocates
-// the step's samples) or, for strides 3 and 4 (a segment is then one chunk), the cells
-// and fractions of its three samples; the chunk is then reversed step by step. Each
+// Per wavefront (64 rays of one tile), the steps are processed from the last to the first
+// in chunks of 3, aligned on the step index so that the tile's rays move through the same
+// cells together. A chunk is replayed forward from a state at its start (a checkpoint, or one
+// reached from there), keeping in LDS the cells and fractions of each step's three samples,
+// and then reversed step by step. Each
 // sample's contributions are merged per lane, as monomial coefficients, while the ray
 // stays in one cell; lanes that left the same cell are summed across the wavefront into a
 // per-wavefront LDS cache of cell totals, which goes to the gradient with one FP64 atomic
@@ -163,7 +162,7 @@ __device__ __forceinline__ void enter(const SceneDev& S, Accum& A, bool act, uns
   const bool out = act && key != A.key && A.key != CELL_NONE;
   const unsigned long long out_m = act_m & __ballot(key != A.key) & __ballot(A.key != CELL_NONE);
   if (out_m) {
-    __builtin_amdgcn_s_setprio(3);  // the merge's reduction chains first (see the recording form)
+    __builtin_amdgcn_s_setprio(3);  // the merge's reduction chains first (see adjoint_tile)
     if (PARK) {
       const bool busy = out && A.pkey != CELL_NONE;
       const unsigned long long busy_m = out_m & __ballot(A.pkey != CELL_NONE);
@@ -202,24 +201,97 @@ struct CellMerge : Accum {
   }
 };
 
-// Occupancy: chunks of 8 steps take 13 KB of LDS per wavefront, so 3 wavefronts per SIMD;
-// chunks of 6 take 10 KB, and 4 fit when the registers are held to 128.
-template <int KS>
-constexpr int adj_waves_per_simd() { return KS == 6 ? 4 : 3; }
+// How a chunk of the reverse gets its steps' states.
+enum class Replay {
+  STORED,   // stride 1: every step's start state is a checkpoint
+  SEGMENT,  // stride 3: a segment is one chunk, replayed from its checkpoint
+  WALK,     // strides 4 and 6: each chunk from the checkpoint before it, over steps in between
+  CHUNKS,   // longer strides: a pass over the segment leaves its chunks' start states
+};
 
-// Recording form: chunks of 4 steps take 13 KB of LDS per wavefront (3 wavefronts per
-// SIMD), chunks of 3 take 10 KB (4 per SIMD with the registers held to 128).
-template <int KS>
-constexpr int rec_waves_per_simd() { return KS == 3 ? 4 : 3; }
+// The replay of a chunk keeps, for each of its steps, the record index and fractions of the
+// step's three samples as the forward located them (16 bytes per sample and lane in LDS,
+// sample s of step i of lane l at [(i * 3 + s) * 64 + l]). The reverse of a step then reads
+// them back, issues its three cell gathers together and evaluates value, gradient and mixed
+// second derivatives at exactly the forward's cells and fractions, without relocating the
+// samples from the state (no stage points, no K1 / K2, no dependent gathers). Chunks of 3
+// steps take 10 KB of LDS per wavefront: 4 wavefronts per SIMD, registers held to 128.
+//
+// With CHUNKS the start states of a part's chunks lie in a private array (24 bytes per
+// chunk, coalesced, mostly in the L2): a part's steps run twice, where replays from the
+// checkpoint to every chunk's start would be quadratic in the stride.
+//
+// Bound by VALU issue. 1M rays, adjoint, against chunks of 8 (stride 6: of 6) step states in
+// LDS, whose samples the reverse located again, at 3 (4) wavefronts per SIMD: stride 1 4910 ->
+// 4610 us, 6 5290 -> 4860, 8 6050 -> 5390, 16 6640 -> 5500; stride 4, recorded before too, by
+// 4 at 3 wavefronts per SIMD: 5130 -> 4990; stride 3: 4390 -> 4310. 512 x 512 rays, stride 16: 2900 -> 2000, since its
+// 4096 wavefronts now reside at once.
+constexpr int CHUNK = 3;
+constexpr int CHUNK_FLOATS = CHUNK * 3 * 64 * 4;
+constexpr int PART_CHUNKS = 8;  // chunks of a part: strides up to 24 are one part
 
-// LDS per wavefront: the replayed step-start states of one chunk, slot (i, component) of
-// lane l at replay[(i * 6 + c) * 64 + l] (conflict-free), then the cell-total cache.
-template <int KS>
-constexpr int lds_floats_per_wave() { return KS * 6 * 64 + PEND_SLOTS * 8; }
+constexpr int adj_floats_per_wave() { return CHUNK_FLOATS + PEND_SLOTS * 8; }
 
-template <int DT, int KS, bool STORED>
-__device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int lane, float* __restrict__ replay) {
-  constexpr bool PARK = adj_waves_per_simd<KS>() == 3;  // registers for the parks
+// Chunks between two write-outs of the cache's stale slots: each write-out exposes its
+// atomics' latency once, and at every chunk of 3 steps that cost showed (-2 % adjoint time at
+// 9 steps; at 12 or more the cache fills and misses write slots out one at a time).
+constexpr int WRITEOUT_CHUNKS = 3;
+
+// The state at a segment's first step: the entry state or the checkpoint before it.
+__device__ __forceinline__ void segment_state(const SceneDev& S, int q, int seg, State& st) {
+  if (seg == 0) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
+  } else {
+    load_ckpt(S, q, seg - 1, st);
+  }
+}
+
+// Replay cnt > 0 steps from st, their samples into LDS; the last step only up to its third sample.
+template <int DT>
+__device__ __forceinline__ void record_chunk(const SceneDev& S, const RayBase& B, State& st, int cnt, f32x4* smp,
+                                             int lane) {
+  Sample P;
+  sample_at_state<DT>(S, B, st, P);
+#pragma unroll 1
+  for (int i = 0; i < cnt - 1; ++i) sharma_step<DT>(S, B, st, P, SampleRow{smp + i * 3 * 64 + lane});
+  sharma_step<DT, SampleRow, NoIssue, StepEnd::SAMPLES>(S, B, st, P, SampleRow{smp + (cnt - 1) * 3 * 64 + lane});
+}
+
+// Reverse of one chunk, from the samples in LDS: steps c0 + cnt - 1 .. c0 of lanes with cnt > 0.
+template <int DT>
+__device__ __forceinline__ void reverse_chunk(const SceneDev& S, CellMerge<false>& M, const f32x4* smp, int cnt,
+                                              float rb[3], float tb[3], int lane) {
+  __builtin_amdgcn_s_setprio(1);
+#pragma unroll  // one copy per step: 1 % faster than the rolled loop, same registers
+  for (int i = CHUNK - 1; i >= 0; --i) {
+    const bool act = i < cnt;
+    SampleRev R1, R2, R3;
+    float wA[3], wB[3];
+    if (act) {
+      const f32x4* row = smp + i * 3 * 64 + lane;
+      const f32x4 s1 = row[0], s2 = row[64], s3 = row[128];
+      const unsigned r1 = __float_as_uint(s1.x), r2 = __float_as_uint(s2.x), r3 = __float_as_uint(s3.x);
+      float c1[8], c2[8], c3[8];
+      fetch_cell<DT>(S, r3, c3);
+      fetch_cell<DT>(S, r2, c2);
+      fetch_cell<DT>(S, r1, c1);
+      const float f3[3] = {s3.y, s3.z, s3.w}, f2[3] = {s2.y, s2.z, s2.w}, f1[3] = {s1.y, s1.z, s1.w};
+      sample_rev_at(S, c3, r3, f3, R3);
+      sample_rev_at(S, c2, r2, f2, R2);
+      sample_rev_at(S, c1, r1, f1, R1);
+      stage_weights(S, rb, tb, wA, wB);
+    }
+    reverse_stages(S, M, act, R1, R2, R3, wA, wB, rb, tb, lane);
+  }
+}
+
+// Wave priority, lowest to highest: the replay (a chain of dependent gathers), the reverse
+// (independent gathers, long VALU runs), the merge (serial wavefront reductions, raised in
+// `enter`). Each ordering step measured -2 % adjoint time in alternating runs, whatever the
+// levels.
+template <int DT, Replay MODE>
+__device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int lane, float* __restrict__ lds) {
   AdjRay R;
   adjoint_ray_setup(S, tile, lane, R);
   const int q = R.q, n = R.n;
@@ -227,118 +299,96 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
   const RayBase& B = R.B;
   float* rb = R.rb;
   float* tb = R.tb;
-  // STORED (stride 1): every step's start state is in the checkpoints and a chunk is
-  // filled from them; otherwise a segment of K steps is replayed from its checkpoint in
-  // chunks.
-  const int K = S.ckpt_k;
-  const int seg_len = STORED ? KS : K;
-  const int m_chunks = seg_len / KS;
-  const int nseg_lane = active ? (n + seg_len - 1) / seg_len : 0;
-  const int nseg = wave_max_nonneg(nseg_lane);
+  CellMerge<false> M(lds + CHUNK_FLOATS);
+  f32x4* smp = reinterpret_cast<f32x4*>(lds);
 
-  CellMerge<PARK> M(replay + KS * 6 * 64);
-
-  for (int seg = nseg - 1; seg >= 0; --seg) {
-    for (int ch = m_chunks - 1; ch >= 0; --ch) {
-      const int c0 = seg * seg_len + ch * KS;  // first step of the chunk
-      const bool lane_chunk = active && c0 < n;
-      if (STORED && lane_chunk) {
-        // step j starts from slot j - 1 (zero deviation at j = 0); all loads first
-        float v[KS][6];
-#pragma unroll
-        for (int i = 0; i < KS; ++i) {
-          const int j = c0 + i;
+  if constexpr (MODE == Replay::CHUNKS) {
+    const int K = S.ckpt_k;
+    const int part_len = min(K, CHUNK * PART_CHUNKS);
+    const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
+    int due = WRITEOUT_CHUNKS;
+    for (int seg = nseg - 1; seg >= 0; --seg) {
+      for (int p0 = ((K - 1) / part_len) * part_len; p0 >= 0; p0 -= part_len) {
+        const int s0 = seg * K + p0;                            // first step of the part
+        const int m = active ? min(part_len, min(K - p0, n - s0)) : 0;  // the lane's steps in it
+        const int nch = wave_max_nonneg((max(m, 0) + CHUNK - 1) / CHUNK);
+        float start[PART_CHUNKS][6];
+        __builtin_amdgcn_s_setprio(0);
+        if (m > 0) {
           State st;
-          if (j >= 1 && j < n) {
-            load_ckpt(S, q, j - 1, st);
-          } else {
+          state_at_step(B, seg * K, st);
+          segment_state(S, q, seg, st);
+          Sample P;
+          if (nch > 1 || p0 > 0) sample_at_state<DT>(S, B, st, P);
+#pragma unroll 1
+          for (int i = 0; i < p0; ++i) sharma_step<DT>(S, B, st, P);  // to the part's start
+#pragma unroll 1
+          for (int c = 0;; ++c) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
+            for (int a = 0; a < 3; ++a) { start[c][a] = st.d[a]; start[c][3 + a] = st.e[a]; }
+            if ((c + 1) * CHUNK >= m) break;
+#pragma unroll 1
+            for (int i = 0; i < CHUNK; ++i) sharma_step<DT>(S, B, st, P);
           }
-#pragma unroll
-          for (int a = 0; a < 3; ++a) { v[i][a] = st.d[a]; v[i][3 + a] = st.e[a]; }
         }
+#pragma unroll 1
+        for (int c = nch - 1; c >= 0; --c) {
+          const int c0 = c * CHUNK;
+          const int cnt = min(CHUNK, m - c0);
+          __builtin_amdgcn_s_setprio(0);
+          if (cnt > 0) {
+            State st;
+            state_at_step(B, s0 + c0, st);
 #pragma unroll
-        for (int i = 0; i < KS; ++i) {
-#pragma unroll
-          for (int c = 0; c < 6; ++c) replay[(i * 6 + c) * 64 + lane] = v[i][c];
+            for (int a = 0; a < 3; ++a) { st.d[a] = start[c][a]; st.e[a] = start[c][3 + a]; }
+            record_chunk<DT>(S, B, st, cnt, smp, lane);
+          }
+          reverse_chunk<DT>(S, M, smp, cnt, rb, tb, lane);
+          if (--due == 0) {
+            chunk_end(S, M.P, lane);
+            due = WRITEOUT_CHUNKS;
+          }
         }
-      } else if (!STORED && lane_chunk) {
-        State st;
-        state_at_step(B, seg * K, st);
-        if (seg == 0) {
+      }
+    }
+  } else {
+    const int nch = wave_max_nonneg(active ? (n + CHUNK - 1) / CHUNK : 0);
+    for (int ch = nch - 1; ch >= 0; --ch) {
+      const int c0 = ch * CHUNK;  // first step of the chunk
+      const int cnt = active ? min(CHUNK, n - c0) : 0;
+      __builtin_amdgcn_s_setprio(0);
+      if (cnt > 0) {
+        if constexpr (MODE == Replay::STORED) {
+          State st[CHUNK];
 #pragma unroll
-          for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
+          for (int i = 0; i < CHUNK; ++i)
+            if (i < cnt) segment_state(S, q, c0 + i, st[i]);
+#pragma unroll
+          for (int i = 0; i < CHUNK; ++i) {
+            if (i < cnt) {
+              State s = st[i];
+              state_at_step(B, c0 + i, s);
+              record_chunk<DT>(S, B, s, 1, smp + i * 3 * 64, lane);
+            }
+          }
         } else {
-          load_ckpt(S, q, seg - 1, st);
-        }
-        // At stride 6 each step samples its own state: P live across the steps costs 29
-        // spilled registers at this kernel's 128 (1M rays: 5620 us with it carried, 5215 without).
-        constexpr bool CARRY = KS != 6;
-        constexpr StepEnd END = CARRY ? StepEnd::NEXT_SAMPLE : StepEnd::STATE;
-        Sample P;
-        if (CARRY) sample_at_state<DT>(S, B, st, P);
+          // constant for SEGMENT: with the stride read, its replay took 2 % of the adjoint more
+          const int K = MODE == Replay::SEGMENT ? CHUNK : S.ckpt_k;
+          const int seg = c0 / K, s0 = seg * K;
+          State st;
+          state_at_step(B, s0, st);
+          segment_state(S, q, seg, st);
+          if (MODE == Replay::WALK && c0 > s0) {
+            Sample P;
+            sample_at_state<DT>(S, B, st, P);
 #pragma unroll 1
-        for (int i = 0; i < ch * KS; ++i) {
-          if (!CARRY) sample_at_state<DT>(S, B, st, P);
-          sharma_step<DT, NoRecord, NoIssue, END>(S, B, st, P);  // to the chunk start
-        }
-        const int cnt = min(KS, n - c0);  // steps of the chunk (the state after the last is not needed)
-#pragma unroll 1
-        for (int i = 0;; ++i) {
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            replay[(i * 6 + a) * 64 + lane] = st.d[a];
-            replay[(i * 6 + 3 + a) * 64 + lane] = st.e[a];
+            for (int i = s0; i < c0; ++i) sharma_step<DT>(S, B, st, P);  // to the chunk's start
           }
-          if (i + 1 == cnt) break;
-          if (!CARRY) sample_at_state<DT>(S, B, st, P);
-          sharma_step<DT, NoRecord, NoIssue, END>(S, B, st, P);
+          record_chunk<DT>(S, B, st, cnt, smp, lane);
         }
       }
-      // reverse the chunk's steps, one stage at a time (C, B, A)
-#pragma unroll 1
-      for (int i = KS - 1; i >= 0; --i) {
-        const bool act = lane_chunk && (c0 + i < n);
-        // the samples of stages A and B: their forces K1, K2 locate P2 and P3 (the same
-        // arithmetic as the forward's), their derivatives serve the reverse of the stage
-        SampleRev R1, R2, R3;
-        Cell Q1;
-        float wA[3], wB[3];
-        if (act) {
-          // recompute the step's three sample points (same arithmetic as the forward)
-          State s;
-          s.jf = (float)(2 * (c0 + i));
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            s.d[a] = replay[(i * 6 + a) * 64 + lane];
-            s.e[a] = replay[(i * 6 + 3 + a) * 64 + lane];
-            s.bh[a] = fmaf(s.jf, B.g2hi[a], B.U0hi[a]);
-          }
-          float bh[3], sm[3];
-          locate_state(S, B, s, Q1);
-          sample_rev<DT>(S, Q1, R1);
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            bh[a] = s.bh[a] + B.g2hi[a];
-            sm[a] = small_part(B, a, s.jf + 1.0f, stage2_dev(S, s, a, R1.eta * R1.g[a]));  // as force_code
-          }
-          Cell Q2;
-          locate3(S, bh, sm, Q2);
-          sample_rev<DT>(S, Q2, R2);
-          Cell Q3;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            bh[a] = bh[a] + B.g2hi[a];
-            sm[a] = small_part(B, a, s.jf + 2.0f, stage3_dev(S, a, stage3_base(S, s, a), R2.eta * R2.g[a]));
-          }
-          locate3(S, bh, sm, Q3);
-          sample_rev<DT>(S, Q3, R3);
-          stage_weights(S, rb, tb, wA, wB);
-        }
-        reverse_stages(S, M, act, R1, R2, R3, wA, wB, rb, tb, lane);
-      }
-      chunk_end(S, M.P, lane);
+      reverse_chunk<DT>(S, M, smp, cnt, rb, tb, lane);
+      if (ch % WRITEOUT_CHUNKS == 0) chunk_end(S, M.P, lane);
     }
   }
   // v0 from the ray header again rather than held in registers through the sweep
@@ -351,100 +401,8 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
   drain(S, M, M.P, lane);
 }
 
-// Recording form (checkpoint strides KS = 3 and 4, one chunk per checkpoint segment): the
-// replay of a chunk keeps, for each of its steps, the record index and fractions of the
-// step's three samples as the forward located them (16 bytes per sample and lane in LDS, sample s of
-// step i of lane l at [(i * 3 + s) * 64 + l]). The reverse of a step then reads them back,
-// issues its three cell gathers together and evaluates value, gradient and mixed second
-// derivatives at exactly the forward's cells and fractions, without relocating the
-// samples from the state (no stage points, no K1 / K2, no dependent gathers).
-template <int KS>
-constexpr int rec_floats_per_wave() { return KS * 3 * 64 * 4 + PEND_SLOTS * 8; }
-
-// Chunks between two write-outs of the cache's stale slots.
-template <int KS>
-constexpr int rec_writeout_chunks() { return KS == 3 ? 3 : 2; }
-
-template <int DT, int KS>
-__device__ __forceinline__ void adjoint_tile_rec(const SceneDev& S, int tile, int lane, float* __restrict__ lds) {
-  constexpr bool PARK = rec_waves_per_simd<KS>() == 3;  // registers for the parks
-  AdjRay R;
-  adjoint_ray_setup(S, tile, lane, R);
-  const int q = R.q, n = R.n;
-  const bool active = R.active;
-  const RayBase& B = R.B;
-  float* rb = R.rb;
-  float* tb = R.tb;
-  // the launcher takes this form only for a checkpoint stride of KS: a segment is one chunk
-  const int nseg = wave_max_nonneg(active ? (n + KS - 1) / KS : 0);
-
-  CellMerge<PARK> M(lds + KS * 3 * 64 * 4);
-  f32x4* smp = reinterpret_cast<f32x4*>(lds);
-
-  for (int seg = nseg - 1; seg >= 0; --seg) {
-    const int c0 = seg * KS;  // first step of the chunk
-    const bool lane_chunk = active && c0 < n;
-    // Wave priority, lowest to highest: the replay (a chain of dependent gathers), the
-    // reverse (independent gathers, long VALU runs), the merge (serial wavefront
-    // reductions, raised in `enter`). Each ordering step measured -2 % adjoint time in
-    // alternating runs, whatever the levels.
-    __builtin_amdgcn_s_setprio(0);
-    if (lane_chunk) {
-      State st;
-      state_at_step(B, c0, st);
-      if (seg == 0) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
-      } else {
-        load_ckpt(S, q, seg - 1, st);
-      }
-      // the chunk's steps, the last one only up to its third sample
-      const int cnt = min(KS, n - c0);
-      Sample P;
-      sample_at_state<DT>(S, B, st, P);
-#pragma unroll 1
-      for (int i = 0; i < cnt - 1; ++i) sharma_step<DT>(S, B, st, P, SampleRow{smp + i * 3 * 64 + lane});
-      sharma_step<DT, SampleRow, NoIssue, StepEnd::SAMPLES>(S, B, st, P, SampleRow{smp + (cnt - 1) * 3 * 64 + lane});
-    }
-    // reverse the chunk's steps, one stage at a time (C, B, A)
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll  // one copy per step: 1 % faster than the rolled loop, same registers
-    for (int i = KS - 1; i >= 0; --i) {
-      const bool act = lane_chunk && (c0 + i < n);
-      SampleRev R1, R2, R3;
-      float wA[3], wB[3];
-      if (act) {
-        const f32x4* row = smp + i * 3 * 64 + lane;
-        const f32x4 s1 = row[0], s2 = row[64], s3 = row[128];
-        const unsigned r1 = __float_as_uint(s1.x), r2 = __float_as_uint(s2.x), r3 = __float_as_uint(s3.x);
-        float c1[8], c2[8], c3[8];
-        fetch_cell<DT>(S, r3, c3);
-        fetch_cell<DT>(S, r2, c2);
-        fetch_cell<DT>(S, r1, c1);
-        const float f3[3] = {s3.y, s3.z, s3.w}, f2[3] = {s2.y, s2.z, s2.w}, f1[3] = {s1.y, s1.z, s1.w};
-        sample_rev_at(S, c3, r3, f3, R3);
-        sample_rev_at(S, c2, r2, f2, R2);
-        sample_rev_at(S, c1, r1, f1, R1);
-        stage_weights(S, rb, tb, wA, wB);
-      }
-      reverse_stages(S, M, act, R1, R2, R3, wA, wB, rb, tb, lane);
-    }
-    // stale slots go out every ~8 steps: each write-out exposes its atomics' latency once,
-    // and at every chunk of 3 steps that cost showed (-2 % adjoint time at 9 steps; at 12 or
-    // more the cache fills and misses write slots out one at a time)
-    if (seg % rec_writeout_chunks<KS>() == 0) chunk_end(S, M.P, lane);
-  }
-  float V0[3] = {0.0f, 0.0f, 0.0f};
-  if (active) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) V0[a] = gld(S.ckpt + (size_t)q + (size_t)(12 + a) * (size_t)S.ckpt_pad);
-  }
-  entry_term(S, B, V0, active, tb, M, lane);
-  drain(S, M, M.P, lane);
-}
-
-template <int DT, int KS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rec_waves_per_simd<KS>()))) void k_trace_adj_rec(
+template <int DT, Replay MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_adj(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -452,17 +410,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rec_waves_p
   const int si = find_scene(scenes, n_scenes, gtile);
   const SceneDev& S = scenes[si];
   extern __shared__ float lds[];
-  adjoint_tile_rec<DT, KS>(S, gtile - S.tile_begin, lane, lds + wave * rec_floats_per_wave<KS>());
+  adjoint_tile<DT, MODE>(S, gtile - S.tile_begin, lane, lds + wave * adj_floats_per_wave());
 }
 
-template <int DT, int KS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rec_waves_per_simd<KS>()))) void k_trace_adj_rec_persistent(
+template <int DT, Replay MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_adj_persistent(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, unsigned int* __restrict__ queues,
     const int* __restrict__ order) {
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
   const int xcd = blockIdx.x & 7;
   extern __shared__ float lds[];
-  float* mine = lds + wave * rec_floats_per_wave<KS>();
+  float* mine = lds + wave * adj_floats_per_wave();
   for (int q = 0; q < 8; ++q) {
     const int qx = (xcd + q) & 7;
     int q_begin, q_end;
@@ -475,23 +433,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rec_waves_p
       t = wave_uniform(gld(order + t));
       const int si = find_scene(scenes, n_scenes, t);
       const SceneDev& S = scenes[si];
-      adjoint_tile_rec<DT, KS>(S, t - S.tile_begin, lane, mine);
+      adjoint_tile<DT, MODE>(S, t - S.tile_begin, lane, mine);
     }
   }
 }
 
-template <int DT, int KS>
-static hipError_t launch_adj_rec(const LaunchPlan& P, hipStream_t stream) {
-  if (P.ckpt_k != KS) return hipErrorInvalidValue;  // one chunk per checkpoint segment
-  const size_t lds = sizeof(float) * rec_floats_per_wave<KS>() * (size_t)P.wpb;
+template <int DT, Replay MODE>
+static hipError_t launch_adj_mode(const LaunchPlan& P, hipStream_t stream) {
+  const size_t lds = sizeof(float) * adj_floats_per_wave() * (size_t)P.wpb;
   if (P.persistent) {
-    const int grid = persistent_grid(k_trace_adj_rec_persistent<DT, KS>, P, lds);
-    hipLaunchKernelGGL((k_trace_adj_rec_persistent<DT, KS>), dim3(grid), dim3(64 * P.wpb), lds, stream, P.scenes,
+    const int grid = persistent_grid(k_trace_adj_persistent<DT, MODE>, P, lds);
+    hipLaunchKernelGGL((k_trace_adj_persistent<DT, MODE>), dim3(grid), dim3(64 * P.wpb), lds, stream, P.scenes,
                        P.n_scenes, P.total_tiles, P.queues, P.tile_order);
   } else {
     int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_adj_rec<DT, KS>), dim3(nblocks), dim3(64 * P.wpb), lds, stream, P.scenes,
-                       P.n_scenes, P.total_tiles, P.wpb, nblocks);
+    hipLaunchKernelGGL((k_trace_adj<DT, MODE>), dim3(nblocks), dim3(64 * P.wpb), lds, stream, P.scenes, P.n_scenes,
+                       P.total_tiles, P.wpb, nblocks);
   }
   return hipGetLastError();
 }
@@ -596,68 +553,17 @@ static hipError_t launch_adj_ql(const LaunchPlan& P, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int DT, int KS, bool STORED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<KS>()))) void k_trace_adj(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
-  const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
-  if (gtile >= total_tiles) return;  // whole wavefront
-  const int si = find_scene(scenes, n_scenes, gtile);
-  const SceneDev& S = scenes[si];
-  extern __shared__ float lds[];
-  adjoint_tile<DT, KS, STORED>(S, gtile - S.tile_begin, lane, lds + wave * lds_floats_per_wave<KS>());
-}
-
-template <int DT, int KS, bool STORED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<KS>()))) void k_trace_adj_persistent(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, unsigned int* __restrict__ queues,
-    const int* __restrict__ order) {
-  const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
-  const int xcd = blockIdx.x & 7;
-  extern __shared__ float lds[];
-  float* replay = lds + wave * lds_floats_per_wave<KS>();
-  for (int q = 0; q < 8; ++q) {
-    const int qx = (xcd + q) & 7;
-    int q_begin, q_end;
-    xcd_tile_range(total_tiles, qx, q_begin, q_end);
-    while (true) {
-      int t = 0;
-      if (lane == 0) t = (int)atomicAdd(&queues[8 + qx], 1u);
-      t = wave_uniform(t) + q_begin;  // lane 0's claim (all lanes active)
-      if (t >= q_end) break;
-      t = wave_uniform(gld(order + t));
-      const int si = find_scene(scenes, n_scenes, t);
-      const SceneDev& S = scenes[si];
-      adjoint_tile<DT, KS, STORED>(S, t - S.tile_begin, lane, replay);
-    }
-  }
-}
-
-template <int DT, int KS, bool STORED>
-static hipError_t launch_adj_t(const LaunchPlan& P, hipStream_t stream) {
-  const size_t lds = sizeof(float) * lds_floats_per_wave<KS>() * (size_t)P.wpb;
-  if (P.persistent) {
-    const int grid = persistent_grid(k_trace_adj_persistent<DT, KS, STORED>, P, lds);
-    hipLaunchKernelGGL((k_trace_adj_persistent<DT, KS, STORED>), dim3(grid), dim3(64 * P.wpb), lds, stream,
-                       P.scenes, P.n_scenes, P.total_tiles, P.queues, P.tile_order);
-  } else {
-    int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_adj<DT, KS, STORED>), dim3(nblocks), dim3(64 * P.wpb), lds, stream, P.scenes,
-                       P.n_scenes, P.total_tiles, P.wpb, nblocks);
-  }
-  return hipGetLastError();
-}
-
 template <int DT>
 static hipError_t launch_adj_dt(const LaunchPlan& P, hipStream_t stream) {
   if (P.tracer == 1) return launch_adj_ql<DT>(P, stream);
-  // chunks of step-start states in LDS: stride 1 fills chunks of 8 from the checkpoints,
-  // stride 6 replays chunks of 6, strides 8, 16, ... chunks of 8
-  if (P.ckpt_k == 1) return launch_adj_t<DT, 8, true>(P, stream);
-  if (P.ckpt_k == 3) return launch_adj_rec<DT, 3>(P, stream);
-  if (P.ckpt_k == 4) return launch_adj_rec<DT, 4>(P, stream);
-  if (P.ckpt_k == 6) return launch_adj_t<DT, 6, false>(P, stream);
-  return launch_adj_t<DT, 8, false>(P, stream);
+  if (P.ckpt_k == 1) return launch_adj_mode<DT, Replay::STORED>(P, stream);
+  if (P.ckpt_k == CHUNK) return launch_adj_mode<DT, Replay::SEGMENT>(P, stream);
+  // up to stride 6 a chunk's start is 1.5 steps from a checkpoint on average; a pass that
+  // leaves the starts replays as many but for each segment's last chunk, which it cuts short
+  // (1M rays, stride 4: 4990 us this way, 5660 with the pass; stride 6: 4860, 5140). From 8
+  // on the walks are the longer way (3.5 steps per chunk of 3, growing with the stride).
+  if (P.ckpt_k <= 6) return launch_adj_mode<DT, Replay::WALK>(P, stream);
+  return launch_adj_mode<DT, Replay::CHUNKS>(P, stream);
 }
 
 // Processing order of the persistent adjoint. A tile's reverse sweep lasts as long as

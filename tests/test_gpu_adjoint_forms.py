@@ -63,6 +63,13 @@ def test_every_chunk_form(name, ckpt):
     _check(WORKLOADS[name](), name, ckpt=ckpt)
 
 
+@pytest.mark.parametrize("ckpt", [32, 40, 256])
+@pytest.mark.parametrize("persistent", [False, True])
+def test_strides_of_several_parts(ckpt, persistent):
+    """Segments longer than the 24 steps whose chunk starts the coherent form keeps at once."""
+    _check(WORKLOADS["coherent"](), "coherent", ckpt=ckpt, launch=api.make_launch((8, 8), 4, persistent))
+
+
 @pytest.mark.parametrize("name", ["one-tile", "pixel-list", "many-sparse"])
 @pytest.mark.parametrize("ckpt", [3, 16])
 def test_sparse_rays(name, ckpt):
