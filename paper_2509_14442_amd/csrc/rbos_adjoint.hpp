@@ -49,15 +49,20 @@ __device__ __forceinline__ void sample_rev(const SceneDev& S, const Cell& C, Sam
 // the totals (corner_of_monomials, scaled by 1 / dec). In apron cells the field is
 // constant along the clamped axis (g and H vanish there); the two corners that share one
 // edge voxel receive contributions that add up to the clamped-axis weights.
-__device__ __forceinline__ void force_rev(const SceneDev& S, const SampleRev& R, const float w[3], float p[3],
-                                          float acc[8]) {
+// force_terms returns p and (s, W); add_terms adds their coefficients.
+__device__ __forceinline__ f32x4 force_terms(const SceneDev& S, const SampleRev& R, const float w[3], float p[3]) {
   const float s = S.dec * fmaf(w[0], R.g[0], fmaf(w[1], R.g[1], w[2] * R.g[2]));
   const float Wx = R.eta * w[0], Wy = R.eta * w[1], Wz = R.eta * w[2];
   // H = (H_xy, H_xz, H_yz)
   p[0] = fmaf(s, R.g[0], fmaf(Wy, R.H[0], Wz * R.H[1]));
   p[1] = fmaf(s, R.g[1], fmaf(Wx, R.H[0], Wz * R.H[2]));
   p[2] = fmaf(s, R.g[2], fmaf(Wx, R.H[1], Wy * R.H[2]));
-  const float u = R.f[0], v = R.f[1], x = R.f[2];
+  return f32x4{s, Wx, Wy, Wz};
+}
+
+__device__ __forceinline__ void add_terms(const float f[3], f32x4 t, float acc[8]) {
+  const float s = t.x, Wx = t.y, Wy = t.z, Wz = t.w;
+  const float u = f[0], v = f[1], x = f[2];
   const float m1 = fmaf(s, u, Wx);              // u:   s u + Wx
   const float m2 = fmaf(s, v, Wy);              // v:   s v + Wy
   const float m3 = fmaf(v, m1, Wy * u);         // uv:  s uv + Wx v + Wy u
@@ -69,6 +74,11 @@ __device__ __forceinline__ void force_rev(const SceneDev& S, const SampleRev& R,
   acc[5] = fmaf(x, m1, fmaf(Wz, u, acc[5]));    // uw:  s uw + Wx w + Wz u
   acc[6] = fmaf(x, m2, fmaf(Wz, v, acc[6]));    // vw:  s vw + Wy w + Wz v
   acc[7] = fmaf(x, m3, fmaf(Wz, u * v, acc[7]));  // uvw: s uvw + Wx vw + Wy uw + Wz uv
+}
+
+__device__ __forceinline__ void force_rev(const SceneDev& S, const SampleRev& R, const float w[3], float p[3],
+                                          float acc[8]) {
+  add_terms(R.f, force_terms(S, R, w, p), acc);
 }
 
 constexpr int CELL_NONE = INT_MIN;  // no cell (record indices are < 2^27)
@@ -259,7 +269,7 @@ __device__ __forceinline__ void stage_weights(const SceneDev& S, const float rb[
 // Stages C, B, A of the reverse (lanes with act), each sample's contributions into the
 // accumulators of its cell; rb, tb become the adjoints before the step. The merge M takes
 // the samples: M.enter(S, act, act_m, key, lane) when lanes with act (ballot act_m) come to
-// a sample in cell `key`, whose coefficients are then added to M.acc.
+// a sample in cell `key`, then M.take(S, sample of the step, R, w, p) for its force_rev.
 template <class Merge>
 __device__ __forceinline__ void reverse_stages(const SceneDev& S, Merge& M, bool act,
                                                const SampleRev& R1, const SampleRev& R2, const SampleRev& R3,
@@ -271,7 +281,7 @@ __device__ __forceinline__ void reverse_stages(const SceneDev& S, Merge& M, bool
     float w[3], p[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) w[a] = S.c_v[a] * tb[a];
-    force_rev(S, R3, w, p, M.acc);
+    M.take(S, 2, R3, w, p);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       rs[a] = rb[a] + p[a];
@@ -282,7 +292,7 @@ __device__ __forceinline__ void reverse_stages(const SceneDev& S, Merge& M, bool
   M.enter(S, act, act_m, act ? R2.key : 0, lane);
   if (act) {  // stage B
     float p[3];
-    force_rev(S, R2, wB, p, M.acc);
+    M.take(S, 1, R2, wB, p);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       rs[a] += p[a];
@@ -293,7 +303,7 @@ __device__ __forceinline__ void reverse_stages(const SceneDev& S, Merge& M, bool
   M.enter(S, act, act_m, act ? R1.key : 0, lane);
   if (act) {  // stage A
     float p[3];
-    force_rev(S, R1, wA, p, M.acc);
+    M.take(S, 0, R1, wA, p);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       rb[a] = rs[a] + p[a];

@@ -199,6 +199,9 @@ struct CellMerge : Accum {
   __device__ __forceinline__ void enter(const SceneDev& S, bool act, unsigned long long act_m, int k, int lane) {
     rbos::enter<PARK>(S, *this, act, act_m, k, lane, P);
   }
+  __device__ __forceinline__ void take(const SceneDev& S, int, const SampleRev& R, const float w[3], float p[3]) {
+    force_rev(S, R, w, p, acc);
+  }
 };
 
 // How a chunk of the reverse gets its steps' states.

@@ -203,6 +203,9 @@ struct QueueMerge {
     if (out_m) push(S, out, out_m, lane);
     if (act) key = k;
   }
+  __device__ __forceinline__ void take(const SceneDev& S, int, const SampleRev& R, const float w[3], float p[3]) {
+    force_rev(S, R, w, p, acc);
+  }
 
   // Entries and slots go out where the caller has its next gathers issued, so that the
   // atomics' latency runs beside the arithmetic of a step.
@@ -327,6 +330,179 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds, plan);
 }
 
+// With few tiles a wavefront's instruction stream is the whole time while three of four SIMDs
+// idle. So a tile takes a block of four wavefronts, one per SIMD of a compute unit, each with
+// its own part of the work on successive chunks of 6 or 8 steps: one replays a chunk's samples
+// into LDS; one reverses the chunk after it (the adjoint of the ray alone: it leaves each
+// sample's s and W); two sum the samples of the chunk after that, half of its steps each,
+// every one with a queue and a table of its own. Each sum into a voxel is made by the same
+// operations as in the form of one wavefront.
+//
+// Bound by the summing wavefronts' instructions (96 x 96 rays, 128^3, stride 3: 520 us; without
+// their inserts 271, without any sums 260, the replay alone 247; one wavefront per tile 1098).
+// 64 x 64 rays of the unit box: 182 -> 102 us; 8192 random pixels: 1082 -> 624. Three summing
+// wavefronts take 446 us of the 520, but 738 for the random pixels: consecutive cells of a ray
+// then more often meet in different tables, and more atomics follow.
+struct ChainTerms {
+  f32x4* row;  // the step's terms: sample s at row[s * 64]
+  __device__ __forceinline__ void enter(const SceneDev&, bool, unsigned long long, int, int) {}
+  __device__ __forceinline__ void take(const SceneDev& S, int sample, const SampleRev& R, const float w[3],
+                                       float p[3]) {
+    row[sample * 64] = force_terms(S, R, w, p);
+  }
+};
+
+// All wavefronts of the block; orders LDS only: gathers and atomics stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int KS>
+constexpr int pipe_rows() { return KS * 3 * 64; }  // samples of a chunk
+constexpr int PIPE_SUMS = 2;  // wavefronts that sum
+
+template <int DT, int KS>
+__device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, int wave, int lane, float* lds,
+                                                  const QueuePlan& plan) {
+  constexpr int ROWS = pipe_rows<KS>();
+  f32x4* const samples = reinterpret_cast<f32x4*>(lds) + lane;  // ring of 3 chunks
+  f32x4* const terms = samples + 3 * ROWS;                      // ring of 2 chunks
+  float* const entry = lds + 5 * ROWS * 4 + lane;               // the chain's last tb
+  float* const queues = lds + 5 * ROWS * 4 + 3 * 64;
+  AdjRay R;
+  adjoint_ray_setup(S, tile, lane, R);
+  const int q = R.q, n = R.n;
+  const bool active = R.active;
+  const RayBase& B = R.B;
+  const int K = S.ckpt_k;
+  // the same in every wavefront; each passes nch + 1 barriers, at the ends of rounds 0 .. nch
+  const int nch = max(1, wave_max_nonneg(active ? (n + KS - 1) / KS : 0));
+
+  if (wave == 0) {
+    // reverse chunk nch - r in round r
+    lds_barrier();
+#pragma unroll 1
+    for (int r = 1; r <= nch; ++r) {
+      const int ch = nch - r;
+      const int cnt = active ? min(KS, n - ch * KS) : 0;
+      const f32x4* rows = samples + (r - 1) % 3 * ROWS;
+      f32x4* out = terms + (r & 1) * ROWS;
+      StepRows cur;
+      if (KS - 1 < cnt) load_rows<DT>(S, rows + (KS - 1) * 3 * 64, cur);
+#pragma unroll 1
+      for (int i = KS - 1; i >= 0; --i) {
+        const bool act = i < cnt;
+        SampleRev R1, R2, R3;
+        float wA[3], wB[3];
+        if (act) {
+          sample_rev_at(S, cur.c[2], cur.rec[2], cur.f[2], R3);
+          sample_rev_at(S, cur.c[1], cur.rec[1], cur.f[1], R2);
+          sample_rev_at(S, cur.c[0], cur.rec[0], cur.f[0], R1);
+          stage_weights(S, R.rb, R.tb, wA, wB);
+        }
+        if (i > 0 && i - 1 < cnt) load_rows<DT>(S, rows + (i - 1) * 3 * 64, cur);
+        ChainTerms M{out + i * 3 * 64};
+        reverse_stages(S, M, act, R1, R2, R3, wA, wB, R.rb, R.tb, lane);
+      }
+      if (r == nch) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) entry[a * 64] = R.tb[a];
+      }
+      lds_barrier();
+    }
+    return;
+  }
+  if (wave == 1) {
+    // replay chunk nch - 1 - r in round r
+    State st;
+    Ahead P;
+    auto start = [&](int ch) {
+      const int c0 = ch * KS, k0 = c0 / K * K;
+      if (!active || c0 >= n) return;
+      state_at_step(B, k0, st);
+      if (k0 == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { st.d[a] = 0.0f; st.e[a] = 0.0f; }
+      } else {
+        load_ckpt(S, q, k0 / K - 1, st);
+      }
+      start_ahead<DT>(S, B, st, P);
+    };
+    start(nch - 1);
+#pragma unroll 1
+    for (int r = 0; r < nch; ++r) {
+      const int ch = nch - 1 - r;
+      const int cnt = active ? min(KS, n - ch * KS) : 0;
+      f32x4* rows = samples + r % 3 * ROWS;
+      if (cnt > 0) {
+#pragma unroll 1
+        for (int i = ch * KS % K; i > 0; --i) sharma_step_ahead<DT>(S, B, st, P);
+#pragma unroll 1
+        for (int i = 0; i < cnt - 1; ++i) sharma_step_ahead<DT>(S, B, st, P, SampleRow{rows + i * 3 * 64});
+        sharma_step_ahead<DT, SampleRow, NoIssue, false>(S, B, st, P, SampleRow{rows + (cnt - 1) * 3 * 64});
+      }
+      if (ch > 0) start(ch - 1);
+      lds_barrier();
+    }
+    lds_barrier();
+    return;
+  }
+  // sum chunk nch + 1 - r in round r
+  const int share = wave - 2;  // 0: the chunk's first steps
+  QueueMerge M(queues + (size_t)share * (plan.bytes() / 4), plan, lane);
+  const int i0 = KS * share / PIPE_SUMS, i1 = KS * (share + 1) / PIPE_SUMS;
+  lds_barrier();
+  lds_barrier();
+#pragma unroll 1
+  for (int r = 2; r <= nch + 1; ++r) {
+    const int ch = nch + 1 - r;
+    const int cnt = active ? min(KS, n - ch * KS) : 0;
+    const f32x4* rows = samples + (r - 2) % 3 * ROWS;
+    const f32x4* in = terms + ((r - 1) & 1) * ROWS;
+#pragma unroll 1
+    for (int i = i1 - 1; i >= i0; --i) {
+      const bool act = i < cnt;
+      const unsigned long long act_m = __ballot(act);
+      if (act_m == 0) continue;
+      f32x4 row[3], t[3];
+      if (act) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          row[s] = rows[(i * 3 + s) * 64];
+          t[s] = in[(i * 3 + s) * 64];
+        }
+      }
+      M.ease(S, lane);
+#pragma unroll
+      for (int s = 2; s >= 0; --s) {
+        M.enter(S, act, act_m, act ? (int)__float_as_uint(row[s].x) : 0, lane);
+        if (act) {
+          const float f[3] = {row[s].y, row[s].z, row[s].w};
+          add_terms(f, t[s], M.acc);
+        }
+      }
+    }
+    if (r <= nch) lds_barrier();
+  }
+  if (share == 0) {
+    const float tb[3] = {entry[0], entry[64], entry[128]};
+    entry_term(S, B, B.V, active, tb, M, lane);
+  }
+  M.drain(S, lane);
+}
+
+template <int DT, int KS>
+__global__ __launch_bounds__(64 * (2 + PIPE_SUMS)) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_pipe(
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+  extern __shared__ float lds[];
+  const int gtile = xcd_remap(blockIdx.x, total_tiles);
+  const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
+  adjoint_tile_pipe<DT, KS>(S, gtile - S.tile_begin, wave_uniform(threadIdx.x >> 6), threadIdx.x & 63, lds, plan);
+}
+
 // Quasi-linear tracer: the line points j = 0 .. 2n are independent of each other, so a
 // tile's range of them is shared out over `parts` wavefronts. The entry term is linear in
 // the adjoint of the entry velocity: each part adds its own share.
@@ -435,6 +611,24 @@ bool adjoint_by_queue(const LaunchPlan& P) {
   return P.total_tiles <= per_cu * P.n_cus || P.rays_per_cell < 6.0f;
 }
 
+// A block of the four-wavefront form takes a compute unit's LDS: as many tiles as units run at
+// once, twice as many in turn, where it still is the faster form more often than not. Adjoint,
+// one wavefront per tile / four, us: 128^3 room, stride 3, 36 tiles 1106 / 540, 256 tiles 1080
+// / 538, 484 tiles 1098 / 981, 900 tiles 1225 / 1817; 96^3, 484 tiles 820 / 1030; 128^3, stride
+// 16, 144 tiles 1184 / 522, 484 tiles 1187 / 976; 64^3, stride 4, 256 tiles 510 / 288, 484
+// tiles 528 / 450; 32^3, stride 3, 484 tiles 246 / 217.
+static bool adjoint_by_pipe(const LaunchPlan& P) { return P.tracer != 1 && P.total_tiles <= 2 * P.n_cus; }
+
+template <int DT, int KS>
+static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
+  QueuePlan plan = queue_plan(P);
+  plan.table.bits[P.view_axis] = 3;  // half a chunk's steps each; 16 slots along the view gain nothing (538, 517 us)
+  const size_t lds = (size_t)pipe_rows<KS>() * 5 * 16 + 3 * 64 * 4 + PIPE_SUMS * plan.bytes();
+  hipLaunchKernelGGL((k_trace_adj_pipe<DT, KS>), dim3(P.total_tiles), dim3(64 * (2 + PIPE_SUMS)), lds, stream, P.scenes,
+                     P.n_scenes, P.total_tiles, plan);
+  return hipGetLastError();
+}
+
 template <int DT, int KS>
 static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
   const QueuePlan plan = queue_plan(P);
@@ -452,6 +646,8 @@ static hipError_t launch_queue_dt(const LaunchPlan& P, hipStream_t stream) {
                        P.n_scenes, P.total_tiles, parts, plan);
     return hipGetLastError();
   }
+  if (adjoint_by_pipe(P))
+    return P.ckpt_k == 3 || P.ckpt_k == 6 ? launch_pipe_t<DT, 6>(P, stream) : launch_pipe_t<DT, 8>(P, stream);
   switch (queue_chunk(P)) {
     case 3: return launch_queue_t<DT, 3>(P, stream);
     case 4: return launch_queue_t<DT, 4>(P, stream);

@@ -76,6 +76,13 @@ def test_sparse_rays(name, ckpt):
     _check(WORKLOADS[name](), name, ckpt=ckpt)
 
 
+@pytest.mark.parametrize("ckpt", [1, 4, 6, 8])
+def test_sparse_rays_one_wavefront_per_tile(ckpt):
+    """600 tiles: beyond the form of four wavefronts per tile, each chunk length of the other."""
+    w = room_workload((96, 88, 80), 160, 240, seed=9, max_steps=1024, pat=256)
+    _check(w, "sparse", ckpt=ckpt)
+
+
 @pytest.mark.parametrize("name", list(WORKLOADS))
 def test_quasilinear(name):
     _check(WORKLOADS[name](), name, tracer=1)
