@@ -2,7 +2,7 @@
 // back-propagated through the wall step and every Sharma step of Eq. (1).
 //
 // Per wavefront (64 rays of one tile), the steps are processed from the last to the first
-// in chunks of 3, aligned on the step index so that the tile's rays move through the same
+// in chunks of 3 or 4, aligned on the step index so that the tile's rays move through the same
 // cells together. A chunk is replayed forward from a state at its start (a checkpoint, or one
 // reached from there), keeping in LDS the cells and fractions of each step's three samples,
 // and then reversed step by step. Each
@@ -207,8 +207,8 @@ struct CellMerge : Accum {
 // How a chunk of the reverse gets its steps' states.
 enum class Replay {
   STORED,   // stride 1: every step's start state is a checkpoint
-  SEGMENT,  // stride 3: a segment is one chunk, replayed from its checkpoint
-  WALK,     // strides 4 and 6: each chunk from the checkpoint before it, over steps in between
+  SEGMENT,  // strides 3 and 4: a segment is one chunk, replayed from its checkpoint
+  WALK,     // stride 6: each chunk from the checkpoint before it, over the steps in between
   CHUNKS,   // longer strides: a pass over the segment leaves its chunks' start states
 };
 
@@ -218,7 +218,8 @@ enum class Replay {
 // them back, issues its three cell gathers together and evaluates value, gradient and mixed
 // second derivatives at exactly the forward's cells and fractions, without relocating the
 // samples from the state (no stage points, no K1 / K2, no dependent gathers). Chunks of 3
-// steps take 10 KB of LDS per wavefront: 4 wavefronts per SIMD, registers held to 128.
+// steps take 10 KB of LDS per wavefront: 4 wavefronts per SIMD, registers held to 128; chunks
+// of 4 take 13 KB: 3 per SIMD.
 //
 // With CHUNKS the start states of a part's chunks lie in a private array (24 bytes per
 // chunk, coalesced, mostly in the L2): a part's steps run twice, where replays from the
@@ -226,19 +227,27 @@ enum class Replay {
 //
 // Bound by VALU issue. 1M rays, adjoint, against chunks of 8 (stride 6: of 6) step states in
 // LDS, whose samples the reverse located again, at 3 (4) wavefronts per SIMD: stride 1 4910 ->
-// 4610 us, 6 5290 -> 4860, 8 6050 -> 5390, 16 6640 -> 5500; stride 4, recorded before too, by
-// 4 at 3 wavefronts per SIMD: 5130 -> 4990; stride 3: 4390 -> 4310. 512 x 512 rays, stride 16: 2900 -> 2000, since its
-// 4096 wavefronts now reside at once.
-constexpr int CHUNK = 3;
-constexpr int CHUNK_FLOATS = CHUNK * 3 * 64 * 4;
+// 4610 us, 6 5290 -> 4860, 8 6050 -> 5390, 16 6640 -> 5500. 512 x 512 rays, stride 16: 2900 ->
+// 2010, since its 4096 wavefronts now reside at once.
 constexpr int PART_CHUNKS = 8;  // chunks of a part: strides up to 24 are one part
 
-constexpr int adj_floats_per_wave() { return CHUNK_FLOATS + PEND_SLOTS * 8; }
+template <int CHUNK>
+constexpr int chunk_floats() { return CHUNK * 3 * 64 * 4; }
+
+template <int CHUNK>
+constexpr int adj_floats_per_wave() { return chunk_floats<CHUNK>() + PEND_SLOTS * 8; }
+
+template <int CHUNK>
+constexpr int adj_waves_per_simd() { return CHUNK == 3 ? 4 : 3; }
+
+template <int CHUNK>
+constexpr bool adj_park() { return CHUNK != 3; }  // registers for the parks
 
 // Chunks between two write-outs of the cache's stale slots: each write-out exposes its
 // atomics' latency once, and at every chunk of 3 steps that cost showed (-2 % adjoint time at
 // 9 steps; at 12 or more the cache fills and misses write slots out one at a time).
-constexpr int WRITEOUT_CHUNKS = 3;
+template <int CHUNK>
+constexpr int writeout_chunks() { return CHUNK == 3 ? 3 : 2; }
 
 // The state at a segment's first step: the entry state or the checkpoint before it.
 __device__ __forceinline__ void segment_state(const SceneDev& S, int q, int seg, State& st) {
@@ -262,8 +271,8 @@ __device__ __forceinline__ void record_chunk(const SceneDev& S, const RayBase& B
 }
 
 // Reverse of one chunk, from the samples in LDS: steps c0 + cnt - 1 .. c0 of lanes with cnt > 0.
-template <int DT>
-__device__ __forceinline__ void reverse_chunk(const SceneDev& S, CellMerge<false>& M, const f32x4* smp, int cnt,
+template <int DT, int CHUNK>
+__device__ __forceinline__ void reverse_chunk(const SceneDev& S, CellMerge<adj_park<CHUNK>()>& M, const f32x4* smp, int cnt,
                                               float rb[3], float tb[3], int lane) {
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll  // one copy per step: 1 % faster than the rolled loop, same registers
@@ -293,7 +302,7 @@ __device__ __forceinline__ void reverse_chunk(const SceneDev& S, CellMerge<false
 // (independent gathers, long VALU runs), the merge (serial wavefront reductions, raised in
 // `enter`). Each ordering step measured -2 % adjoint time in alternating runs, whatever the
 // levels.
-template <int DT, Replay MODE>
+template <int DT, Replay MODE, int CHUNK>
 __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int lane, float* __restrict__ lds) {
   AdjRay R;
   adjoint_ray_setup(S, tile, lane, R);
@@ -302,14 +311,14 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
   const RayBase& B = R.B;
   float* rb = R.rb;
   float* tb = R.tb;
-  CellMerge<false> M(lds + CHUNK_FLOATS);
+  CellMerge<adj_park<CHUNK>()> M(lds + chunk_floats<CHUNK>());
   f32x4* smp = reinterpret_cast<f32x4*>(lds);
 
   if constexpr (MODE == Replay::CHUNKS) {
     const int K = S.ckpt_k;
     const int part_len = min(K, CHUNK * PART_CHUNKS);
     const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
-    int due = WRITEOUT_CHUNKS;
+    int due = writeout_chunks<CHUNK>();
     for (int seg = nseg - 1; seg >= 0; --seg) {
       for (int p0 = ((K - 1) / part_len) * part_len; p0 >= 0; p0 -= part_len) {
         const int s0 = seg * K + p0;                            // first step of the part
@@ -346,10 +355,10 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
             for (int a = 0; a < 3; ++a) { st.d[a] = start[c][a]; st.e[a] = start[c][3 + a]; }
             record_chunk<DT>(S, B, st, cnt, smp, lane);
           }
-          reverse_chunk<DT>(S, M, smp, cnt, rb, tb, lane);
+          reverse_chunk<DT, CHUNK>(S, M, smp, cnt, rb, tb, lane);
           if (--due == 0) {
             chunk_end(S, M.P, lane);
-            due = WRITEOUT_CHUNKS;
+            due = writeout_chunks<CHUNK>();
           }
         }
       }
@@ -390,8 +399,8 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
           record_chunk<DT>(S, B, st, cnt, smp, lane);
         }
       }
-      reverse_chunk<DT>(S, M, smp, cnt, rb, tb, lane);
-      if (ch % WRITEOUT_CHUNKS == 0) chunk_end(S, M.P, lane);
+      reverse_chunk<DT, CHUNK>(S, M, smp, cnt, rb, tb, lane);
+      if (ch % writeout_chunks<CHUNK>() == 0) chunk_end(S, M.P, lane);
     }
   }
   // v0 from the ray header again rather than held in registers through the sweep
@@ -404,8 +413,8 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
   drain(S, M, M.P, lane);
 }
 
-template <int DT, Replay MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_adj(
+template <int DT, Replay MODE, int CHUNK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CHUNK>()))) void k_trace_adj(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -413,17 +422,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int si = find_scene(scenes, n_scenes, gtile);
   const SceneDev& S = scenes[si];
   extern __shared__ float lds[];
-  adjoint_tile<DT, MODE>(S, gtile - S.tile_begin, lane, lds + wave * adj_floats_per_wave());
+  adjoint_tile<DT, MODE, CHUNK>(S, gtile - S.tile_begin, lane, lds + wave * adj_floats_per_wave<CHUNK>());
 }
 
-template <int DT, Replay MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_adj_persistent(
+template <int DT, Replay MODE, int CHUNK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CHUNK>()))) void k_trace_adj_persistent(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, unsigned int* __restrict__ queues,
     const int* __restrict__ order) {
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
   const int xcd = blockIdx.x & 7;
   extern __shared__ float lds[];
-  float* mine = lds + wave * adj_floats_per_wave();
+  float* mine = lds + wave * adj_floats_per_wave<CHUNK>();
   for (int q = 0; q < 8; ++q) {
     const int qx = (xcd + q) & 7;
     int q_begin, q_end;
@@ -436,21 +445,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       t = wave_uniform(gld(order + t));
       const int si = find_scene(scenes, n_scenes, t);
       const SceneDev& S = scenes[si];
-      adjoint_tile<DT, MODE>(S, t - S.tile_begin, lane, mine);
+      adjoint_tile<DT, MODE, CHUNK>(S, t - S.tile_begin, lane, mine);
     }
   }
 }
 
-template <int DT, Replay MODE>
+template <int DT, Replay MODE, int CHUNK>
 static hipError_t launch_adj_mode(const LaunchPlan& P, hipStream_t stream) {
-  const size_t lds = sizeof(float) * adj_floats_per_wave() * (size_t)P.wpb;
+  const size_t lds = sizeof(float) * adj_floats_per_wave<CHUNK>() * (size_t)P.wpb;
   if (P.persistent) {
-    const int grid = persistent_grid(k_trace_adj_persistent<DT, MODE>, P, lds);
-    hipLaunchKernelGGL((k_trace_adj_persistent<DT, MODE>), dim3(grid), dim3(64 * P.wpb), lds, stream, P.scenes,
+    const int grid = persistent_grid(k_trace_adj_persistent<DT, MODE, CHUNK>, P, lds);
+    hipLaunchKernelGGL((k_trace_adj_persistent<DT, MODE, CHUNK>), dim3(grid), dim3(64 * P.wpb), lds, stream, P.scenes,
                        P.n_scenes, P.total_tiles, P.queues, P.tile_order);
   } else {
     int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_adj<DT, MODE>), dim3(nblocks), dim3(64 * P.wpb), lds, stream, P.scenes, P.n_scenes,
+    hipLaunchKernelGGL((k_trace_adj<DT, MODE, CHUNK>), dim3(nblocks), dim3(64 * P.wpb), lds, stream, P.scenes, P.n_scenes,
                        P.total_tiles, P.wpb, nblocks);
   }
   return hipGetLastError();
@@ -584,14 +593,23 @@ static hipError_t launch_adj_ql(const LaunchPlan& P, hipStream_t stream) {
 template <int DT>
 static hipError_t launch_adj_dt(const LaunchPlan& P, hipStream_t stream) {
   if (P.tracer == 1) return launch_adj_ql<DT>(P, stream);
-  if (P.ckpt_k == 1) return launch_adj_mode<DT, Replay::STORED>(P, stream);
-  if (P.ckpt_k == CHUNK) return launch_adj_mode<DT, Replay::SEGMENT>(P, stream);
-  // up to stride 6 a chunk's start is 1.5 steps from a checkpoint on average; a pass that
-  // leaves the starts replays as many but for each segment's last chunk, which it cuts short
-  // (1M rays, stride 4: 4990 us this way, 5660 with the pass; stride 6: 4860, 5140). From 8
-  // on the walks are the longer way (3.5 steps per chunk of 3, growing with the stride).
-  if (P.ckpt_k <= 6) return launch_adj_mode<DT, Replay::WALK>(P, stream);
-  return launch_adj_mode<DT, Replay::CHUNKS>(P, stream);
+  switch (P.ckpt_k) {
+    case 1: return launch_adj_mode<DT, Replay::STORED, 3>(P, stream);
+    case 3: return launch_adj_mode<DT, Replay::SEGMENT, 3>(P, stream);
+    case 4: return launch_adj_mode<DT, Replay::SEGMENT, 4>(P, stream);
+    // a chunk's start is 1.5 steps from a checkpoint on average; a pass that leaves the starts
+    // replays as many but for each segment's last chunk, which it cuts short (1M rays: 4860
+    // us this way, 5140 with the pass). From 8 on the walks are the longer way.
+    case 6: return launch_adj_mode<DT, Replay::WALK, 3>(P, stream);
+  }
+  // Chunks of 4 run 3 wavefronts per SIMD with parks, chunks of 3 run 4: the former where they
+  // need no more rounds of resident wavefronts for it. Adjoint by chunks of 4 / 3, us, at tiles
+  // per compute unit: stride 16, 4.7: 333 / 407, 7.1: 233 / 254, 17.6: 5570 / 5634, 34: 1665 /
+  // 1885; 16: 2783 / 2110, 30: 3420 / 3128, 64: 6020 / 5498; stride 8, 6.9: 1047 / 1105, 22: 2583 /
+  // 2871, 64: 5862 / 5402.
+  const int per_cu = (P.total_tiles + P.n_cus - 1) / P.n_cus;
+  if ((per_cu + 11) / 12 <= (per_cu + 15) / 16) return launch_adj_mode<DT, Replay::CHUNKS, 4>(P, stream);
+  return launch_adj_mode<DT, Replay::CHUNKS, 3>(P, stream);
 }
 
 // Processing order of the persistent adjoint. A tile's reverse sweep lasts as long as

@@ -598,7 +598,10 @@ static size_t queue_lds(const LaunchPlan& P) {
 // the faster: 128^3 room, stride 3, adjoint coherent / queue in us: 48 x 48 rays 7938 /
 // 1105, 256 x 256 (7 rays per cell) 2464 / 1209; 32^3, 160 x 160 (46) 280 / 251. Beyond
 // that the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3, 384 x 384
-// (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. The quasi-linear form shares a tile
+// (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. Strides 1, 8, 16, ... take 8-step chunks
+// and 3 wavefronts per compute unit, so the line falls with the rounds. Stride 16: 290 x 290,
+// 160^3 (6) 3394 / 2770, 224^3 (3) 7014 / 4030; 360 x 360, 224^3 (4.8) 5599 / 5693, 300^3 (2.7)
+// 10394 / 7872; 471 x 395 (5.5) 2693 / 3744; 4515 tiles (2.4) 5570 / 6006. The quasi-linear form shares a tile
 // out over wavefronts while there are few: 64^3, 160 x 160 (12) 773 / 135, 256 x 256 (30)
 // 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 / 2839, 512 x 512 (13)
 // 2974 / 5041.
@@ -608,7 +611,9 @@ bool adjoint_by_queue(const LaunchPlan& P) {
     return P.rays_per_cell < (P.total_tiles <= 2 * P.n_cus ? 64.0f : few ? 40.0f : 8.0f);
   }
   const int per_cu = std::min(4, (int)(160 * 1024 / queue_lds(P)));
-  return P.total_tiles <= per_cu * P.n_cus || P.rays_per_cell < 6.0f;
+  const int rounds = (P.total_tiles + per_cu * P.n_cus - 1) / (per_cu * P.n_cus);
+  if (rounds <= 1) return true;
+  return P.rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
 }
 
 // A block of the four-wavefront form takes a compute unit's LDS: as many tiles as units run at
