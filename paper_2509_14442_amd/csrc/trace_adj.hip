@@ -476,13 +476,13 @@ __device__ __forceinline__ void adjoint_tile_ql(const SceneDev& S, int tile, int
   const float h = S.hf;
   CellMerge<true> M(cache);
   float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
-  // The points lie on the entry line, known ahead: each one's gather is issued before its
-  // predecessor is merged. Two samples take turns (no copy of a register that is still in
-  // flight). 1M rays: 2730 us with each point's gather waited on, 2640 so; persistent blocks
-  // 2930 -> 2680.
-  Sample even, odd;
-  const auto fetch = [&](int j, Sample& P) {
-    if (active && j <= 2 * n) {
+#pragma unroll 1
+  for (int j = 0; j < npts; ++j) {
+    const bool act = active && j <= 2 * n;
+    SampleRev Rs;
+    float w[3];
+    if (act) {
+      ql_force_adjoint(S, R, j, w);
       const float jf = (float)j;
       float bh[3], sm[3];
 #pragma unroll
@@ -492,54 +492,29 @@ __device__ __forceinline__ void adjoint_tile_ql(const SceneDev& S, int tile, int
       }
       Cell C;
       locate3(S, bh, sm, C);
-      P.rec = cell_index(S, C);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) P.f[a] = C.f[a];
-      fetch_cell<DT>(S, P.rec, P.c);
+      sample_rev<DT>(S, C, Rs);
     }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  const auto merge = [&](int j, const Sample& P) {
-    const bool act = active && j <= 2 * n;
-    M.enter(S, act, __ballot(act), act ? (int)P.rec : 0, lane);
+    M.enter(S, act, __ballot(act), act ? Rs.key : 0, lane);
     if (act) {
-      SampleRev Rs;
-      float w[3], p[3];
-      ql_force_adjoint(S, R, j, w);
-      sample_rev_at(S, P.c, P.rec, P.f, Rs);
+      float p[3];
       force_rev(S, Rs, w, p, M.acc);
       const float tj = (float)j * (0.5f * h);
 #pragma unroll
       for (int a = 0; a < 3; ++a) pv[a] = fmaf(tj, p[a], pv[a]);
     }
-  };
-  fetch(0, even);
-#pragma unroll 1
-  for (int j = 0; j < npts; j += 2) {
-    fetch(j + 1, odd);
-    merge(j, even);
-    fetch(j + 2, even);
-    merge(j + 1, odd);
-    if ((j & 14) == 14) chunk_end(S, M.P, lane);
+    if ((j & 15) == 15) chunk_end(S, M.P, lane);
   }
   float tb0[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) tb0[a] = fmaf((float)n * h, R.rb[a], R.tb[a]) + pv[a];
-  // v0 from the ray header again rather than held in registers through the sweep
-  float V0[3] = {0.0f, 0.0f, 0.0f};
-  if (active) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) V0[a] = gld(S.ckpt + (size_t)R.q + (size_t)(12 + a) * (size_t)S.ckpt_pad);
-  }
-  entry_term(S, B, V0, active, tb0, M, lane);
+  entry_term(S, B, B.V, active, tb0, M, lane);
   drain(S, M, M.P, lane);
 }
 
-// 5 wavefronts per SIMD: the next point's gather covers the latency that the sixth used to,
-// and at 80 registers the two samples spill (1M rays: 3130 us at 6, 2640 at 5, 2810 at 4;
-// without the parks, which then fit, 2690 at 6 and 2790 at 5).
+// Held to 80 registers for 6 wavefronts per SIMD: this latency-bound grid form runs 4 %
+// faster that way, its small spill included (the persistent form gains nothing from it).
 template <int DT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_trace_adj_ql(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_trace_adj_ql(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -551,7 +526,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 }
 
 template <int DT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_trace_adj_ql_persistent(const SceneDev* __restrict__ scenes, int n_scenes,
+__global__ __launch_bounds__(256) void k_trace_adj_ql_persistent(const SceneDev* __restrict__ scenes, int n_scenes,
                                                                  int total_tiles, unsigned int* __restrict__ queues,
                                                                  const int* __restrict__ order) {
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
