@@ -191,7 +191,9 @@ typedef struct rbos_adjoint_io {
   const float* dL_ddir; /* [dev] [n_rays][3] dL/d(wall_dir); nullable (no direction term) */
 } rbos_adjoint_io;
 
-/* Launch shape (nullable: library defaults). */
+/* Launch shape (nullable: library defaults). Calls with few wavefronts, and adjoints with few
+   rays per cell, run in forms with a grid of their own: of this struct they use only
+   tile_w and tile_h. rbos_launch_forms says which form a call takes. */
 typedef struct rbos_launch {
   int32_t tile_w, tile_h;     /* rays per wavefront tile, tile_w * tile_h == 64 */
   int32_t waves_per_block;    /* 1, 2 or 4 */
@@ -376,6 +378,26 @@ size_t rbos_mlp_pde_workspace_bytes(int32_t width, int32_t depth, int64_t n_poin
    a fixed order) when given, and ADDS dL_PDE/d params into dparams [dev] when given. */
 int rbos_mlp_pde_loss(const rbos_mlp* mlp, const rbos_pde* pde, const float* points, int64_t n_points, float* loss,
                       float* dparams, float* residuals, void* workspace, size_t ws_bytes, void* stream);
+
+/* --- kernel forms -------------------------------------------------------------------- */
+
+/* GRID and PERSISTENT follow rbos_launch. The others take only its tile shape: AHEAD (forward)
+   issues a step's gathers before the step that needs them, QUEUE (adjoint) collects the
+   voxel sums of each ray in queues instead of summing rays of one cell, PIPE (adjoint, four
+   wavefronts per tile) does so with the sweep's parts on wavefronts of their own. */
+enum {
+  RBOS_FORM_GRID = 0,
+  RBOS_FORM_PERSISTENT = 1,
+  RBOS_FORM_AHEAD = 2,
+  RBOS_FORM_QUEUE = 3,
+  RBOS_FORM_PIPE = 4
+};
+
+/* The forms rbos_trace_forward and rbos_trace_adjoint take for these scenes and this launch
+   on a device of `compute_units` compute units (256 on an MI355X). Host only: validates as
+   they do and reads no device memory; needs no workspace, outputs or GPU. */
+int rbos_launch_forms(const rbos_scene* scenes, int32_t n_scenes, const rbos_launch* launch, int32_t compute_units,
+                      int32_t* forward, int32_t* adjoint);
 
 /* --- binding support --------------------------------------------------------------- */
 

@@ -254,6 +254,18 @@ class Tracer:
             self._arr[i] = s.struct
             self._arr[i].ckpt_stride = stride
 
+    def forms(self, compute_units: Optional[int] = None):
+        """The kernel forms ("grid", "persistent", "ahead", "queue", "pipe") of this batch's
+        forward and adjoint; compute_units defaults to the current device's."""
+        if compute_units is None:
+            compute_units = torch.cuda.get_device_properties(self.workspace.device).multi_processor_count
+        out = []
+        for launch in (self._launch_ptr(), self._adjoint_launch_ptr()):
+            f, a = C.c_int32(), C.c_int32()
+            L.check(lib().rbos_launch_forms(self._arr, self.n, launch, compute_units, C.byref(f), C.byref(a)))
+            out.append((L.FORMS[f.value], L.FORMS[a.value]))
+        return out[0][0], out[1][1]
+
     def _launch_ptr(self):
         return C.byref(self.launch) if self.launch is not None else None
 

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstddef>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -76,6 +77,10 @@ int check_launch(const rbos_launch* L, Launch& out) {
   out.blocks_per_cu = L->blocks_per_cu;
   return RBOS_OK;
 }
+
+static_assert(RBOS_FORM_GRID == rbos::FORM_GRID && RBOS_FORM_PERSISTENT == rbos::FORM_PERSISTENT &&
+              RBOS_FORM_AHEAD == rbos::FORM_AHEAD && RBOS_FORM_QUEUE == rbos::FORM_QUEUE &&
+              RBOS_FORM_PIPE == rbos::FORM_PIPE);
 
 bool valid_dtype(int32_t dtype) { return dtype >= RBOS_F32 && dtype <= RBOS_BF16_XPAIR; }
 
@@ -327,6 +332,10 @@ SceneDev make_dev(const rbos_scene* S, const Launch& L, int tile_begin, int rend
   return d;
 }
 
+// A workspace pointer for `prepare` where only validation is wanted: it is checked for
+// alignment and never dereferenced.
+void* const unread_workspace = reinterpret_cast<void*>(uintptr_t{256});
+
 // Common front half of the three tracing entry points.
 struct Prepared {
   Launch L;
@@ -401,23 +410,16 @@ double rays_per_cell(const rbos_scene& S) {
   return std::fmin(per_cell, std::sqrt(per_cell) * density);
 }
 
-int finish_launch(Prepared& P, const rbos_scene* scenes, void* workspace, hipStream_t stream, rbos::LaunchPlan& plan) {
-  unsigned char* ws = static_cast<unsigned char*>(workspace);
-  hipError_t e = rbos::launch_upload(ws + P.Y.table, P.table.data(), sizeof(SceneDev) * P.table.size(), stream);
-  if (e != hipSuccess) return fail(RBOS_E_HIP, "scene table upload failed: %s", hipGetErrorString(e));
-  plan.scenes = reinterpret_cast<const SceneDev*>(ws + P.Y.table);
+// What the choice of a kernel form depends on (host only, no device call).
+rbos::LaunchPlan plan_of(const Prepared& P, const rbos_scene* scenes, int n_cus) {
+  rbos::LaunchPlan plan{};
   plan.n_scenes = (int)P.table.size();
   plan.total_tiles = (int)P.Y.total_tiles;
   plan.wpb = P.L.wpb;
   plan.dtype = P.table.empty() ? 0 : P.table[0].dtype;
   plan.persistent = P.L.persistent;
   plan.blocks_per_cu = P.L.blocks_per_cu;
-  plan.n_cus = compute_units();
-  plan.queues = reinterpret_cast<unsigned int*>(ws + P.Y.queues);
-  plan.total_render_blocks = P.Y.total_render_blocks;
-  plan.partials = reinterpret_cast<float*>(ws + P.Y.partials);
-  plan.tile_cost = reinterpret_cast<int*>(ws + P.Y.tile_cost);
-  plan.tile_order = reinterpret_cast<int*>(ws + P.Y.tile_order);
+  plan.n_cus = n_cus;
   int longest = 1;
   for (const SceneDev& d : P.table) longest = std::max(longest, d.max_steps);
   plan.order_shift = 0;
@@ -434,10 +436,28 @@ int finish_launch(Prepared& P, const rbos_scene* scenes, void* workspace, hipStr
   plan.view_axis = 0;
   for (int a = 1; a < 3 && !P.table.empty(); ++a)
     if (std::fabs(scenes[0].cam_fwd[a]) > std::fabs(scenes[0].cam_fwd[plan.view_axis])) plan.view_axis = a;
-  if (P.L.persistent) {
-    e = rbos::launch_fill_u32(plan.queues, 0u, 16, stream);
-    if (e != hipSuccess) return fail(RBOS_E_HIP, "queue reset failed: %s", hipGetErrorString(e));
-  }
+  return plan;
+}
+
+// The plan with its device buffers in the workspace; the scene table is uploaded there.
+int finish_launch(Prepared& P, const rbos_scene* scenes, void* workspace, hipStream_t stream, rbos::LaunchPlan& plan) {
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  hipError_t e = rbos::launch_upload(ws + P.Y.table, P.table.data(), sizeof(SceneDev) * P.table.size(), stream);
+  if (e != hipSuccess) return fail(RBOS_E_HIP, "scene table upload failed: %s", hipGetErrorString(e));
+  plan = plan_of(P, scenes, compute_units());
+  plan.scenes = reinterpret_cast<const SceneDev*>(ws + P.Y.table);
+  plan.queues = reinterpret_cast<unsigned int*>(ws + P.Y.queues);
+  plan.total_render_blocks = P.Y.total_render_blocks;
+  plan.partials = reinterpret_cast<float*>(ws + P.Y.partials);
+  plan.tile_cost = reinterpret_cast<int*>(ws + P.Y.tile_cost);
+  plan.tile_order = reinterpret_cast<int*>(ws + P.Y.tile_order);
+  return RBOS_OK;
+}
+
+// Zero the tile queues' counters, for a persistent kernel.
+int reset_queues(const rbos::LaunchPlan& plan, hipStream_t stream) {
+  hipError_t e = rbos::launch_fill_u32(plan.queues, 0u, 16, stream);
+  if (e != hipSuccess) return fail(RBOS_E_HIP, "queue reset failed: %s", hipGetErrorString(e));
   return RBOS_OK;
 }
 
@@ -473,17 +493,18 @@ int adjoint_enqueue(Prepared& P, const rbos_scene* scenes, int32_t n_scenes, voi
   rbos::LaunchPlan plan{};
   int rc = finish_launch(P, scenes, ws, stream_h, plan);
   if (rc) return rc;
+  const rbos::Form form = rbos::adjoint_form(plan);
   hipError_t e = hipSuccess;
-  if (rbos::adjoint_by_queue(plan)) {
-    e = rbos::launch_trace_adj_queue(plan, stream_h);
-    if (e != hipSuccess) return fail(RBOS_E_HIP, "adjoint launch failed: %s", hipGetErrorString(e));
-    return RBOS_OK;
-  }
-  if (plan.persistent) {
+  if (form == rbos::FORM_PERSISTENT) {
+    rc = reset_queues(plan, stream_h);
+    if (rc) return rc;
     e = rbos::launch_tile_order(plan, stream_h);
     if (e != hipSuccess) return fail(RBOS_E_HIP, "tile order launch failed: %s", hipGetErrorString(e));
   }
-  e = rbos::launch_trace_adj(plan, stream_h);
+  if (form == rbos::FORM_QUEUE || form == rbos::FORM_PIPE)
+    e = rbos::launch_trace_adj_queue(plan, stream_h);
+  else
+    e = rbos::launch_trace_adj(plan, stream_h);
   if (e != hipSuccess) return fail(RBOS_E_HIP, "adjoint launch failed: %s", hipGetErrorString(e));
   return RBOS_OK;
 }
@@ -637,6 +658,10 @@ int rbos_trace_forward(const rbos_scene* scenes, int32_t n_scenes, const rbos_tr
   hipStream_t stream_h = static_cast<hipStream_t>(stream);
   rc = finish_launch(P, scenes, workspace, stream_h, plan);
   if (rc) return rc;
+  if (rbos::forward_form(plan) == rbos::FORM_PERSISTENT) {
+    rc = reset_queues(plan, stream_h);
+    if (rc) return rc;
+  }
   hipError_t e = rbos::launch_trace_fwd(plan, stream_h);
   if (e != hipSuccess) return fail(RBOS_E_HIP, "forward launch failed: %s", hipGetErrorString(e));
   return RBOS_OK;
@@ -697,9 +722,8 @@ int rbos_trace_adjoint_noalloc(const rbos_scene* scenes, int32_t n_scenes, const
                                const rbos_adjoint_io* io, const rbos_launch* launch, void* stream) {
   g_err.clear();
   Prepared P;
-  // host validation against the scratch size first (no device call): the workspace
-  // pointer given here is only checked for alignment and never dereferenced
-  int rc = prepare(scenes, n_scenes, launch, reinterpret_cast<void*>(uintptr_t{256}), NOALLOC_SCRATCH_BYTES, false, P);
+  // host validation against the scratch size first (no device call)
+  int rc = prepare(scenes, n_scenes, launch, unread_workspace, NOALLOC_SCRATCH_BYTES, false, P);
   if (rc == RBOS_E_WORKSPACE)
     return fail(RBOS_E_WORKSPACE,
                 "rbos_trace_adjoint_noalloc: these scenes need %zu bytes of device scratch, the static buffer "
@@ -713,6 +737,20 @@ int rbos_trace_adjoint_noalloc(const rbos_scene* scenes, int32_t n_scenes, const
   rc = noalloc_scratch(&scratch_dev);
   if (rc) return rc;
   return adjoint_enqueue(P, scenes, n_scenes, scratch_dev, static_cast<hipStream_t>(stream));
+}
+
+int rbos_launch_forms(const rbos_scene* scenes, int32_t n_scenes, const rbos_launch* launch, int32_t compute_units,
+                      int32_t* forward, int32_t* adjoint) {
+  g_err.clear();
+  if (!forward || !adjoint) return fail(RBOS_E_NULL, "forward or adjoint is NULL");
+  if (compute_units < 1) return fail(RBOS_E_RANGE, "compute_units must be positive");
+  Prepared P;
+  int rc = prepare(scenes, n_scenes, launch, unread_workspace, SIZE_MAX, false, P);
+  if (rc) return rc;
+  const rbos::LaunchPlan plan = plan_of(P, scenes, compute_units);
+  *forward = rbos::forward_form(plan);
+  *adjoint = rbos::adjoint_form(plan);
+  return RBOS_OK;
 }
 
 size_t rbos_mlp_param_count(int32_t width, int32_t depth) {

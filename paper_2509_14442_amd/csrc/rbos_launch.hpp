@@ -17,7 +17,7 @@ struct LaunchPlan {
   int persistent;           // 1: persistent blocks + per-XCD tile queues
   int blocks_per_cu;        // persistent: resident blocks per compute unit; 0 = the kernel's occupancy limit
   int n_cus;                // compute units of the device
-  unsigned int* queues;     // 8 counters (zeroed before the launch)
+  unsigned int* queues;     // 16 counters, zeroed before a persistent kernel: forward 0 .. 7, adjoint 8 .. 15
   int ckpt_k;               // checkpoint stride shared by all scenes (adjoint)
   int tracer;               // shared by all scenes: 0 nonlinear, 1 quasi-linear
   int total_render_blocks;  // render: sum of per-scene blocks
@@ -44,12 +44,17 @@ inline int persistent_grid(Kernel kernel, const LaunchPlan& P, size_t lds_bytes)
   return bpc * P.n_cus;
 }
 
+// The kernel form a call takes, from the plan alone (host only; the values are those of
+// RBOS_FORM_* in the public header).
+enum Form { FORM_GRID, FORM_PERSISTENT, FORM_AHEAD, FORM_QUEUE, FORM_PIPE };
+Form forward_form(const LaunchPlan& P);
+Form adjoint_form(const LaunchPlan& P);
+
 hipError_t launch_trace_fwd(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_render(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_trace_adj(const LaunchPlan& P, hipStream_t stream);
-// the adjoint for few rays per cell or few wavefronts, and whether this call is one
+// the adjoint for few rays per cell or few wavefronts (FORM_QUEUE, FORM_PIPE)
 hipError_t launch_trace_adj_queue(const LaunchPlan& P, hipStream_t stream);
-bool adjoint_by_queue(const LaunchPlan& P);
 // persistent adjoint: fill P.tile_order from the forward's step counts
 hipError_t launch_tile_order(const LaunchPlan& P, hipStream_t stream);
 hipError_t launch_field_pack(int nx, int ny, int nz, const float* src, int from_temperature, float rho0G, float T0,

@@ -605,7 +605,7 @@ static size_t queue_lds(const LaunchPlan& P) {
 // out over wavefronts while there are few: 64^3, 160 x 160 (12) 773 / 135, 256 x 256 (30)
 // 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 / 2839, 512 x 512 (13)
 // 2974 / 5041.
-bool adjoint_by_queue(const LaunchPlan& P) {
+static bool adjoint_by_queue(const LaunchPlan& P) {
   if (P.tracer == 1) {
     const bool few = P.total_tiles <= 4 * P.n_cus;
     return P.rays_per_cell < (P.total_tiles <= 2 * P.n_cus ? 64.0f : few ? 40.0f : 8.0f);
@@ -623,6 +623,11 @@ bool adjoint_by_queue(const LaunchPlan& P) {
 // 16, 144 tiles 1184 / 522, 484 tiles 1187 / 976; 64^3, stride 4, 256 tiles 510 / 288, 484
 // tiles 528 / 450; 32^3, stride 3, 484 tiles 246 / 217.
 static bool adjoint_by_pipe(const LaunchPlan& P) { return P.tracer != 1 && P.total_tiles <= 2 * P.n_cus; }
+
+Form adjoint_form(const LaunchPlan& P) {
+  if (adjoint_by_queue(P)) return adjoint_by_pipe(P) ? FORM_PIPE : FORM_QUEUE;
+  return P.persistent ? FORM_PERSISTENT : FORM_GRID;
+}
 
 template <int DT, int KS>
 static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
@@ -651,7 +656,7 @@ static hipError_t launch_queue_dt(const LaunchPlan& P, hipStream_t stream) {
                        P.n_scenes, P.total_tiles, parts, plan);
     return hipGetLastError();
   }
-  if (adjoint_by_pipe(P))
+  if (adjoint_form(P) == FORM_PIPE)
     return P.ckpt_k == 3 || P.ckpt_k == 6 ? launch_pipe_t<DT, 6>(P, stream) : launch_pipe_t<DT, 8>(P, stream);
   switch (queue_chunk(P)) {
     case 3: return launch_queue_t<DT, 3>(P, stream);

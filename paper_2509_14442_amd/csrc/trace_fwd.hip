@@ -227,15 +227,21 @@ __global__ __launch_bounds__(256) void k_trace_fwd_persistent(const SceneDev* __
 // 511; 128^3, 160 x 160: 388 -> 261 us, 768 x 768 895 -> 1038. The quasi-linear gathers do
 // not wait for each other; more registers alone let two run together: 192^3, 160 x 160 rays
 // 504 -> 354 us, 512 x 512 (16 per unit) 621 -> 561.
+Form forward_form(const LaunchPlan& P) {
+  if (P.total_tiles <= (P.tracer == 1 ? 16 : 9) * P.n_cus) return FORM_AHEAD;
+  return P.persistent ? FORM_PERSISTENT : FORM_GRID;
+}
+
 template <int DT, bool QL>
 static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
-  if (P.total_tiles <= (QL ? 16 : 9) * P.n_cus) {
+  const Form form = forward_form(P);
+  if (form == FORM_AHEAD) {
     hipLaunchKernelGGL((k_trace_fwd<DT, QL, true>), dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes,
                        P.total_tiles, 1, P.total_tiles);
     return hipGetLastError();
   }
   const dim3 block(64 * P.wpb);
-  if (P.persistent) {
+  if (form == FORM_PERSISTENT) {
     const dim3 grid(persistent_grid(k_trace_fwd_persistent<DT, QL>, P, 0));
     hipLaunchKernelGGL((k_trace_fwd_persistent<DT, QL>), grid, block, 0, stream, P.scenes, P.n_scenes,
                        P.total_tiles, P.queues);

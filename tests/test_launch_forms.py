@@ -1,0 +1,64 @@
+"""The rule that chooses a call's kernel forms, on the host: rbos_launch_forms validates and
+decides as the launching calls do, without a GPU. 256 compute units throughout."""
+
+import ctypes as C
+import math
+
+import pytest
+
+import paper_2509_14442_amd._lib as L
+
+CUS = 256
+
+
+def room(dims=(128, 128, 128), width=512, height=512, stride=3, tracer=0, pixels=0, axis=1, dtype=0):
+    """A 4 x 4 x 3 m room seen from 1.5 m in front of a face, 40 degrees wide, along `axis`."""
+    s = L.rbos_scene()
+    s.nx, s.ny, s.nz = dims
+    s.box_lo, s.box_hi = L.D3(0, 0, 0), L.D3(4, 4, 3)
+    s.dtype, s.enc_scale, s.enc_offset, s.field = dtype, 1.0, 0.0, 0x1000
+    fwd, right, up = [(1, 0, 0), (0, 1, 0), (0, 0, 1)], [(0, 1, 0), (1, 0, 0), (1, 0, 0)], [(0, 0, 1), (0, 0, 1), (0, 1, 0)]
+    pos = [2.0, 2.0, 1.5]
+    pos[axis] = -1.5
+    s.cam_pos, s.cam_fwd = L.D3(*pos), L.D3(*fwd[axis])
+    s.cam_right, s.cam_up, s.cam_fov_x_deg = L.D3(*right[axis]), L.D3(*up[axis]), 40.0
+    s.width, s.height, s.spp = width, height, 1
+    s.n_pixels = pixels or width * height
+    s.pixel_ids = 0x2000 if pixels else None
+    s.wall_origin, s.wall_normal = L.D3(2, 4, 1.5), L.D3(0, -1, 0)
+    s.wall_u, s.wall_v = L.D3(1, 0, 0), L.D3(0, 0, 1)
+    voxel = min(4 / dims[0], 4 / dims[1], 3 / dims[2])
+    s.step, s.max_steps, s.ckpt_stride, s.tracer = 0.5 * voxel, 16 * math.ceil(7.1 / voxel / 8), stride, tracer
+    return s
+
+
+def forms(*scenes, launch=None, cus=CUS):
+    arr = (L.rbos_scene * len(scenes))(*scenes)
+    f, a = C.c_int32(-1), C.c_int32(-1)
+    L.check(L.load().rbos_launch_forms(arr, len(scenes), C.byref(launch) if launch else None, cus, C.byref(f), C.byref(a)))
+    return L.FORMS[f.value], L.FORMS[a.value]
+
+
+def launch(persistent=0, wpb=4):
+    return L.rbos_launch(8, 8, wpb, persistent, 0)
+
+
+def test_validates_as_the_launching_calls_do():
+    lib = L.load()
+    f, a = C.c_int32(-1), C.c_int32(-1)
+    s = room()
+    assert lib.rbos_launch_forms(C.byref(s), 1, None, CUS, None, C.byref(a)) == -1
+    assert lib.rbos_launch_forms(C.byref(s), 1, None, 0, C.byref(f), C.byref(a)) == -3
+    assert lib.rbos_launch_forms(C.byref(s), 1, C.byref(launch(wpb=3)), CUS, C.byref(f), C.byref(a)) == -3
+    s.nx = 1
+    assert lib.rbos_launch_forms(C.byref(s), 1, None, CUS, C.byref(f), C.byref(a)) == -2
+    assert (f.value, a.value) == (-1, -1) and lib.rbos_last_error()
+
+
+@pytest.mark.parametrize("tracer", [0, 1])
+def test_few_wavefronts_leave_the_launch_shape_unused(tracer):
+    small, large = room((64, 64, 48), 96, 80, tracer=tracer), room((128, 128, 128), 1024, 1024, tracer=tracer)
+    for shape in (None, launch(), launch(1), launch(1, 2)):
+        assert forms(small, launch=shape) == ("ahead", "queue" if tracer else "pipe")
+    assert forms(large) == forms(large, launch=launch()) == ("grid", "grid")
+    assert forms(large, launch=launch(1)) == ("persistent", "persistent")
