@@ -1,10 +1,18 @@
-"""Calls that leave the launch shape unused."""
+"""Parity of the kernels that only larger calls reach: persistent forwards and adjoints of both
+tracers, the coherent adjoint's chunk forms, and its cache of cell totals under tiles whose
+rays sit in many cells. Every test asserts the form its call takes.
+
+Bars: forwards bitwise; gradients against the FP64 oracle rel-L2 < 1e-3 and per-voxel 1e-3 for
+all but 0.5 % of the voxels, as every adjoint test; two launches of one kernel 1e-5 (the cells'
+partial sums in another order)."""
 
 import numpy as np
 import pytest
 import torch
 
-from _common import room_workload
+import bos_inputs as bi
+import oracle
+from _common import grad_errors, room_workload, stored_delta
 from paper_2509_14442_amd import api
 
 pytestmark = pytest.mark.gpu
@@ -21,6 +29,132 @@ def _scene(w, dtype="f32"):
 def _seeds(scenes, seed):
     rng = np.random.default_rng(seed)
     return [torch.from_numpy(rng.standard_normal((s.n_rays, 2)).astype(np.float32)).to(DEV) for s in scenes]
+
+
+def _forward(scenes, launch, form):
+    tr = api.Tracer(scenes, launch)
+    assert tr.forms()[0] == form
+    print([(s.dims, s.desc.width, s.desc.height) for s in scenes], form, flush=True)
+    for t in tr.ckpt + tr.uv + tr.duv:
+        t.zero_()
+    return tr.forward()
+
+
+def _gradient(w, scene, seeds):
+    """The oracle's gradient for seeds on the GPU."""
+    F = oracle.grid_field(stored_delta(w.T32), w.scene.box_lo, w.scene.box_hi)
+    return oracle.adjoint(F, w.scene, seeds.cpu().numpy().astype(np.float64))
+
+
+def _near(g, ref):
+    l2, frac = grad_errors(g.cpu().numpy(), ref)
+    print(f"  rel-L2 {l2:.2e}, voxels off {frac:.1e}", flush=True)
+    assert l2 < 1e-3 and frac <= 5e-3
+
+
+def _rel(a, b):
+    return float((a - b).norm() / b.norm())
+
+
+def _same_rays(a, i, b, j):
+    for x, y in ((a.uv, b.uv), (a.duv, b.duv), (a.n_steps, b.n_steps), (a.status, b.status), (a.ckpt, b.ckpt)):
+        assert torch.equal(x[i].view(torch.uint8), y[j].view(torch.uint8))  # bits: NaN for missing rays
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16-xpair"])
+@pytest.mark.parametrize("tracer", [0, 1])
+def test_forward_forms_agree_bitwise(tracer, dtype):
+    """One set of scenes through the grid and the persistent kernel, and each small one alone, with
+    its gathers issued ahead: the same bits, checkpoints included."""
+    large = room_workload((60, 52, 44), 580, 500, seed=3, ckpt=3, pat=256)
+    small = [room_workload((41, 64, 33), 77, 61, seed=4, ckpt=3, pat=256),
+             room_workload((24, 20, 18), 13, 130, seed=5, ckpt=3, max_steps=40, pat=256)]
+    for w in [large] + small:
+        w.scene = w.scene.replace(tracer=tracer)
+    scenes = [_scene(w, dtype) for w in [large] + small]
+    grid, pers = _forward(scenes, GRID, "grid"), _forward(scenes, PERSISTENT, "persistent")
+    for i in range(3):
+        _same_rays(grid, i, pers, i)
+    for i in (1, 2):
+        _same_rays(grid, i, _forward([scenes[i]], None, "ahead"), 0)
+
+
+@pytest.mark.parametrize("ckpt", [1, 3, 4, 6, 8, 16, 40])
+def test_adjoint_coherent_grid_and_persistent(ckpt):
+    """1444 tiles: 6 per compute unit, so strides from 8 on take chunks of 4."""
+    w = room_workload((20, 24, 16), 304, 304, seed=7, ckpt=ckpt, pat=256)
+    _adjoint_pair(w)
+
+
+@pytest.mark.parametrize("ckpt", [8, 32, 48, 256])
+def test_adjoint_coherent_parts_in_chunks_of_3(ckpt):
+    """3364 tiles: 14 per compute unit, one round in chunks of 3 and two in chunks of 4. Strides
+    over 24 take several parts."""
+    w = room_workload((20, 24, 16), 464, 464, seed=8, ckpt=ckpt, pat=256)
+    _adjoint_pair(w)
+
+
+def test_adjoint_quasilinear_grid_and_persistent():
+    w = room_workload((20, 24, 16), 304, 304, seed=9, pat=256)
+    w.scene = w.scene.replace(tracer=1)
+    _adjoint_pair(w)
+
+
+def _adjoint_pair(w):
+    sc = _scene(w)
+    seeds = _seeds([sc], 3)
+    out = []
+    for launch, form in ((GRID, "grid"), (PERSISTENT, "persistent")):
+        tr = api.Tracer([sc], launch)
+        assert tr.forms()[1] == form
+        print(w.scene.dims, w.scene.width, "ckpt", w.scene.ckpt_stride, form, flush=True)
+        out.append(tr.forward().adjoint(dL_duv=seeds)[0])
+    assert _rel(out[1], out[0]) < 1e-5
+    _near(out[0], _gradient(w, sc, seeds[0]))
+
+
+_SPARSE = {}
+
+
+def _sparse(tracer):
+    """A 24 x 24 camera on a 240 x 240 x 180 room: rays 3-10 cells apart. With the oracle's gradient."""
+    if tracer not in _SPARSE:
+        w = room_workload((240, 240, 180), 24, 24, seed=7, max_steps=800, pat=256)
+        w.scene = w.scene.replace(tracer=tracer)
+        sc = _scene(w)
+        seeds = _seeds([sc], 8)[0]
+        _SPARSE[tracer] = (w, sc, seeds, _gradient(w, sc, seeds))
+    return _SPARSE[tracer]
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+@pytest.mark.parametrize("tracer,ckpt", [(0, 1), (0, 3), (0, 4), (0, 6), (0, 8), (0, 16), (0, 64), (1, 3)])
+def test_coherent_adjoint_with_every_lane_in_its_own_cell(tracer, ckpt, persistent):
+    """The sparse camera beside a large one of many rays per cell: the call takes the coherent
+    kernels, where one wavefront reduction then follows another for dozens of cells, and the
+    32-slot cache of cell totals fills and writes slots out within a chunk."""
+    w, sparse, seeds, ref = _sparse(tracer)
+    dense = room_workload((20, 24, 16), 304, 304, seed=7, ckpt=ckpt, pat=256)
+    dense.scene = dense.scene.replace(tracer=tracer)
+    scenes = [_scene(dense), api.Scene(w.scene, sparse.field, sparse.pattern, ckpt_stride=ckpt)]
+    tr = api.Tracer(scenes, PERSISTENT if persistent else GRID)
+    assert tr.forms()[1] == ("persistent" if persistent else "grid")
+    print("tracer", tracer, "ckpt", ckpt, tr.forms(), flush=True)
+    _near(tr.forward().adjoint(dL_duv=[_seeds(scenes[:1], 3)[0], seeds])[1], ref)
+
+
+def test_noalloc_adjoint_orders_its_tiles_in_the_scratch():
+    """Persistent coherent adjoints: queues, tile costs and order in the static scratch, the second
+    call on what the first left there. Bar 1e-12: the FP64 additions in another order."""
+    for side, dims, ckpt in ((304, (20, 24, 16), 3), (296, (16, 16, 16), 8)):
+        sc = _scene(room_workload(dims, side, side, seed=side, ckpt=ckpt, pat=256))
+        tr = api.Tracer([sc], PERSISTENT)
+        assert tr.forms()[1] == "persistent"
+        seeds = _seeds([sc], 5)
+        print(side, dims, ckpt, flush=True)
+        a = tr.forward().adjoint(dL_duv=seeds)[0]
+        b = tr.adjoint(dL_duv=seeds, noalloc=True)[0]
+        assert float((a - b).abs().max()) <= 1e-12 * float(a.abs().max())
 
 
 def test_unused_persistent_flag_enqueues_nothing():
