@@ -473,7 +473,7 @@ __device__ __forceinline__ void adjoint_tile_ql(const SceneDev& S, int tile, int
   const bool active = R.active;
   const RayBase& B = R.B;
   const int npts = wave_max_nonneg(active ? 2 * n + 1 : 0);
-  const float h = S.hf;
+  const float h = S.hf, h_6 = S.h_6;
   CellMerge<true> M(cache);
   float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
 #pragma unroll 1
@@ -482,7 +482,8 @@ __device__ __forceinline__ void adjoint_tile_ql(const SceneDev& S, int tile, int
     SampleRev Rs;
     float w[3];
     if (act) {
-      ql_force_adjoint(S, R, j, w);
+      float v[3];
+      ql_force_adjoint(R, j, h, h_6, v);
       const float jf = (float)j;
       float bh[3], sm[3];
 #pragma unroll
@@ -493,6 +494,8 @@ __device__ __forceinline__ void adjoint_tile_ql(const SceneDev& S, int tile, int
       Cell C;
       locate3(S, bh, sm, C);
       sample_rev<DT>(S, C, Rs);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) w[a] = v[a] * S.km[a];  // dL/dK -> dL/dG
     }
     M.enter(S, act, __ballot(act), act ? Rs.key : 0, lane);
     if (act) {

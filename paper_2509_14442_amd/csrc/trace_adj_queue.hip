@@ -516,7 +516,7 @@ __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int til
   const RayBase& B = R.B;
   const int npts = wave_max_nonneg(active ? 2 * n + 1 : 0);
   const int j0 = (int)((long long)npts * part / parts), j1 = (int)((long long)npts * (part + 1) / parts);
-  const float h = S.hf;
+  const float h = S.hf, h_6 = S.h_6;
   QueueMerge M(lds, plan, lane);
   float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
   auto sample_point_j = [&](int j, Sample& P) {
@@ -545,7 +545,9 @@ __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int til
     float w[3];
     if (act) {
       sample_rev_at(S, P0.c, P0.rec, P0.f, Rs);
-      ql_force_adjoint(S, R, j, w);
+      ql_force_adjoint(R, j, h, h_6, w);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) w[a] *= S.km[a];  // dL/dK -> dL/dG
     }
     P0 = P1;
     if (active && j + 2 < j1 && j + 2 <= 2 * n) sample_point_j(j + 2, P1);
