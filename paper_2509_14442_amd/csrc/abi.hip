@@ -392,9 +392,10 @@ int compute_units() {
 
 // Rays of one tile that share an interpolation cell, from the scene's geometry: a cell's
 // cross-section seen along the viewing direction over the area of a pixel, both at the
-// middle of the box. The rays of a pixel list are taken as evenly spread in the image: a
-// wavefront then holds a stretch of image rows, thinned out by the list's density.
+// middle of the box. Nothing is known here of a pixel list but its length: it counts as rays
+// with cells of their own, and the choice of a form says where that may not be relied on.
 double rays_per_cell(const rbos_scene& S) {
+  if (S.pixel_ids) return 1.0;
   double vox[3], area = 0.0, depth = 0.0;
   const int n[3] = {S.nx, S.ny, S.nz};
   for (int a = 0; a < 3; ++a) vox[a] = (S.box_hi[a] - S.box_lo[a]) / n[a];
@@ -404,10 +405,7 @@ double rays_per_cell(const rbos_scene& S) {
   }
   const double diag = std::hypot(S.box_hi[0] - S.box_lo[0], S.box_hi[1] - S.box_lo[1], S.box_hi[2] - S.box_lo[2]);
   const double pitch = 2.0 * std::tan(0.5 * S.cam_fov_x_deg * M_PI / 180.0) / S.width * std::fmax(depth, 0.25 * diag);
-  const double per_cell = area / (pitch * pitch);
-  if (!S.pixel_ids) return per_cell;
-  const double density = (double)S.n_pixels / ((double)S.width * S.height);
-  return std::fmin(per_cell, std::sqrt(per_cell) * density);
+  return area / (pitch * pitch);
 }
 
 // What the choice of a kernel form depends on (host only, no device call).
@@ -429,6 +427,7 @@ rbos::LaunchPlan plan_of(const Prepared& P, const rbos_scene* scenes, int n_cus)
   double weight = 0.0, logs = 0.0;  // geometric mean over the tiles of all scenes
   for (size_t i = 0; i < P.table.size(); ++i) {
     if (P.table[i].n_tiles == 0) continue;
+    plan.lists = plan.lists || scenes[i].pixel_ids;
     weight += P.table[i].n_tiles;
     logs += P.table[i].n_tiles * std::log(rays_per_cell(scenes[i]));
   }

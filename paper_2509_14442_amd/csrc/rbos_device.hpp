@@ -1096,6 +1096,36 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Whether the pixels `pix` of the active lanes see more than `limit` cells between them, where
+// their rays cross the plane through the box's centre that faces the camera (wave-uniform; for
+// choices of speed alone: straight rays, pixel centres).
+__device__ __forceinline__ bool pixels_spread(const SceneDev& S, int pix, int limit) {
+  const int col = pix % S.width, row = pix / S.width;
+  const float px = fmaf((float)(2 * col + 1), S.cam_ax.hi, -S.cam_cx.hi);
+  const float py = fmaf(-(float)(2 * row + 1), S.cam_ax.hi, S.cam_cy.hi);
+  float depth = 0.0f, diag = 0.0f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    depth = fmaf(S.cam_fwd[a].hi, fmaf(0.5f * S.n_f[a], S.vox[a], S.lo_f[a]) - S.cam_pos[a].hi, depth);
+    diag = fmaf(S.n_f[a] * S.vox[a], S.n_f[a] * S.vox[a], diag);
+  }
+  depth = fmaxf(depth, 0.25f * sqrtf(diag));  // a camera in the box
+  int p[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float dir = fmaf(px, S.cam_right[a].hi, fmaf(py, S.cam_up[a].hi, S.cam_fwd[a].hi));
+    const float u = fmaf(fmaf(depth, dir, S.cam_pos[a].hi) - S.lo_f[a], S.inv_vox[a].hi, 0.5f);
+    p[a] = (int)__builtin_amdgcn_fmed3f(floorf(u), 0.0f, S.n_f[a]);
+  }
+  const int key = p[0] + S.P0 * p[1] + S.P01 * p[2];
+  unsigned long long pend = __ballot(true);
+  for (int i = 0; i < limit && pend; ++i) {
+    const int k = __builtin_amdgcn_readlane(key, __ffsll((long long)pend) - 1);
+    pend &= ~__ballot(key == k);
+  }
+  return pend != 0;
+}
+
 // max over lanes of a non-negative int
 __device__ __forceinline__ int wave_max_nonneg(int v) {
   v = max(v, dpp_i<0xb1>(v));

@@ -16,7 +16,7 @@
 // rows of the next step) and the registers for it are taken: one wavefront per SIMD.
 #include <algorithm>
 
-#include "rbos_adjoint.hpp"
+#include "rbos_coherent.hpp"
 #include "rbos_launch.hpp"
 
 namespace rbos {
@@ -330,6 +330,42 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds, plan);
 }
 
+// Pixel lists beyond the four-wavefront form. The list lies on the device, so the tile's
+// wavefront looks at its own pixels: in up to LIST_BUNCH cells they
+// are rows of a region seen by many pixels per cell, and the coherent sweep runs. Adjoint at
+// stride 3, 128^3, coherent / queue: 170 x 170 pixels of a 2048 x 1536 camera (3 or 4 cells) 733
+// / 843 us, of 4096 x 3072 (2 or 3) 614 / 721, of 1024 x 768 (6 or 7) 1084 / 875; 30000 random
+// pixels (a cell each) 6961 / 1408. One wavefront per SIMD at most, so its registers are free.
+constexpr int LIST_BUNCH = 4;
+
+__device__ __forceinline__ bool tile_bunched(const SceneDev& S, int tile, int lane) {
+  int r, pix, smp;
+  bool spread = false;
+  if (tile_ray(S, tile, lane, r, pix, smp)) spread = pixels_spread(S, pix, LIST_BUNCH);
+  return __ballot(spread) == 0;  // wave-uniform: the lanes with rays agree
+}
+
+template <int DT, int KS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_list(
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+  extern __shared__ float lds[];
+  const int gtile = xcd_remap(blockIdx.x, total_tiles);
+  const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
+  const int tile = gtile - S.tile_begin, lane = threadIdx.x;
+  if (!S.pixel_ids || !tile_bunched(S, tile, lane))
+    adjoint_tile_queue<DT, KS>(S, tile, lane, lds, plan);
+  else if constexpr (KS == 3)
+    adjoint_tile<DT, Replay::SEGMENT, 3>(S, tile, lane, lds);
+  else if constexpr (KS == 4)
+    adjoint_tile<DT, Replay::SEGMENT, 4>(S, tile, lane, lds);
+  else if constexpr (KS == 6)
+    adjoint_tile<DT, Replay::WALK, 3>(S, tile, lane, lds);
+  else if (S.ckpt_k == 1)
+    adjoint_tile<DT, Replay::STORED, 3>(S, tile, lane, lds);
+  else
+    adjoint_tile<DT, Replay::CHUNKS, 4>(S, tile, lane, lds);
+}
+
 // With few tiles a wavefront's instruction stream is the whole time while three of four SIMDs
 // idle. So a tile takes a block of four wavefronts, one per SIMD of a compute unit, each with
 // its own part of the work on successive chunks of 6 or 8 steps: one replays a chunk's samples
@@ -607,14 +643,25 @@ static size_t queue_lds(const LaunchPlan& P) {
 // out over wavefronts while there are few: 64^3, 160 x 160 (12) 773 / 135, 256 x 256 (30)
 // 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 / 2839, 512 x 512 (13)
 // 2974 / 5041.
+//
+// A pixel list's rays per cell are not known here. Lists go by queue up to one residency (see
+// k_trace_adj_list; quasi-linear up to 4 tiles per compute unit), where that is the faster form
+// for regions of the image and for random pixels alike, and by the coherent kernels beyond.
+// Coherent / queue, 128^3: nonlinear, 1024 x 768 pixels, 240 x 240 of them (900 tiles) 1161 /
+// 891, 60000 random ones of 512 x 512 5883 / 2385; 2025 tiles, 360 x 360 pixels of 2048 x 1536 906
+// / 1666, of 512 x 512 2438 / 3255, random ones 4146 / 4870; 7813 tiles, random 9021 / 20272.
+// Quasi-linear, 900 tiles: 658 / 401 and 5586 / 2309; 2025 tiles: 754 / 958 and 3845 / 4374; 7813
+// tiles 8191 / 18159.
 static bool adjoint_by_queue(const LaunchPlan& P) {
   if (P.tracer == 1) {
     const bool few = P.total_tiles <= 4 * P.n_cus;
+    if (P.lists && !few) return false;
     return P.rays_per_cell < (P.total_tiles <= 2 * P.n_cus ? 64.0f : few ? 40.0f : 8.0f);
   }
   const int per_cu = std::min(4, (int)(160 * 1024 / queue_lds(P)));
   const int rounds = (P.total_tiles + per_cu * P.n_cus - 1) / (per_cu * P.n_cus);
   if (rounds <= 1) return true;
+  if (P.lists) return false;
   return P.rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
 }
 
@@ -624,7 +671,10 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
 // / 538, 484 tiles 1098 / 981, 900 tiles 1225 / 1817; 96^3, 484 tiles 820 / 1030; 128^3, stride
 // 16, 144 tiles 1184 / 522, 484 tiles 1187 / 976; 64^3, stride 4, 256 tiles 510 / 288, 484
 // tiles 528 / 450; 32^3, stride 3, 484 tiles 246 / 217.
-static bool adjoint_by_pipe(const LaunchPlan& P) { return P.tracer != 1 && P.total_tiles <= 2 * P.n_cus; }
+// Pixel lists take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera (452 tiles)
+// 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 / 2172; 256
+// tiles 1039 / 1292, 637 / 299 and 1070 / 1152.
+static bool adjoint_by_pipe(const LaunchPlan& P) { return P.tracer != 1 && P.total_tiles <= (P.lists ? 1 : 2) * P.n_cus; }
 
 Form adjoint_form(const LaunchPlan& P) {
   if (adjoint_by_queue(P)) return adjoint_by_pipe(P) ? FORM_PIPE : FORM_QUEUE;
@@ -644,7 +694,9 @@ static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
 template <int DT, int KS>
 static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
   const QueuePlan plan = queue_plan(P);
-  hipLaunchKernelGGL((k_trace_adj_queue<DT, KS>), dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
+  static_assert(adj_floats_per_wave<KS == 4 || KS == 8 ? 4 : 3>() <= KS * 3 * 64 * 4 + 128 * 9, "the coherent sweep's LDS");
+  auto* kernel = P.lists ? &k_trace_adj_list<DT, KS> : &k_trace_adj_queue<DT, KS>;
+  hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
                      P.total_tiles, plan);
   return hipGetLastError();
 }

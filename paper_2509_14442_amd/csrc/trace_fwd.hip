@@ -89,7 +89,7 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
     } else {
       // Segments of K steps; every segment after the first starts with a step whose start
       // state is stored. That step is a copy of its own with unconditional stores, issued
-      // after its first gather (see NoIssue): in one loop with a branch around the stores,
+      // after its second gather (see NoIssue): in one loop with a branch around the stores,
       // the wait for the next gather at the branch's join would have to cover them.
       const int K = S.ckpt_k;
       int until = min(K, S.max_steps);
@@ -179,10 +179,22 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
   }
 }
 
+// When a step's gathers are issued: as it comes to their points, ahead, or whichever the
+// wavefront's rays call for. A pixel list may be spread out, every ray in a cell of its own (16384
+// to 130000 random pixels of a 512 x 512 camera, 128^3: ahead 286 to 334 us, at use 392 to 407),
+// or a region of the image, whose rows stay within few cells: its gathers hit the caches, and the
+// instructions that issue them ahead cost more than they hide (240 x 240 pixels of a 2048 x 1536
+// camera: 307 against 254 us, of 1024 x 768: 301 and 253; 170 x 170 of 512 x 384: 287 and 256). The
+// list lies on the device, so the wavefront looks for itself: rows of these regions lie in 4 to 13
+// cells, the random lists' pixels in 24 to 64. The results are the same.
+enum class Gathers { AT_USE, AHEAD, BY_WAVE };
+constexpr int LIST_CELLS = 16;
+
 // Held to 64 registers for 8 wavefronts per SIMD (68 would allow 7): the trace without
-// checkpoints runs 3 % faster; with checkpoints it is unchanged. AHEAD: for few wavefronts.
-template <int DT, bool QL, bool AHEAD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AHEAD ? 2 : 8))) void k_trace_fwd(
+// checkpoints runs 3 % faster; with checkpoints it is unchanged. The other modes: for few
+// wavefronts.
+template <int DT, bool QL, Gathers MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == Gathers::AT_USE ? 8 : 2))) void k_trace_fwd(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -192,7 +204,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AHEAD ? 2 :
   const int tile = gtile - S.tile_begin;
   int r, pix, smp;
   if (!tile_ray(S, tile, lane, r, pix, smp)) return;
-  trace_one<DT, QL, AHEAD>(S, r, pix, smp);
+  if (MODE == Gathers::BY_WAVE && S.pixel_ids && !pixels_spread(S, pix, LIST_CELLS))
+    trace_one<DT, QL, false>(S, r, pix, smp);
+  else
+    trace_one<DT, QL, MODE != Gathers::AT_USE>(S, r, pix, smp);
 }
 
 // Persistent form: blocks pull tiles from per-XCD queues (every 8th run of tiles), and
@@ -236,8 +251,13 @@ template <int DT, bool QL>
 static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
   const Form form = forward_form(P);
   if (form == FORM_AHEAD) {
-    hipLaunchKernelGGL((k_trace_fwd<DT, QL, true>), dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes,
-                       P.total_tiles, 1, P.total_tiles);
+    // a compute unit with one tile waits for every gather, whatever the list
+    auto* kernel = &k_trace_fwd<DT, QL, Gathers::AHEAD>;
+    if constexpr (!QL) {
+      if (P.lists && P.total_tiles > P.n_cus) kernel = &k_trace_fwd<DT, QL, Gathers::BY_WAVE>;
+    }
+    hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes, P.total_tiles, 1,
+                       P.total_tiles);
     return hipGetLastError();
   }
   const dim3 block(64 * P.wpb);
@@ -247,7 +267,7 @@ static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
                        P.total_tiles, P.queues);
   } else {
     const int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_fwd<DT, QL, false>), dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes,
+    hipLaunchKernelGGL((k_trace_fwd<DT, QL, Gathers::AT_USE>), dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes,
                        P.total_tiles, P.wpb, nblocks);
   }
   return hipGetLastError();

@@ -31,6 +31,11 @@ def _seeds(scenes, seed):
     return [torch.from_numpy(rng.standard_normal((s.n_rays, 2)).astype(np.float32)).to(DEV) for s in scenes]
 
 
+def _listed(w, ids):
+    s = _scene(w)
+    return api.Scene(w.scene, s.field, s.pattern, torch.from_numpy(ids.astype(np.int32)).to(DEV))
+
+
 def _forward(scenes, launch, form):
     tr = api.Tracer(scenes, launch)
     assert tr.forms()[0] == form
@@ -141,6 +146,43 @@ def test_coherent_adjoint_with_every_lane_in_its_own_cell(tracer, ckpt, persiste
     assert tr.forms()[1] == ("persistent" if persistent else "grid")
     print("tracer", tracer, "ckpt", ckpt, tr.forms(), flush=True)
     _near(tr.forward().adjoint(dL_duv=[_seeds(scenes[:1], 3)[0], seeds])[1], ref)
+
+
+def _lists(w):
+    """Pixel lists of 257 tiles and more: a region, the same in random order, random pixels of the
+    whole image, and a list that turns from one into the other, with a ragged last tile."""
+    W, H = w.scene.width, w.scene.height
+    region = (np.arange(H // 2 - 70, H // 2 + 70)[:, None] * W + np.arange(W // 2 - 65, W // 2 + 65)[None]).ravel()
+    spread = np.sort(np.random.default_rng(1).choice(W * H, 17000, replace=False))
+    return {"region": region, "shuffled": np.random.default_rng(2).permutation(region), "random": spread,
+            "both": np.concatenate([region[:9003], spread[::2]])}
+
+
+@pytest.mark.parametrize("name", ["region", "shuffled", "random", "both"])
+def test_pixel_list_forward_equals_the_image_bitwise(name):
+    """A wavefront of a list issues its gathers ahead or not as its pixels lie: the image's bits."""
+    w = room_workload((60, 64, 90), 400, 360, seed=3, ckpt=3, pat=256)
+    ids = _lists(w)[name]
+    tr, image = _forward([_listed(w, ids)], None, "ahead"), _forward([_scene(w)], GRID, "ahead")
+    at = torch.from_numpy(ids).to(DEV).long()
+    for x, y in ((tr.uv, image.uv), (tr.duv, image.duv), (tr.n_steps, image.n_steps), (tr.status, image.status)):
+        assert torch.equal(x[0].view(torch.uint8), y[0][at].view(torch.uint8))
+
+
+@pytest.mark.parametrize("name,ckpt", [("region", k) for k in (1, 3, 4, 6, 8, 40)] +
+                         [("both", k) for k in (1, 3, 4, 6, 8)] + [("shuffled", 3), ("random", 3)])
+def test_pixel_list_adjoint(name, ckpt):
+    """Lists between one tile per compute unit and one residency: tiles of few cells go coherent,
+    the others by queue, within one launch. 1600 x 1200 pixels: the region's tiles lie in 1 or 2 cells."""
+    w = room_workload((20, 24, 16), 1600, 1200, seed=4, ckpt=ckpt, pat=256)
+    ids = _lists(w)[name]
+    sc = _listed(w, ids)
+    seeds = _seeds([sc], 3)
+    tr = api.Tracer([sc])
+    assert tr.forms()[1] == "queue"
+    print(name, "ckpt", ckpt, len(ids), flush=True)
+    F = oracle.grid_field(stored_delta(w.T32), w.scene.box_lo, w.scene.box_hi)
+    _near(tr.forward().adjoint(dL_duv=seeds)[0], oracle.adjoint(F, w.scene, seeds[0].cpu().numpy().astype(np.float64), ids.astype(np.int32)))
 
 
 def test_noalloc_adjoint_orders_its_tiles_in_the_scratch():

@@ -62,3 +62,23 @@ def test_few_wavefronts_leave_the_launch_shape_unused(tracer):
         assert forms(small, launch=shape) == ("ahead", "queue" if tracer else "pipe")
     assert forms(large) == forms(large, launch=launch()) == ("grid", "grid")
     assert forms(large, launch=launch(1)) == ("persistent", "persistent")
+
+
+@pytest.mark.parametrize("tracer", [0, 1])
+@pytest.mark.parametrize("stride", [1, 3, 4, 6, 8, 16])
+def test_pixel_lists_are_queued_up_to_one_residency(tracer, stride):
+    """Nothing is known on the host of a list but its length: 512 x 512 pixels of a 2048 x 2048
+    camera may be a region of it, whose rows hold 22 rays per cell."""
+    per_cu = 4 if tracer or stride in (3, 4, 6) else 3  # one-wavefront blocks, by registers and LDS
+    for width in (300, 512, 2048, 8192):
+        def adjoint(tiles):
+            return forms(room(width=width, height=width, stride=stride, tracer=tracer, pixels=64 * tiles))[1]
+        assert adjoint(CUS) == ("queue" if tracer else "pipe")
+        assert adjoint(CUS + 1) == adjoint(per_cu * CUS) == "queue"
+        assert adjoint(per_cu * CUS + 1) == adjoint(4096) == "grid"
+
+
+def test_a_list_among_images_keeps_the_call_coherent_beyond_one_residency():
+    image = room((224, 200, 180), 300, 300)  # 3 rays per cell
+    assert forms(image)[1] == forms(image, image)[1] == "queue"
+    assert forms(image, room(pixels=64))[1] == "grid"
