@@ -632,17 +632,23 @@ static size_t queue_lds(const LaunchPlan& P) {
 }
 
 // With every wavefront resident at once (4 per compute unit by registers, fewer by LDS), the
-// nonlinear form is never slower than the coherent kernel, and the fewer rays share a cell
-// the faster: 128^3 room, stride 3, adjoint coherent / queue in us: 48 x 48 rays 7938 /
-// 1105, 256 x 256 (7 rays per cell) 2464 / 1209; 32^3, 160 x 160 (46) 280 / 251. Beyond
-// that the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3, 384 x 384
-// (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. Strides 1, 8, 16, ... take 8-step chunks
-// and 3 wavefronts per compute unit, so the line falls with the rounds. Stride 16: 290 x 290,
-// 160^3 (6) 3394 / 2770, 224^3 (3) 7014 / 4030; 360 x 360, 224^3 (4.8) 5599 / 5693, 300^3 (2.7)
-// 10394 / 7872; 471 x 395 (5.5) 2693 / 3744; 4515 tiles (2.4) 5570 / 6006. The quasi-linear form shares a tile
-// out over wavefronts while there are few: 64^3, 160 x 160 (12) 773 / 135, 256 x 256 (30)
-// 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 / 2839, 512 x 512 (13)
-// 2974 / 5041.
+// nonlinear form is the faster the fewer rays share a cell: 128^3 room, stride 3, adjoint coherent
+// / queue in us: 48 x 48 rays 7938 / 1105, 256 x 256 (7 rays per cell) 2464 / 1209; 48^3, 256 x 256
+// (53) 398 / 375; 40^3 (76) 305 / 307; 32^3 (118) 229 / 242; 20^3 (303) 132 / 146. Where the line
+// lies depends on what the coherent kernel of the stride replays: stride 4, 64^3 (30) 568 / 529,
+// 48^3 (53) 351 / 372, 32^3 204 / 236; 6, 20^3 146 / 141; 1, 48^3 (37) 454 / 420, 40^3 (54) 333 /
+// 343, 24^3 (150) 171 / 196; 8, 32^3 (84) 236 / 233, 24^3 (150) 167 / 170; 16, 48^3 (37) 436 / 409,
+// 40^3 (54) 326 / 332, 32^3 (84) 243 / 259.
+//
+// Beyond one residency the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3,
+// 384 x 384 (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. Strides 1, 8, 16, ... take 8-step
+// chunks and 3 wavefronts per compute unit, so the line falls with the rounds. Stride 16: 290 x
+// 290, 160^3 (6) 3394 / 2770, 224^3 (3) 7014 / 4030; 360 x 360, 224^3 (4.8) 5599 / 5693, 300^3
+// (2.7) 10394 / 7872; 471 x 395 (5.5) 2693 / 3744; 4515 tiles (2.4) 5570 / 6006.
+//
+// The quasi-linear form shares a tile out over wavefronts while there are few: 64^3, 160 x 160
+// (12) 773 / 135, 256 x 256 (30) 513 / 314, 384 x 384 (67) 478 / 712; 192^3, 384 x 384 (7) 3331 /
+// 2839, 512 x 512 (13) 2974 / 5041.
 //
 // A pixel list's rays per cell are not known here. Lists go by queue up to one residency (see
 // k_trace_adj_list; quasi-linear up to 4 tiles per compute unit), where that is the faster form
@@ -660,7 +666,10 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
   }
   const int per_cu = std::min(4, (int)(160 * 1024 / queue_lds(P)));
   const int rounds = (P.total_tiles + per_cu * P.n_cus - 1) / (per_cu * P.n_cus);
-  if (rounds <= 1) return true;
+  if (rounds <= 1) {
+    if (P.lists || P.total_tiles <= 2 * P.n_cus || P.ckpt_k == 6) return true;
+    return P.rays_per_cell < (P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 48.0f);
+  }
   if (P.lists) return false;
   return P.rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
 }

@@ -82,3 +82,13 @@ def test_a_list_among_images_keeps_the_call_coherent_beyond_one_residency():
     image = room((224, 200, 180), 300, 300)  # 3 rays per cell
     assert forms(image)[1] == forms(image, image)[1] == "queue"
     assert forms(image, room(pixels=64))[1] == "grid"
+
+
+@pytest.mark.parametrize("stride", [1, 3, 4, 6, 8, 16])
+def test_many_rays_per_cell_go_coherent_within_one_residency(stride):
+    """700 tiles, beyond the four-wavefront form: about 145, 67 and 16 rays per cell."""
+    def adjoint(n):
+        return forms(room((n, n, n), 211, 211, stride=stride))[1]
+    assert adjoint(24) == ("queue" if stride == 6 else "grid")
+    assert adjoint(35) == ("queue" if stride in (3, 6, 8) else "grid")
+    assert adjoint(72) == "queue"
