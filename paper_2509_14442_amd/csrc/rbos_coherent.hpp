@@ -195,9 +195,9 @@ struct CellMerge : Accum {
 
 // How a chunk of the reverse gets its steps' states.
 enum class Replay {
-  STORED,   // stride 1: every step's start state is a checkpoint
+  STORED,   // stride 1: every step's start state is a checkpoint; nothing is replayed
   SEGMENT,  // strides 3 and 4: a segment is one chunk, replayed from its checkpoint
-  WALK,     // stride 6: each chunk from the checkpoint before it, over the steps in between
+  WALK,     // strides 6 and 8: each chunk from the checkpoint before it, over the steps in between
   CHUNKS,   // longer strides: a pass over the segment leaves its chunks' start states
 };
 
@@ -214,10 +214,14 @@ enum class Replay {
 // chunk, coalesced, mostly in the L2): a part's steps run twice, where replays from the
 // checkpoint to every chunk's start would be quadratic in the stride.
 //
-// Bound by VALU issue. 1M rays, adjoint, against chunks of 8 (stride 6: of 6) step states in
-// LDS, whose samples the reverse located again, at 3 (4) wavefronts per SIMD: stride 1 4910 ->
-// 4610 us, 6 5290 -> 4860, 8 6050 -> 5390, 16 6640 -> 5500. 512 x 512 rays, stride 16: 2900 ->
-// 2010, since its 4096 wavefronts now reside at once.
+// STORED needs no replay: a chunk's LDS takes the states of twice its steps, loaded together, and
+// the reverse locates each step's samples from its state. Recorded samples would cost it two
+// gathers and the LDS traffic for nothing: 400 x 400 rays, 128^3, 1600 us against 1675, 640 x 640,
+// 192^3, 4610 against 4890, f16 4810 against 5260.
+//
+// Adjoint of 1M rays, against chunks of 8 (stride 6: of 6) step states in LDS, whose samples the
+// reverse located again, at 3 (4) wavefronts per SIMD: 6 5360 -> 5000 us, 8 5620 -> 5370, 16 6200
+// -> 5600. 512 x 512 rays, stride 16: 2910 -> 2010, since its 4096 wavefronts now reside at once.
 constexpr int PART_CHUNKS = 8;  // chunks of a part: strides up to 24 are one part
 
 template <int CHUNK>
@@ -257,6 +261,31 @@ __device__ __forceinline__ void record_chunk(const SceneDev& S, const RayBase& B
 #pragma unroll 1
   for (int i = 0; i < cnt - 1; ++i) sharma_step<DT>(S, B, st, P, SampleRow{smp + i * 3 * 64 + lane});
   sharma_step<DT, SampleRow, NoIssue, StepEnd::SAMPLES>(S, B, st, P, SampleRow{smp + (cnt - 1) * 3 * 64 + lane});
+}
+
+// The three samples of the step from st, located as sharma_step does from the same forces.
+template <int DT>
+__device__ __forceinline__ void stored_samples(const SceneDev& S, const RayBase& B, const State& st, SampleRev& R1,
+                                               SampleRev& R2, SampleRev& R3) {
+  Sample P;
+  sample_at_state<DT>(S, B, st, P);
+  sample_rev_at(S, P.c, P.rec, P.f, R1);
+  float bh[3], sm[3];
+  Cell C;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    bh[a] = st.bh[a] + B.g2hi[a];
+    sm[a] = small_part(B, a, st.jf + 1.0f, stage2_dev(S, st, a, R1.eta * R1.g[a]));
+  }
+  locate3(S, bh, sm, C);
+  sample_rev<DT>(S, C, R2);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    bh[a] += B.g2hi[a];
+    sm[a] = small_part(B, a, st.jf + 2.0f, stage3_dev(S, a, stage3_base(S, st, a), R2.eta * R2.g[a]));
+  }
+  locate3(S, bh, sm, C);
+  sample_rev<DT>(S, C, R3);
 }
 
 // Reverse of one chunk, from the samples in LDS: steps c0 + cnt - 1 .. c0 of lanes with cnt > 0.
@@ -303,7 +332,48 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
   CellMerge<adj_park<CHUNK>()> M(lds + chunk_floats<CHUNK>());
   f32x4* smp = reinterpret_cast<f32x4*>(lds);
 
-  if constexpr (MODE == Replay::CHUNKS) {
+  if constexpr (MODE == Replay::STORED) {
+    constexpr int STEPS = 2 * CHUNK;  // whose states take a chunk's LDS
+    const int nch = wave_max_nonneg(active ? (n + STEPS - 1) / STEPS : 0);
+    for (int ch = nch - 1; ch >= 0; --ch) {
+      const int c0 = ch * STEPS;
+      const int cnt = active ? min(STEPS, n - c0) : 0;
+      if (cnt > 0) {
+        State st[STEPS];  // all loads in flight together
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i)
+          if (i < cnt) segment_state(S, q, c0 + i, st[i]);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+          if (i >= cnt) continue;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            lds[(i * 6 + a) * 64 + lane] = st[i].d[a];
+            lds[(i * 6 + 3 + a) * 64 + lane] = st[i].e[a];
+          }
+        }
+      }
+#pragma unroll 1
+      for (int i = STEPS - 1; i >= 0; --i) {
+        const bool act = i < cnt;
+        SampleRev R1, R2, R3;
+        float wA[3], wB[3];
+        if (act) {
+          State st;
+          state_at_step(B, c0 + i, st);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            st.d[a] = lds[(i * 6 + a) * 64 + lane];
+            st.e[a] = lds[(i * 6 + 3 + a) * 64 + lane];
+          }
+          stored_samples<DT>(S, B, st, R1, R2, R3);
+          stage_weights(S, rb, tb, wA, wB);
+        }
+        reverse_stages(S, M, act, R1, R2, R3, wA, wB, rb, tb, lane);
+      }
+      chunk_end(S, M.P, lane);
+    }
+  } else if constexpr (MODE == Replay::CHUNKS) {
     const int K = S.ckpt_k;
     const int part_len = min(K, CHUNK * PART_CHUNKS);
     const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
@@ -359,34 +429,19 @@ __device__ __forceinline__ void adjoint_tile(const SceneDev& S, int tile, int la
       const int cnt = active ? min(CHUNK, n - c0) : 0;
       __builtin_amdgcn_s_setprio(0);
       if (cnt > 0) {
-        if constexpr (MODE == Replay::STORED) {
-          State st[CHUNK];
-#pragma unroll
-          for (int i = 0; i < CHUNK; ++i)
-            if (i < cnt) segment_state(S, q, c0 + i, st[i]);
-#pragma unroll
-          for (int i = 0; i < CHUNK; ++i) {
-            if (i < cnt) {
-              State s = st[i];
-              state_at_step(B, c0 + i, s);
-              record_chunk<DT>(S, B, s, 1, smp + i * 3 * 64, lane);
-            }
-          }
-        } else {
-          // constant for SEGMENT: with the stride read, its replay took 2 % of the adjoint more
-          const int K = MODE == Replay::SEGMENT ? CHUNK : S.ckpt_k;
-          const int seg = c0 / K, s0 = seg * K;
-          State st;
-          state_at_step(B, s0, st);
-          segment_state(S, q, seg, st);
-          if (MODE == Replay::WALK && c0 > s0) {
-            Sample P;
-            sample_at_state<DT>(S, B, st, P);
+        // constant for SEGMENT: with the stride read, its replay took 2 % of the adjoint more
+        const int K = MODE == Replay::SEGMENT ? CHUNK : S.ckpt_k;
+        const int seg = c0 / K, s0 = seg * K;
+        State st;
+        state_at_step(B, s0, st);
+        segment_state(S, q, seg, st);
+        if (MODE == Replay::WALK && c0 > s0) {
+          Sample P;
+          sample_at_state<DT>(S, B, st, P);
 #pragma unroll 1
-            for (int i = s0; i < c0; ++i) sharma_step<DT>(S, B, st, P);  // to the chunk's start
-          }
-          record_chunk<DT>(S, B, st, cnt, smp, lane);
+          for (int i = s0; i < c0; ++i) sharma_step<DT>(S, B, st, P);  // to the chunk's start
         }
+        record_chunk<DT>(S, B, st, cnt, smp, lane);
       }
       reverse_chunk<DT, CHUNK>(S, M, smp, cnt, rb, tb, lane);
       if (ch % writeout_chunks<CHUNK>() == 0) chunk_end(S, M.P, lane);

@@ -172,26 +172,48 @@ static hipError_t launch_adj_ql(const LaunchPlan& P, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Chunks of 4 run 3 wavefronts per SIMD with parks, chunks of 3 run 4 without: the former while
+// they reside at once, and again where 16 wavefronts per compute unit leave a long second round.
+// Adjoint by chunks of 4 / 3, us, at `tiles` per compute unit, 128^3 unless said:
+// - stride 1: 9.8 1603 / 1738; 12.7 1896 / 1627; 16 2242 / 1722; 22 1462 / 1611 (96^3); 25 2357 /
+//   2460; 25 4608 / 4721 (192^3); 32.3 2779 / 2612; 36 2858 / 2966; 46 3421 / 3385; 50 6664 / 6194
+//   (192^3); 64 4750 / 4577;
+// - stride 6: 11.4 1727 / 1938; 13 2137 / 1784; 17.5 2576 / 2292; 19 5110 / 5199 (192^3); 21 2548 /
+//   2824; 25 2702 / 2814; 30 3061 / 2942; 36 3328 / 3271; 64 5480 / 5000;
+// - stride 8: 11.4 1677 / 1985; 13 2090 / 1844; 17.5 2507 / 2422; 19 5110 / 5459 (192^3); 25 2651 /
+//   2977; 30 3006 / 3172; 32 3091 / 3142, 5980 / 5691 (192^3), 7903 / 7435 (224^3); 36 3246 / 3531;
+//   50 4303 / 4491; 64 5366 / 5506;
+// - stride 16: 11.4 1759 / 1987; 13 2184 / 1838; 17.5 2600 / 2376; 21 2612 / 2982; 25 2801 / 2972;
+//   30 3160 / 3223, 1414 / 1388 (64^3), 8010 / 7674 (224^3); 36 3495 / 3600; 39 3810 / 3854; 50
+//   4601 / 4583; 64 6020 / 5600;
+// - stride 32: 13 2223 / 2042; 17.5 2679 / 2606; 21 2627 / 3286; 30 3200 / 3577; 50 4694 / 5048.
+static bool chunks_of_4(int stride, float tiles) {
+  if (tiles <= 12.0f) return true;
+  if (tiles <= 18.0f) return false;
+  if (tiles <= 28.0f || stride > 16) return true;
+  if (stride == 8) return tiles <= 30.5f || tiles > 33.0f;
+  return (stride == 1 || stride == 16) && tiles > 33.0f && tiles <= 40.0f;
+}
+
 template <int DT>
 static hipError_t launch_adj_dt(const LaunchPlan& P, hipStream_t stream) {
   if (P.tracer == 1) return launch_adj_ql<DT>(P, stream);
+  const bool of4 = chunks_of_4(P.ckpt_k, (float)P.total_tiles / (float)P.n_cus);
   switch (P.ckpt_k) {
-    case 1: return launch_adj_mode<DT, Replay::STORED, 3>(P, stream);
+    case 1:
+      return of4 ? launch_adj_mode<DT, Replay::STORED, 4>(P, stream) : launch_adj_mode<DT, Replay::STORED, 3>(P, stream);
     case 3: return launch_adj_mode<DT, Replay::SEGMENT, 3>(P, stream);
     case 4: return launch_adj_mode<DT, Replay::SEGMENT, 4>(P, stream);
-    // a chunk's start is 1.5 steps from a checkpoint on average; a pass that leaves the starts
-    // replays as many but for each segment's last chunk, which it cuts short (1M rays: 4860
-    // us this way, 5140 with the pass). From 8 on the walks are the longer way.
-    case 6: return launch_adj_mode<DT, Replay::WALK, 3>(P, stream);
+    // A walk to a chunk's start takes 1.5 or 2 steps on average; a pass that leaves the starts takes
+    // as many but for each segment's last chunk, which it cuts short: stride 6, 1M rays, 5000 us
+    // by walks, 5200 by passes; stride 8 in chunks of 4, 5370 and 5630. Chunks of 3 do not divide
+    // 8: there 3.5 steps, and the pass is the shorter way.
+    case 6:
+      return of4 ? launch_adj_mode<DT, Replay::WALK, 4>(P, stream) : launch_adj_mode<DT, Replay::WALK, 3>(P, stream);
+    case 8:
+      return of4 ? launch_adj_mode<DT, Replay::WALK, 4>(P, stream) : launch_adj_mode<DT, Replay::CHUNKS, 3>(P, stream);
   }
-  // Chunks of 4 run 3 wavefronts per SIMD with parks, chunks of 3 run 4: the former where they
-  // need no more rounds of resident wavefronts for it. Adjoint by chunks of 4 / 3, us, at tiles
-  // per compute unit: stride 16, 4.7: 333 / 407, 7.1: 233 / 254, 17.6: 5570 / 5634, 34: 1665 /
-  // 1885; 16: 2783 / 2110, 30: 3420 / 3128, 64: 6020 / 5498; stride 8, 6.9: 1047 / 1105, 22: 2583 /
-  // 2871, 64: 5862 / 5402.
-  const int per_cu = (P.total_tiles + P.n_cus - 1) / P.n_cus;
-  if ((per_cu + 11) / 12 <= (per_cu + 15) / 16) return launch_adj_mode<DT, Replay::CHUNKS, 4>(P, stream);
-  return launch_adj_mode<DT, Replay::CHUNKS, 3>(P, stream);
+  return of4 ? launch_adj_mode<DT, Replay::CHUNKS, 4>(P, stream) : launch_adj_mode<DT, Replay::CHUNKS, 3>(P, stream);
 }
 
 // Processing order of the persistent adjoint. A tile's reverse sweep lasts as long as

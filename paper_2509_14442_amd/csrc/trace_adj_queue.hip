@@ -359,9 +359,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
   else if constexpr (KS == 4)
     adjoint_tile<DT, Replay::SEGMENT, 4>(S, tile, lane, lds);
   else if constexpr (KS == 6)
-    adjoint_tile<DT, Replay::WALK, 3>(S, tile, lane, lds);
+    adjoint_tile<DT, Replay::WALK, 4>(S, tile, lane, lds);
+  else if (S.ckpt_k == 8)
+    adjoint_tile<DT, Replay::WALK, 4>(S, tile, lane, lds);
   else if (S.ckpt_k == 1)
-    adjoint_tile<DT, Replay::STORED, 3>(S, tile, lane, lds);
+    adjoint_tile<DT, Replay::STORED, 4>(S, tile, lane, lds);
   else
     adjoint_tile<DT, Replay::CHUNKS, 4>(S, tile, lane, lds);
 }
@@ -636,8 +638,8 @@ static size_t queue_lds(const LaunchPlan& P) {
 // / queue in us: 48 x 48 rays 7938 / 1105, 256 x 256 (7 rays per cell) 2464 / 1209; 48^3, 256 x 256
 // (53) 398 / 375; 40^3 (76) 305 / 307; 32^3 (118) 229 / 242; 20^3 (303) 132 / 146. Where the line
 // lies depends on what the coherent kernel of the stride replays: stride 4, 64^3 (30) 568 / 529,
-// 48^3 (53) 351 / 372, 32^3 204 / 236; 6, 20^3 146 / 141; 1, 48^3 (37) 454 / 420, 40^3 (54) 333 /
-// 343, 24^3 (150) 171 / 196; 8, 32^3 (84) 236 / 233, 24^3 (150) 167 / 170; 16, 48^3 (37) 436 / 409,
+// 48^3 (53) 351 / 372, 32^3 204 / 236; 6, 20^3 146 / 141; 1, 64^3 (21) 649 / 586, 48^3 (37) 381 /
+// 418, 24^3 (150) 149 / 196; 8, 32^3 (84) 236 / 233, 24^3 (150) 167 / 170; 16, 48^3 (37) 436 / 409,
 // 40^3 (54) 326 / 332, 32^3 (84) 243 / 259.
 //
 // Beyond one residency the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3,
@@ -668,7 +670,7 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
   const int rounds = (P.total_tiles + per_cu * P.n_cus - 1) / (per_cu * P.n_cus);
   if (rounds <= 1) {
     if (P.lists || P.total_tiles <= 2 * P.n_cus || P.ckpt_k == 6) return true;
-    return P.rays_per_cell < (P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 48.0f);
+    return P.rays_per_cell < (P.ckpt_k == 1 ? 30.0f : P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 48.0f);
   }
   if (P.lists) return false;
   return P.rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
@@ -703,7 +705,7 @@ static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
 template <int DT, int KS>
 static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
   const QueuePlan plan = queue_plan(P);
-  static_assert(adj_floats_per_wave<KS == 4 || KS == 8 ? 4 : 3>() <= KS * 3 * 64 * 4 + 128 * 9, "the coherent sweep's LDS");
+  static_assert(adj_floats_per_wave<KS == 3 ? 3 : 4>() <= KS * 3 * 64 * 4 + 128 * 9, "the coherent sweep's LDS");
   auto* kernel = P.lists ? &k_trace_adj_list<DT, KS> : &k_trace_adj_queue<DT, KS>;
   hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
                      P.total_tiles, plan);

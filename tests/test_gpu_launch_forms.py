@@ -91,7 +91,7 @@ def test_adjoint_coherent_grid_and_persistent(ckpt):
     _adjoint_pair(w)
 
 
-@pytest.mark.parametrize("ckpt", [8, 32, 48, 256])
+@pytest.mark.parametrize("ckpt", [1, 6, 8, 32, 48, 256])
 def test_adjoint_coherent_parts_in_chunks_of_3(ckpt):
     """3364 tiles: 14 per compute unit, one round in chunks of 3 and two in chunks of 4. Strides
     over 24 take several parts."""
