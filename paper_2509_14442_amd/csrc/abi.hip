@@ -418,10 +418,10 @@ rbos::LaunchPlan plan_of(const Prepared& P, const rbos_scene* scenes, int n_cus)
   plan.persistent = P.L.persistent;
   plan.blocks_per_cu = P.L.blocks_per_cu;
   plan.n_cus = n_cus;
-  int longest = 1;
-  for (const SceneDev& d : P.table) longest = std::max(longest, d.max_steps);
+  plan.max_steps = 1;
+  for (const SceneDev& d : P.table) plan.max_steps = std::max(plan.max_steps, d.max_steps);
   plan.order_shift = 0;
-  while ((longest >> plan.order_shift) >= 1024) ++plan.order_shift;
+  while ((plan.max_steps >> plan.order_shift) >= 1024) ++plan.order_shift;
   plan.ckpt_k = P.table.empty() ? 0 : P.table[0].ckpt_k;
   plan.tracer = P.table.empty() ? 0 : P.table[0].tracer;
   double weight = 0.0, logs = 0.0;  // geometric mean over the tiles of all scenes

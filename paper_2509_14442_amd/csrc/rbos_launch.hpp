@@ -20,6 +20,7 @@ struct LaunchPlan {
   unsigned int* queues;     // 16 counters, zeroed before a persistent kernel: forward 0 .. 7, adjoint 8 .. 15
   int ckpt_k;               // checkpoint stride shared by all scenes (adjoint)
   int tracer;               // shared by all scenes: 0 nonlinear, 1 quasi-linear
+  int max_steps;            // the largest of all scenes
   int total_render_blocks;  // render: sum of per-scene blocks
   float* partials;          // render: per-block partial loss sums
   int* tile_cost;           // adjoint, persistent: longest ray of each tile (steps)

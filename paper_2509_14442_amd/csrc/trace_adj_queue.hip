@@ -15,6 +15,7 @@
 // instruction when alone on its SIMD), so gathers are issued ahead (sharma_step_ahead, the
 // rows of the next step) and the registers for it are taken: one wavefront per SIMD.
 #include <algorithm>
+#include <cmath>
 
 #include "rbos_coherent.hpp"
 #include "rbos_launch.hpp"
@@ -642,6 +643,14 @@ static size_t queue_lds(const LaunchPlan& P) {
 // 418, 24^3 (150) 149 / 196; 8, 32^3 (84) 236 / 233, 24^3 (150) 167 / 170; 16, 48^3 (37) 436 / 409,
 // 40^3 (54) 326 / 332, 32^3 (84) 243 / 259.
 //
+// At strides beyond 16 the queue forms walk from the checkpoint to every 8-step chunk, half of the
+// segment on average, where the coherent kernel passes over each part of it once more: both lines
+// fall with the 1.5th power of that walk. Coherent / queue, strides 16, 32, 64, 128, 256: 96^3, 176
+// x 176 rays (6) 1915 / 873, 1933 / 1034, 2006 / 1315, 2143 / 1910, 2445 / 3085; 32^3, 160 x 160 (46)
+// 275 / 267, 278 / 319, 291 / 402, 320 / 537; 192^3, 160 x 160 (1.3), 256: 10445 / 6921; beyond one
+// residency, 224^3, 290 x 290 (3) 7025 / 4016, 7092 / 4747, 7309 / 6179, 7777 / 9054, 8709 / 14147;
+// 300^3, 360 x 360 (2.7) 10374 / 7845, 10446 / 9429, 10794 / 12277, 12785 / 29734.
+//
 // Beyond one residency the coherent kernels' occupancy wins from about 6 rays per cell on: 192^3,
 // 384 x 384 (7) 4003 / 4238; 128^3, 384 x 384 (17) 1823 / 2855. Strides 1, 8, 16, ... take 8-step
 // chunks and 3 wavefronts per compute unit, so the line falls with the rounds. Stride 16: 290 x
@@ -668,12 +677,16 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
   }
   const int per_cu = std::min(4, (int)(160 * 1024 / queue_lds(P)));
   const int rounds = (P.total_tiles + per_cu * P.n_cus - 1) / (per_cu * P.n_cus);
+  // steps run per step recorded, against stride 16
+  const float walk = P.ckpt_k <= 16 ? 1.0f : (1.0f + 0.1f * (float)(std::min(P.ckpt_k, P.max_steps) / 8 - 1)) / 1.1f;
+  const float rays_per_cell = P.rays_per_cell * walk * std::sqrt(walk);
   if (rounds <= 1) {
-    if (P.lists || P.total_tiles <= 2 * P.n_cus || P.ckpt_k == 6) return true;
-    return P.rays_per_cell < (P.ckpt_k == 1 ? 30.0f : P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 48.0f);
+    if (P.lists || P.total_tiles <= P.n_cus || P.ckpt_k == 6) return true;
+    if (P.total_tiles <= 2 * P.n_cus && P.ckpt_k <= 16) return true;
+    return rays_per_cell < (P.ckpt_k == 1 ? 30.0f : P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 44.0f);
   }
   if (P.lists) return false;
-  return P.rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
+  return rays_per_cell < (per_cu == 4 ? 6.0f : std::max(2.0f, 12.0f / (float)rounds));
 }
 
 // A block of the four-wavefront form takes a compute unit's LDS: as many tiles as units run at
@@ -684,8 +697,12 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
 // tiles 528 / 450; 32^3, stride 3, 484 tiles 246 / 217.
 // Pixel lists take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera (452 tiles)
 // 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 / 2172; 256
-// tiles 1039 / 1292, 637 / 299 and 1070 / 1152.
-static bool adjoint_by_pipe(const LaunchPlan& P) { return P.tracer != 1 && P.total_tiles <= (P.lists ? 1 : 2) * P.n_cus; }
+// tiles 1039 / 1292, 637 / 299 and 1070 / 1152. So do strides beyond 16, whose walk is one
+// wavefront's: stride 64, 192^3, 400 tiles 2872 / 3085, 96^3, 484 tiles 1315 / 1560, 144 tiles 1279 /
+// 769; stride 256, 144 tiles 2944 / 2380, coherent 4472.
+static bool adjoint_by_pipe(const LaunchPlan& P) {
+  return P.tracer != 1 && P.total_tiles <= (P.lists || P.ckpt_k > 16 ? 1 : 2) * P.n_cus;
+}
 
 Form adjoint_form(const LaunchPlan& P) {
   if (adjoint_by_queue(P)) return adjoint_by_pipe(P) ? FORM_PIPE : FORM_QUEUE;

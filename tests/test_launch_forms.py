@@ -92,3 +92,21 @@ def test_many_rays_per_cell_go_coherent_within_one_residency(stride):
     assert adjoint(24) == ("queue" if stride == 6 else "grid")
     assert adjoint(35) == ("queue" if stride in (3, 6, 8) else "grid")
     assert adjoint(72) == "queue"
+
+
+def test_long_strides_leave_the_queue_form_by_their_walk():
+    """The queue forms walk half a segment to every 8-step chunk: the more rays share a cell, the
+    shorter the strides they are taken for."""
+    def first_coherent(n, side):
+        return next((k for k in (16, 32, 64, 128, 256) if forms(room((n, n, n), side, side, stride=k))[1] == "grid"), None)
+    assert first_coherent(32, 160) == 32  # 46 rays per cell, 400 tiles
+    assert first_coherent(96, 176) == 256  # 6, 484
+    assert first_coherent(192, 160) is None  # 1.3, 400
+    assert first_coherent(224, 290) == 128  # 3.1, 1369: two residencies
+    assert first_coherent(300, 360) == 64  # 2.7, 2025: three
+    assert first_coherent(32, 96) is None  # 144: four wavefronts per tile
+    assert forms(room((96, 96, 96), 176, 176, stride=16))[1] == "pipe"
+    assert forms(room((96, 96, 96), 176, 176, stride=64))[1] == "queue"
+    short = room((96, 96, 96), 176, 176, stride=256)
+    short.max_steps = 60  # one segment, cut short
+    assert forms(short)[1] == "queue"
