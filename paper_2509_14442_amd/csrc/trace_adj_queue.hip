@@ -681,8 +681,7 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
   const float walk = P.ckpt_k <= 16 ? 1.0f : (1.0f + 0.1f * (float)(std::min(P.ckpt_k, P.max_steps) / 8 - 1)) / 1.1f;
   const float rays_per_cell = P.rays_per_cell * walk * std::sqrt(walk);
   if (rounds <= 1) {
-    if (P.lists || P.total_tiles <= P.n_cus || P.ckpt_k == 6) return true;
-    if (P.total_tiles <= 2 * P.n_cus && P.ckpt_k <= 16) return true;
+    if (P.lists || P.ckpt_k == 6) return true;
     return rays_per_cell < (P.ckpt_k == 1 ? 30.0f : P.ckpt_k == 3 ? 75.0f : P.ckpt_k == 8 ? 90.0f : 44.0f);
   }
   if (P.lists) return false;
@@ -690,22 +689,32 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
 }
 
 // A block of the four-wavefront form takes a compute unit's LDS: as many tiles as units run at
-// once, twice as many in turn, where it still is the faster form more often than not. Adjoint,
-// one wavefront per tile / four, us: 128^3 room, stride 3, 36 tiles 1106 / 540, 256 tiles 1080
-// / 538, 484 tiles 1098 / 981, 900 tiles 1225 / 1817; 96^3, 484 tiles 820 / 1030; 128^3, stride
-// 16, 144 tiles 1184 / 522, 484 tiles 1187 / 976; 64^3, stride 4, 256 tiles 510 / 288, 484
-// tiles 528 / 450; 32^3, stride 3, 484 tiles 246 / 217.
+// once, twice as many in turn. Adjoint, one wavefront per tile / four, us: 128^3 room, stride 3, 36
+// tiles 1106 / 540, 256 tiles 1080 / 538, 900 tiles 1225 / 1817; stride 16, 144 tiles 1184 / 522;
+// 64^3, stride 4, 256 tiles 510 / 288. Between one tile per unit and two, a second round gains
+// - on fields of up to about 50^3 voxels (stride 3): 32^3, 484 tiles 244 / 213; 48^3, 289 tiles 386 /
+//   338, 361 392 / 376, 484 383 / 356; x-pairs, 484 tiles 424 / 377; but 52^3, 400 tiles 428 / 474,
+//   x-pairs, 324 tiles 460 / 495, 56^3, 484 456 / 510;
+// - else while it is short and the rays share few cells: 192^3, 484 tiles (1.6 rays per cell) 1730 /
+//   1547; 160^3, 361 (1.6) 1412 / 1266, 484 (2.2) 1399 / 1421; 128^3, 361 (2.5) 1106 / 1065, 484 (3.5)
+//   1106 / 1218; 96^3, 289 (3.4) 820 / 756, 324 (3.9) 820 / 823, 361 (4.5) 827 / 861, 484 (6.2) 817 /
+//   1056; 72^3, 289 (6) 595 / 563, 324 (7) 614 / 646; 64^3, 361 (10) 539 / 713, 484 (14) 539 / 862.
 // Pixel lists take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera (452 tiles)
 // 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 / 2172; 256
 // tiles 1039 / 1292, 637 / 299 and 1070 / 1152. So do strides beyond 16, whose walk is one
 // wavefront's: stride 64, 192^3, 400 tiles 2872 / 3085, 96^3, 484 tiles 1315 / 1560, 144 tiles 1279 /
 // 769; stride 256, 144 tiles 2944 / 2380, coherent 4472.
 static bool adjoint_by_pipe(const LaunchPlan& P) {
-  return P.tracer != 1 && P.total_tiles <= (P.lists || P.ckpt_k > 16 ? 1 : 2) * P.n_cus;
+  if (P.tracer == 1 || P.total_tiles > 2 * P.n_cus) return false;
+  const float second_round = (float)P.total_tiles / (float)P.n_cus - 1.0f;
+  if (second_round <= 0.0f) return true;
+  if (P.lists || P.ckpt_k > 16) return false;
+  return P.voxels <= 125000.0 || P.rays_per_cell * second_round <= 1.4f;
 }
 
 Form adjoint_form(const LaunchPlan& P) {
-  if (adjoint_by_queue(P)) return adjoint_by_pipe(P) ? FORM_PIPE : FORM_QUEUE;
+  if (adjoint_by_pipe(P)) return FORM_PIPE;
+  if (adjoint_by_queue(P)) return FORM_QUEUE;
   return P.persistent ? FORM_PERSISTENT : FORM_GRID;
 }
 

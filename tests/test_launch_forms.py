@@ -105,8 +105,23 @@ def test_long_strides_leave_the_queue_form_by_their_walk():
     assert first_coherent(224, 290) == 128  # 3.1, 1369: two residencies
     assert first_coherent(300, 360) == 64  # 2.7, 2025: three
     assert first_coherent(32, 96) is None  # 144: four wavefronts per tile
-    assert forms(room((96, 96, 96), 176, 176, stride=16))[1] == "pipe"
-    assert forms(room((96, 96, 96), 176, 176, stride=64))[1] == "queue"
+    assert forms(room((192, 192, 192), 176, 176, stride=16))[1] == "pipe"
+    assert forms(room((192, 192, 192), 176, 176, stride=64))[1] == "queue"
     short = room((96, 96, 96), 176, 176, stride=256)
     short.max_steps = 60  # one segment, cut short
     assert forms(short)[1] == "queue"
+
+
+def test_second_round_of_four_wavefront_blocks():
+    """Between one tile per compute unit and two: for small fields, or few rays per cell and a short
+    round."""
+    def adjoint(n, side, dtype=0, scenes=1, **kw):
+        return forms(*[room((n, n, n), side, side, dtype=dtype, **kw)] * scenes)[1]
+    assert adjoint(96, 128) == "pipe"  # 256 tiles
+    assert adjoint(96, 132) == "pipe"  # 289 tiles, 3.5 rays per cell
+    assert adjoint(96, 150) == adjoint(96, 176) == adjoint(64, 150) == adjoint(64, 176) == "queue"
+    assert adjoint(192, 176) == "pipe"  # 484, 1.6
+    assert adjoint(50, 176) == adjoint(32, 176) == "pipe"
+    assert adjoint(51, 176) == adjoint(51, 176, dtype=3) == "queue"
+    assert adjoint(48, 120) == "pipe" and adjoint(48, 120, scenes=2) == "queue"  # 225 tiles; 450 on two fields
+    assert adjoint(32, 184) == "queue"  # 529 tiles
