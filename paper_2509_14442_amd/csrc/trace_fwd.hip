@@ -190,11 +190,19 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
 enum class Gathers { AT_USE, AHEAD, BY_WAVE };
 constexpr int LIST_CELLS = 16;
 
-// Held to 64 registers for 8 wavefronts per SIMD (68 would allow 7): the trace without
-// checkpoints runs 3 % faster; with checkpoints it is unchanged. The other modes: for few
-// wavefronts.
+// Wavefronts per SIMD the registers are held to. The Sharma step carries a sample between steps
+// and takes 75 to 77 registers; held to 64 for 8 wavefronts it spills 11 to 18 of them. That pays
+// for FP32 records alone (8 / 6 wavefronts, us: 900 x 900 rays, 192^3, stride 3 1730 / 1760; 1024 x
+// 1024, 128^3, stride 16 1306 / 1340), and costs where samples are decoded or gathered in parts: BF16, 1024 x 1024,
+// 128^3, stride 1 2123 / 1992, stride 3 1660 / 1643, 256 x 256, 64^3 170 / 161; FP16 256 x 256,
+// 128^3 389 / 353, 1024 x 1024, stride 1 2177 / 2059; x-pairs 1894 / 1718, stride 1 2730 / 2114.
 template <int DT, bool QL, Gathers MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == Gathers::AT_USE ? 8 : 2))) void k_trace_fwd(
+constexpr int fwd_waves_per_simd() {
+  return MODE != Gathers::AT_USE ? 2 : QL || DT == DT_F32 ? 8 : 6;
+}
+
+template <int DT, bool QL, Gathers MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<DT, QL, MODE>()))) void k_trace_fwd(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -213,7 +221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == Gat
 // Persistent form: blocks pull tiles from per-XCD queues (every 8th run of tiles), and
 // steal from the other XCDs' queues once their own is drained.
 template <int DT, bool QL>
-__global__ __launch_bounds__(256) void k_trace_fwd_persistent(const SceneDev* __restrict__ scenes, int n_scenes,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_trace_fwd_persistent(const SceneDev* __restrict__ scenes, int n_scenes,
                                                               int total_tiles, unsigned int* __restrict__ queues) {
   const int lane = threadIdx.x & 63;
   const int xcd = blockIdx.x & 7;
