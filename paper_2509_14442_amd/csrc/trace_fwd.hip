@@ -187,18 +187,19 @@ __device__ __forceinline__ void trace_one(const SceneDev& S, int r, int pix, int
 // camera: 307 against 254 us, of 1024 x 768: 301 and 253; 170 x 170 of 512 x 384: 287 and 256). The
 // list lies on the device, so the wavefront looks for itself: rows of these regions lie in 4 to 13
 // cells, the random lists' pixels in 24 to 64. The results are the same.
-enum class Gathers { AT_USE, AHEAD, BY_WAVE };
+enum class Gathers { AT_USE, AT_USE_FEW, AHEAD, BY_WAVE };
 constexpr int LIST_CELLS = 16;
 
 // Wavefronts per SIMD the registers are held to. The Sharma step carries a sample between steps
 // and takes 75 to 77 registers; held to 64 for 8 wavefronts it spills 11 to 18 of them. That pays
-// for FP32 records alone (8 / 6 wavefronts, us: 900 x 900 rays, 192^3, stride 3 1730 / 1760; 1024 x
-// 1024, 128^3, stride 16 1306 / 1340), and costs where samples are decoded or gathered in parts: BF16, 1024 x 1024,
+// for FP32 records beyond 9 tiles per compute unit alone (8 / 6 wavefronts, us: 900 x 900 rays,
+// 192^3, stride 3 1730 / 1760; 1024 x 1024, 128^3, stride 16 1306 / 1340), and costs where wavefronts
+// are few (384 x 384, 88^3 276 / 261) or samples are decoded or gathered in parts: BF16, 1024 x 1024,
 // 128^3, stride 1 2123 / 1992, stride 3 1660 / 1643, 256 x 256, 64^3 170 / 161; FP16 256 x 256,
 // 128^3 389 / 353, 1024 x 1024, stride 1 2177 / 2059; x-pairs 1894 / 1718, stride 1 2730 / 2114.
 template <int DT, bool QL, Gathers MODE>
 constexpr int fwd_waves_per_simd() {
-  return MODE != Gathers::AT_USE ? 2 : QL || DT == DT_F32 ? 8 : 6;
+  return MODE == Gathers::AHEAD || MODE == Gathers::BY_WAVE ? 2 : MODE == Gathers::AT_USE && (QL || DT == DT_F32) ? 8 : 6;
 }
 
 template <int DT, bool QL, Gathers MODE>
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_waves_p
   if (MODE == Gathers::BY_WAVE && S.pixel_ids && !pixels_spread(S, pix, LIST_CELLS))
     trace_one<DT, QL, false>(S, r, pix, smp);
   else
-    trace_one<DT, QL, MODE != Gathers::AT_USE>(S, r, pix, smp);
+    trace_one<DT, QL, MODE == Gathers::AHEAD || MODE == Gathers::BY_WAVE>(S, r, pix, smp);
 }
 
 // Persistent form: blocks pull tiles from per-XCD queues (every 8th run of tiles), and
@@ -250,23 +251,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
 // 511; 128^3, 160 x 160: 388 -> 261 us, 768 x 768 895 -> 1038. The quasi-linear gathers do
 // not wait for each other; more registers alone let two run together: 192^3, 160 x 160 rays
 // 504 -> 354 us, 512 x 512 (16 per unit) 621 -> 561.
+//
+// They are exposed where they miss the caches: beyond one tile per compute unit, several
+// wavefronts of a unit cover what hits, and the instructions that issue gathers ahead only cost.
+// Each XCD's eighth of the tiles sees about an eighth of the field, so the line lies at field
+// sizes. Ahead over at use, strides 3 and 16, 192 x 192, 256 x 256 and 320 x 320 rays:
+// - FP32 80^3 1.11 1.06, 1.16 1.10, 1.08 1.04; 96^3 1.07 1.03, 1.08 1.04, 0.99 0.95; 112^3 0.91 0.85,
+//   0.94 0.88, 0.92 0.86; 192^3 0.77 0.70, 0.82 0.75, 0.84 0.78;
+// - FP32 x-pairs 112^3 1.09 1.07, 1.05 1.04, 1.03 1.02; 128^3 1.07 1.06, 1.05 1.05, 0.98 0.98; 160^3 0.98
+//   0.93, 0.98 0.98, 0.95 0.91;
+// - BF16 112^3 1.11 1.08, 1.15 1.14, 1.02 1.01; 128^3 1.03 1.02, 1.09 1.10, 0.97 0.95; 160^3 0.92 0.87,
+//   0.97 0.95, 0.92 0.89; x-pairs 128^3 1.03 0.97, 1.04 0.98, 1.02 0.98; 160^3 1.02 0.96, 1.02 0.96, 0.97
+//   0.95; 192^3 0.93 0.88, 0.97 0.92, 0.92 0.88;
+// - FP16 costs more to decode still: 256 x 256 rays, 64^3 179 / 212 us, 128^3 353 / 425, 192^3 643 / 690;
+//   x-pairs 128^3 362 / 466; 64 x 64 rays, 192^3 737 / 734.
+// Quasi-linear, us: FP32 24^3 58 / 50, 96^3 177 / 149, FP16 64^3 138 / 113 and so on, but BF16 128^3 209
+// / 218, 192^3 367 / 360. Up to one tile per unit, 64 x 64 rays: FP32 32^3 77 / 75, 128^3 389 / 246;
+// BF16 64^3 169 / 162, 192^3 678 / 503.
 Form forward_form(const LaunchPlan& P) {
-  if (P.total_tiles <= (P.tracer == 1 ? 16 : 9) * P.n_cus) return FORM_AHEAD;
+  const bool ql = P.tracer == 1;
+  double voxels = 0.0;  // of the smallest field that AHEAD is taken for
+  switch (P.dtype) {
+    case DT_F32: voxels = ql ? 0.0 : 1e6; break;
+    case DT_BF16: voxels = ql ? 4e6 : 3e6; break;
+    default: voxels = ql ? 0.0 : 3e6; break;
+  }
+  const bool ahead = ql || code_type(P.dtype) != DT_F16;
+  if (ahead && P.total_tiles <= (ql ? 16 : 9) * P.n_cus && (P.total_tiles <= P.n_cus || P.voxels >= voxels))
+    return FORM_AHEAD;
   return P.persistent ? FORM_PERSISTENT : FORM_GRID;
 }
 
 template <int DT, bool QL>
 static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
   const Form form = forward_form(P);
-  if (form == FORM_AHEAD) {
-    // a compute unit with one tile waits for every gather, whatever the list
-    auto* kernel = &k_trace_fwd<DT, QL, Gathers::AHEAD>;
-    if constexpr (!QL) {
-      if (P.lists && P.total_tiles > P.n_cus) kernel = &k_trace_fwd<DT, QL, Gathers::BY_WAVE>;
+  if constexpr (QL || code_type(DT) != DT_F16) {  // see forward_form
+    if (form == FORM_AHEAD) {
+      // a compute unit with one tile waits for every gather, whatever the list
+      auto* kernel = &k_trace_fwd<DT, QL, Gathers::AHEAD>;
+      if constexpr (!QL) {
+        if (P.lists && P.total_tiles > P.n_cus) kernel = &k_trace_fwd<DT, QL, Gathers::BY_WAVE>;
+      }
+      hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes, P.total_tiles, 1,
+                         P.total_tiles);
+      return hipGetLastError();
     }
-    hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), 0, stream, P.scenes, P.n_scenes, P.total_tiles, 1,
-                       P.total_tiles);
-    return hipGetLastError();
   }
   const dim3 block(64 * P.wpb);
   if (form == FORM_PERSISTENT) {
@@ -275,8 +304,11 @@ static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
                        P.total_tiles, P.queues);
   } else {
     const int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
-    hipLaunchKernelGGL((k_trace_fwd<DT, QL, Gathers::AT_USE>), dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes,
-                       P.total_tiles, P.wpb, nblocks);
+    auto* kernel = &k_trace_fwd<DT, QL, Gathers::AT_USE>;
+    if constexpr (!QL && DT == DT_F32) {
+      if (P.total_tiles <= 9 * P.n_cus) kernel = &k_trace_fwd<DT, QL, Gathers::AT_USE_FEW>;
+    }
+    hipLaunchKernelGGL(kernel, dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes, P.total_tiles, P.wpb, nblocks);
   }
   return hipGetLastError();
 }

@@ -66,11 +66,11 @@ def _same_rays(a, i, b, j):
         assert torch.equal(x[i].view(torch.uint8), y[j].view(torch.uint8))  # bits: NaN for missing rays
 
 
-@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16-xpair"])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "bf16-xpair"])
 @pytest.mark.parametrize("tracer", [0, 1])
 def test_forward_forms_agree_bitwise(tracer, dtype):
     """One set of scenes through the grid and the persistent kernel, and each small one alone, with
-    its gathers issued ahead: the same bits, checkpoints included."""
+    its gathers issued ahead (FP16 codes: in a small grid): the same bits, checkpoints included."""
     large = room_workload((60, 52, 44), 580, 500, seed=3, ckpt=3, pat=256)
     small = [room_workload((41, 64, 33), 77, 61, seed=4, ckpt=3, pat=256),
              room_workload((24, 20, 18), 13, 130, seed=5, ckpt=3, max_steps=40, pat=256)]
@@ -81,7 +81,7 @@ def test_forward_forms_agree_bitwise(tracer, dtype):
     for i in range(3):
         _same_rays(grid, i, pers, i)
     for i in (1, 2):
-        _same_rays(grid, i, _forward([scenes[i]], None, "ahead"), 0)
+        _same_rays(grid, i, _forward([scenes[i]], None, "grid" if dtype == "f16" and not tracer else "ahead"), 0)
 
 
 @pytest.mark.parametrize("ckpt", [1, 3, 4, 6, 8, 16, 40])
@@ -161,7 +161,7 @@ def _lists(w):
 @pytest.mark.parametrize("name", ["region", "shuffled", "random", "both"])
 def test_pixel_list_forward_equals_the_image_bitwise(name):
     """A wavefront of a list issues its gathers ahead or not as its pixels lie: the image's bits."""
-    w = room_workload((60, 64, 90), 400, 360, seed=3, ckpt=3, pat=256)
+    w = room_workload((112, 108, 90), 400, 360, seed=3, ckpt=3, pat=256)
     ids = _lists(w)[name]
     tr, image = _forward([_listed(w, ids)], None, "ahead"), _forward([_scene(w)], GRID, "ahead")
     at = torch.from_numpy(ids).to(DEV).long()

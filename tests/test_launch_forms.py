@@ -125,3 +125,18 @@ def test_second_round_of_four_wavefront_blocks():
     assert adjoint(51, 176) == adjoint(51, 176, dtype=3) == "queue"
     assert adjoint(48, 120) == "pipe" and adjoint(48, 120, scenes=2) == "queue"  # 225 tiles; 450 on two fields
     assert adjoint(32, 184) == "queue"  # 529 tiles
+
+
+@pytest.mark.parametrize("dtype,least", [(0, 100), (3, 145), (2, 145), (5, 145), (1, None), (4, None)])
+def test_gathers_ahead_by_field_size_and_type(dtype, least):
+    """Nonlinear forwards between one and nine tiles per compute unit: gathers ahead from `least`
+    voxels per axis on; FP16 codes never; up to one tile per unit whatever the size."""
+    def forward(n, side, **kw):
+        return forms(room((n, n, n), side, side, dtype=dtype, **kw))[0]
+    for n in (32, 64, 99, 100, 144, 145, 158, 159, 224):
+        few = "grid" if least is None else "ahead"
+        assert forward(n, 64) == forward(n, 128) == few
+        assert forward(n, 129) == forward(n, 384) == (few if least is not None and n >= least else "grid")
+        assert forward(n, 392) == "grid"
+        assert forward(n, 129, tracer=1) == ("grid" if dtype == 2 and n < 159 else "ahead")
+        assert forward(n, 512, tracer=1) == ("grid" if dtype == 2 and n < 159 else "ahead") and forward(n, 520, tracer=1) == "grid"
