@@ -261,6 +261,8 @@ SceneDev make_dev(const rbos_scene* S, const Launch& L, int tile_begin, int rend
   rec_divisor(d.P0, d.rec_div_m[0], d.rec_div_s[0]);
   rec_divisor(d.P01, d.rec_div_m[1], d.rec_div_s[1]);
   d.dtype = S->dtype;
+  for (int a = 1; a < 3; ++a)
+    if (std::fabs(S->cam_fwd[a]) > std::fabs(S->cam_fwd[d.view_axis])) d.view_axis = a;
   d.field = S->field;
   d.dec = (float)dec;
   d.inv_dec = (float)scale;
@@ -433,9 +435,6 @@ rbos::LaunchPlan plan_of(const Prepared& P, const rbos_scene* scenes, int n_cus)
     logs += P.table[i].n_tiles * std::log(rays_per_cell(scenes[i]));
   }
   plan.rays_per_cell = weight > 0.0 ? (float)std::exp(logs / weight) : 1.0f;
-  plan.view_axis = 0;
-  for (int a = 1; a < 3 && !P.table.empty(); ++a)
-    if (std::fabs(scenes[0].cam_fwd[a]) > std::fabs(scenes[0].cam_fwd[plan.view_axis])) plan.view_axis = a;
   return plan;
 }
 

@@ -124,6 +124,7 @@ struct SceneDev {
   int P0, P01;         // record strides: cell records (nx+1), (nx+1)(ny+1); x-pairs (nx+1), (nx+1)(ny+2)
   int P1;              // P01 / P0
   int dtype;
+  int view_axis;       // the axis the camera looks along most
   const void* field;   // cell records, starting with cell (-1, -1, -1); cells -1 .. n-1 on every axis
   float dec;           // 1 / enc_scale
   float inv_dec;       // enc_scale

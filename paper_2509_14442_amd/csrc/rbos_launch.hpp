@@ -29,7 +29,6 @@ struct LaunchPlan {
   float rays_per_cell;      // rays of one tile that share a cell, estimated from the geometry
   bool lists;               // a scene has a pixel list
   double voxels;            // of all scenes
-  int view_axis;            // axis the (first) camera looks along most
 };
 
 // Grid of a persistent kernel: blocks_per_cu blocks on every compute unit, or as many as

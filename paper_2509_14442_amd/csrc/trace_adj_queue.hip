@@ -31,8 +31,8 @@ constexpr int QUEUE_MISSES = 3;
 // does collide goes straight to the gradient. A slot that no entry touched between two
 // sweeps is written out.
 struct VoxelTable {
-  int bits[3];  // slot bits per axis
-  __host__ __device__ int slots() const { return 1 << (bits[0] + bits[1] + bits[2]); }
+  int along, across;  // slot bits on the axis the scene's camera looks along, and on the others
+  __host__ __device__ int slots() const { return 1 << (along + 2 * across); }
 };
 
 struct QueuePlan {
@@ -51,11 +51,14 @@ struct QueueMerge {
   double* sums;    // LDS: the table's voxel sums
   unsigned* tags;  // LDS: the slot's voxel, SLOT_FREE when free, with SLOT_TOUCHED since the last sweep
   QueuePlan Q;
+  int bits[3];     // the table's slot bits per axis
   int count;       // wave-uniform: queue entries
   int claims;      // wave-uniform: slots taken since the last sweep
 
-  __device__ __forceinline__ QueueMerge(float* lds, const QueuePlan& plan, int lane)
+  __device__ __forceinline__ QueueMerge(const SceneDev& S, float* lds, const QueuePlan& plan, int lane)
       : key(CELL_NONE), Q(plan), count(0), claims(0) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) bits[a] = a == S.view_axis ? plan.table.along : plan.table.across;
     vals = reinterpret_cast<f32x4*>(lds);
     keys = reinterpret_cast<int*>(lds + 8 * plan.entries);
     sums = reinterpret_cast<double*>(lds + 9 * plan.entries);
@@ -97,13 +100,13 @@ struct QueueMerge {
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const unsigned c0 = (unsigned)max(p[a] - 1, 0), c1 = (unsigned)min(p[a], S.n[a] - 1);
-        const unsigned mask = (1u << Q.table.bits[a]) - 1u;
+        const unsigned mask = (1u << bits[a]) - 1u;
         v[a][0] = c0 * stride;
         v[a][1] = c1 * stride;
         s[a][0] = (c0 & mask) << shift;
         s[a][1] = (c1 & mask) << shift;
         stride *= (unsigned)S.n[a];
-        shift += Q.table.bits[a];
+        shift += bits[a];
       }
       // claim or find the slots: all eight exchanges in flight together
       unsigned t[8];
@@ -258,7 +261,7 @@ __device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, 
   const int m_chunks = K / KS;
   const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
   f32x4* rows = reinterpret_cast<f32x4*>(lds) + lane;
-  QueueMerge M(lds + KS * 3 * 64 * 4, plan, lane);
+  QueueMerge M(S, lds + KS * 3 * 64 * 4, plan, lane);
 
   // The state a chunk's replay starts from and its first samples, loaded while the chunk
   // before it (the one after it on the ray) is reversed.
@@ -491,7 +494,7 @@ __device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, i
   }
   // sum chunk nch + 1 - r in round r
   const int share = wave - 2;  // 0: the chunk's first steps
-  QueueMerge M(queues + (size_t)share * (plan.bytes() / 4), plan, lane);
+  QueueMerge M(S, queues + (size_t)share * (plan.bytes() / 4), plan, lane);
   const int i0 = KS * share / PIPE_SUMS, i1 = KS * (share + 1) / PIPE_SUMS;
   lds_barrier();
   lds_barrier();
@@ -556,7 +559,7 @@ __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int til
   const int npts = wave_max_nonneg(active ? 2 * n + 1 : 0);
   const int j0 = (int)((long long)npts * part / parts), j1 = (int)((long long)npts * (part + 1) / parts);
   const float h = S.hf, h_6 = S.h_6;
-  QueueMerge M(lds, plan, lane);
+  QueueMerge M(S, lds, plan, lane);
   float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
   auto sample_point_j = [&](int j, Sample& P) {
     const float jf = (float)j;
@@ -624,14 +627,10 @@ static int queue_chunk(const LaunchPlan& P) {
 // 8 slots per axis hold a tile's cells across the view down to one ray per cell; along the
 // view, 16: the slots the bundle has left wait there for the sweep (8: 1776 against 1223 us
 // on the 128^3 room with 256 x 256 rays).
-static QueuePlan queue_plan(const LaunchPlan& P) {
-  QueuePlan q{128, VoxelTable{{3, 3, 3}}};
-  q.table.bits[P.view_axis] = 4;
-  return q;
-}
+constexpr QueuePlan QUEUE_PLAN{128, VoxelTable{4, 3}};
 
 static size_t queue_lds(const LaunchPlan& P) {
-  return (P.tracer == 1 ? 0 : (size_t)queue_chunk(P) * 3 * 64 * 16) + queue_plan(P).bytes();
+  return (P.tracer == 1 ? 0 : (size_t)queue_chunk(P) * 3 * 64 * 16) + QUEUE_PLAN.bytes();
 }
 
 // With every wavefront resident at once (4 per compute unit by registers, fewer by LDS), the
@@ -720,8 +719,8 @@ Form adjoint_form(const LaunchPlan& P) {
 
 template <int DT, int KS>
 static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
-  QueuePlan plan = queue_plan(P);
-  plan.table.bits[P.view_axis] = 3;  // half a chunk's steps each; 16 slots along the view gain nothing (538, 517 us)
+  QueuePlan plan = QUEUE_PLAN;
+  plan.table.along = 3;  // half a chunk's steps each; 16 slots along the view gain nothing (538, 517 us)
   const size_t lds = (size_t)pipe_rows<KS>() * 5 * 16 + 3 * 64 * 4 + PIPE_SUMS * plan.bytes();
   hipLaunchKernelGGL((k_trace_adj_pipe<DT, KS>), dim3(P.total_tiles), dim3(64 * (2 + PIPE_SUMS)), lds, stream, P.scenes,
                      P.n_scenes, P.total_tiles, plan);
@@ -730,11 +729,10 @@ static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
 
 template <int DT, int KS>
 static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
-  const QueuePlan plan = queue_plan(P);
   static_assert(adj_floats_per_wave<KS == 3 ? 3 : 4>() <= KS * 3 * 64 * 4 + 128 * 9, "the coherent sweep's LDS");
   auto* kernel = P.lists ? &k_trace_adj_list<DT, KS> : &k_trace_adj_queue<DT, KS>;
   hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
-                     P.total_tiles, plan);
+                     P.total_tiles, QUEUE_PLAN);
   return hipGetLastError();
 }
 
@@ -742,9 +740,8 @@ template <int DT>
 static hipError_t launch_queue_dt(const LaunchPlan& P, hipStream_t stream) {
   if (P.tracer == 1) {
     const int parts = std::max(1, std::min(16, 8 * P.n_cus / P.total_tiles));
-    const QueuePlan plan = queue_plan(P);
     hipLaunchKernelGGL(k_trace_adj_ql_queue<DT>, dim3(P.total_tiles, parts), dim3(64), queue_lds(P), stream, P.scenes,
-                       P.n_scenes, P.total_tiles, parts, plan);
+                       P.n_scenes, P.total_tiles, parts, QUEUE_PLAN);
     return hipGetLastError();
   }
   if (adjoint_form(P) == FORM_PIPE)

@@ -213,3 +213,25 @@ def test_unused_persistent_flag_enqueues_nothing():
             run()
             written.append((tr.workspace != 0xA5).nonzero().max().item())
     assert written[:2] == written[2:]
+
+
+@pytest.mark.parametrize("tracer", [0, 1])
+def test_queued_batch_of_views_along_every_axis(tracer):
+    """Cameras along +y, +x and -z in one queued call: each scene's voxel table lies along its own
+    view."""
+    views = [{}, dict(cam_pos=(-1.5, 2.0, 1.5), cam_fwd=(1.0, 0.0, 0.0), cam_right=(0.0, -1.0, 0.0), cam_up=(0.0, 0.0, 1.0),
+                      wall_origin=(4.0, 2.0, 1.5), wall_normal=(-1.0, 0.0, 0.0), wall_u=(0.0, -1.0, 0.0), wall_v=(0.0, 0.0, 1.0)),
+             dict(cam_pos=(2.0, 2.0, 4.5), cam_fwd=(0.0, 0.0, -1.0), cam_right=(1.0, 0.0, 0.0), cam_up=(0.0, 1.0, 0.0),
+                  wall_origin=(2.0, 2.0, 0.0), wall_normal=(0.0, 0.0, 1.0), wall_u=(1.0, 0.0, 0.0), wall_v=(0.0, 1.0, 0.0))]
+    ws = []
+    for i, view in enumerate(views):
+        w = room_workload((60, 68, 56), 120, 112, seed=20 + i, ckpt=3, pat=256)
+        w.scene = w.scene.replace(tracer=tracer, **view)
+        ws.append(w)
+    scenes = [_scene(w) for w in ws]
+    seeds = _seeds(scenes, 4)
+    tr = api.Tracer(scenes)
+    assert tr.forms()[1] == "queue"
+    for w, sc, d, g in zip(ws, scenes, seeds, tr.forward().adjoint(dL_duv=seeds)):
+        print("view", w.scene.cam_fwd, "tracer", tracer, flush=True)
+        _near(g, _gradient(w, sc, d))
