@@ -468,8 +468,8 @@ struct DeltaSide : BackwardSet {
 };
 
 // The side that forms the parameter gradient. Operands over the points are 0 past the end.
-// (The loads behind them still lie inside the workspace: up to 127 rows past a layer, 32 KB,
-// are the next layers, then weights and partials.)
+// (The loads behind them run up to BWD_POINTS - 1 rows past a layer: the next layers, and ACT_TAIL
+// rows that the workspace holds past the last one.)
 template <int D>
 struct GradSide : BackwardSet {
   int c, h, c4, k4, mt, nt;
@@ -983,11 +983,13 @@ inline long long wgrad_blocks(long long rows) {
 
 }  // namespace
 
+// Rows past the activations: a backward block loads whole chunks of points (see GradSide).
+constexpr size_t ACT_TAIL = BWD_POINTS - 1;
+
 size_t mlp_work_bytes(int depth, long long n) {
   const long long nblk = wgrad_blocks(n);
   size_t b = 0;
-  b += al256(sizeof(float) * (size_t)depth * (size_t)n * MLP_WIDTH);
-  b += 2 * al256(sizeof(float) * (size_t)n * MLP_WIDTH);  // spare: the size callers have allocated so far
+  b += al256(sizeof(float) * ((size_t)depth * (size_t)n + ACT_TAIL) * MLP_WIDTH);
   b += al256(sizeof(float) * (size_t)depth * MLP_WIDTH * MLP_WIDTH);
   b += al256(sizeof(float) * (size_t)(depth + 1) * (size_t)nblk * MLP_PART);
   b += al256(sizeof(float) * 4 * (size_t)n);
@@ -999,8 +1001,7 @@ void mlp_work_carve(void* ws, int depth, long long n, MlpWork& w) {
   w.nblk = (int)nblk;
   unsigned char* p = static_cast<unsigned char*>(ws);
   w.act = reinterpret_cast<float*>(p);
-  p += al256(sizeof(float) * (size_t)depth * (size_t)n * MLP_WIDTH);
-  p += 2 * al256(sizeof(float) * (size_t)n * MLP_WIDTH);  // spare
+  p += al256(sizeof(float) * ((size_t)depth * (size_t)n + ACT_TAIL) * MLP_WIDTH);
   w.wt = reinterpret_cast<float*>(p);
   p += al256(sizeof(float) * (size_t)depth * MLP_WIDTH * MLP_WIDTH);
   w.partial = reinterpret_cast<float*>(p);

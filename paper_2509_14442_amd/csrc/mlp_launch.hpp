@@ -25,7 +25,7 @@ struct MlpDev {
 // activations a_1 .. a_depth [n][64], transposed hidden weights (depth - 1) x [64][64],
 // per-block partial parameter gradients and the normalised inputs [n][4].
 struct MlpWork {
-  float* act;       // depth x [n][64]
+  float* act;       // depth x [n][64], then the rows a backward block's last loads may reach
   float* wt;        // (depth - 1) x [64][64]
   float* partial;   // (depth + 1) x nblk x MLP_PART floats
   float* xh;        // [n][4] normalised inputs (fourth column 0)
