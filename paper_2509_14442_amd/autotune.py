@@ -39,9 +39,10 @@ LAUNCHES: List[Tuple[Tuple[int, int], int, bool, int]] = [
     ((8, 8), 2, True, 0),
     ((8, 8), 4, True, 2),
 ]
-# 1: every step stored (24 B per ray-step), no replay; 3, 4: chunks that record their
-# samples for the reverse; 6: chunks of 6 at 4 wavefronts per SIMD; 8, 16, 32, 64: chunks
-# of 8
+# 1: every step stored (24 B per ray-step), no replay; 3, 4: a segment is one recorded chunk;
+# 6, 8: chunks of 3 or 4 reached by steps from the checkpoint before them; 16, 32, 64: chunks
+# whose start states a pass over the segment leaves. Calls in a form with a grid of its own
+# (Tracer.forms) time alike for every launch of one tile shape.
 STRIDES = (1, 3, 4, 6, 8, 16, 32, 64)
 LAYOUTS = ("cell", "xpair")
 

@@ -222,7 +222,7 @@ enum class Replay {
 // Adjoint of 1M rays, against chunks of 8 (stride 6: of 6) step states in LDS, whose samples the
 // reverse located again, at 3 (4) wavefronts per SIMD: 6 5360 -> 5000 us, 8 5620 -> 5370, 16 6200
 // -> 5600. 512 x 512 rays, stride 16: 2910 -> 2010, since its 4096 wavefronts now reside at once.
-constexpr int PART_CHUNKS = 8;  // chunks of a part: strides up to 24 are one part
+constexpr int PART_CHUNKS = 8;  // chunks of a part: strides up to 24, in chunks of 4 up to 32, are one part
 
 template <int CHUNK>
 constexpr int chunk_floats() { return CHUNK * 3 * 64 * 4; }
@@ -260,7 +260,7 @@ __device__ __forceinline__ void record_chunk(const SceneDev& S, const RayBase& B
   sample_at_state<DT>(S, B, st, P);
 #pragma unroll 1
   for (int i = 0; i < cnt - 1; ++i) sharma_step<DT>(S, B, st, P, SampleRow{smp + i * 3 * 64 + lane});
-  sharma_step<DT, SampleRow, NoIssue, StepEnd::SAMPLES>(S, B, st, P, SampleRow{smp + (cnt - 1) * 3 * 64 + lane});
+  sharma_step<DT, SampleRow, NoIssue, false>(S, B, st, P, SampleRow{smp + (cnt - 1) * 3 * 64 + lane});
 }
 
 // The three samples of the step from st, located as sharma_step does from the same forces.

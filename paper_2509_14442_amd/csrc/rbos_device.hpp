@@ -704,8 +704,8 @@ __device__ __forceinline__ float small_part(const RayBase& B, int a, float jf, f
 
 // Deviations (grid units) of the stage points of a Sharma step from the state's base
 // point, given the stage forces in code units (G = K / km): P2 = x + h/2 v + h^2/8 K1,
-// P3 = x + h v + h^2/2 K2, with x + h v shared with the position update. The adjoint's
-// reverse relocates stage points with these same functions.
+// P3 = x + h v + h^2/2 K2, with x + h v shared with the position update. The stride-1 adjoint
+// locates its steps' samples from the stored states with these same functions.
 __device__ __forceinline__ float stage2_dev(const SceneDev& S, const State& st, int a, float G1) {
   return fmaf(S.c_p2[a], G1, fmaf(S.h_2, st.e[a], st.d[a]));
 }
@@ -745,12 +745,10 @@ __device__ __forceinline__ void sample_at_state(const SceneDev& S, const RayBase
 // third point and the new position differ by h^2/6 (K1 + 2 K2 - 3 K2), ~1e-7 cell, so the
 // third sample's coefficients serve the new state unless its record is another one: two
 // gathers per step instead of three (1M-ray room: forward 1480 -> 1450 us, 512 x 512 rays 534
-// -> 477, stride-3 adjoint 4570 -> 4390). A step may end early: at SAMPLES once its third
-// sample is located and recorded (no force there, no new state; the last step of a replayed
-// chunk needs only its samples), at STATE with the new state but not its sample (P and st.pu
-// are then left undefined).
-enum class StepEnd { SAMPLES, STATE, NEXT_SAMPLE };
-template <int DT, class Record = NoRecord, class Issue = NoIssue, StepEnd END = StepEnd::NEXT_SAMPLE>
+// -> 477, stride-3 adjoint 4570 -> 4390). With FULL false the step ends once its third sample is
+// located and recorded (no force there, no new state): the last step of a replayed chunk needs
+// only its samples.
+template <int DT, class Record = NoRecord, class Issue = NoIssue, bool FULL = true>
 __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B, State& st, Sample& P,
                                             const Record& record = Record(), const Issue& issue = Issue()) {
   float G1[3], G2[3], G3[3], bh2[3], bh3[3], sm[3], base3[3];
@@ -782,7 +780,7 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
   locate3(S, bh3, sm, C);
   rec = cell_index(S, C);
   record(2, rec, C.f);
-  if constexpr (END == StepEnd::SAMPLES) return;
+  if constexpr (!FULL) return;
   fetch_cell<DT>(S, rec, P.c);
   force_code(S, P.c, C.f, G3);
 #pragma unroll
@@ -794,7 +792,6 @@ __device__ __forceinline__ void sharma_step(const SceneDev& S, const RayBase& B,
     st.bh[a] = bh3[a];
   }
   st.jf += 2.0f;
-  if constexpr (END == StepEnd::STATE) return;
 #pragma unroll
   for (int a = 0; a < 3; ++a)
     locate_floor(st.bh[a], small_part(B, a, st.jf, st.d[a]), S.n_f[a], C.p[a], P.f[a], st.pu[a]);

@@ -5,8 +5,8 @@
 // in chunks of 3 or 4, aligned on the step index so that the tile's rays move through the same
 // cells together. A chunk is replayed forward from a state at its start (a checkpoint, or one
 // reached from there), keeping in LDS the cells and fractions of each step's three samples,
-// and then reversed step by step. Each
-// sample's contributions are merged per lane, as monomial coefficients, while the ray
+// and then reversed step by step; at stride 1 every step's state is at hand and nothing is
+// replayed. Each sample's contributions are merged per lane, as monomial coefficients, while the ray
 // stays in one cell; lanes that left the same cell are summed across the wavefront into a
 // per-wavefront LDS cache of cell totals, which goes to the gradient with one FP64 atomic
 // per corner. A wavefront lowers its issue priority while replaying and raises it while
