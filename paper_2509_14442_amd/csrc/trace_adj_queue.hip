@@ -30,42 +30,39 @@ constexpr int QUEUE_MISSES = 3;
 // slot of its low coordinate bits, so a compact bundle of rays meets no collision; what
 // does collide goes straight to the gradient. A slot that no entry touched between two
 // sweeps is written out.
-struct VoxelTable {
-  int along, across;  // slot bits on the axis the scene's camera looks along, and on the others
-  __host__ __device__ int slots() const { return 1 << (along + 2 * across); }
-};
-
-struct QueuePlan {
-  int entries;  // queue entries (>= 128)
-  VoxelTable table;
-  __host__ __device__ size_t bytes() const { return (size_t)entries * 36 + (size_t)table.slots() * 12; }
-};
+//
+// 8 slots per axis hold a tile's cells across the view down to one ray per cell; along the
+// scene's view, 16: the slots the bundle has left wait there for the sweep (8: 1776 against
+// 1223 us on the 128^3 room with 256 x 256 rays). Half a chunk's steps each leave fewer
+// behind: 16 gain nothing in the four-wavefront form (538, 517 us).
+constexpr int QUEUE_ENTRIES = 128;
+constexpr int QUEUE_ACROSS = 3, QUEUE_ALONG = 4, PIPE_ALONG = 3;  // slot bits
 
 constexpr unsigned SLOT_FREE = 0x7fffffffu, SLOT_TOUCHED = 0x80000000u;  // voxel indices are < 2^27
 
+template <int ALONG>
 struct QueueMerge {
+  static constexpr int SLOTS = 1 << (ALONG + 2 * QUEUE_ACROSS);
+  static constexpr size_t BYTES = (size_t)QUEUE_ENTRIES * 36 + (size_t)SLOTS * 12;
+
   float acc[8];
   int key;         // record index of the lane's cell, CELL_NONE when empty
   f32x4* vals;     // LDS: 8 monomial totals per entry
   int* keys;       // LDS: the entry's cell
   double* sums;    // LDS: the table's voxel sums
   unsigned* tags;  // LDS: the slot's voxel, SLOT_FREE when free, with SLOT_TOUCHED since the last sweep
-  QueuePlan Q;
-  int bits[3];     // the table's slot bits per axis
   int count;       // wave-uniform: queue entries
   int claims;      // wave-uniform: slots taken since the last sweep
 
-  __device__ __forceinline__ QueueMerge(const SceneDev& S, float* lds, const QueuePlan& plan, int lane)
-      : key(CELL_NONE), Q(plan), count(0), claims(0) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) bits[a] = a == S.view_axis ? plan.table.along : plan.table.across;
+  __device__ __forceinline__ QueueMerge(float* lds, int lane)
+      : key(CELL_NONE), count(0), claims(0) {
     vals = reinterpret_cast<f32x4*>(lds);
-    keys = reinterpret_cast<int*>(lds + 8 * plan.entries);
-    sums = reinterpret_cast<double*>(lds + 9 * plan.entries);
-    tags = reinterpret_cast<unsigned*>(sums + plan.table.slots());
+    keys = reinterpret_cast<int*>(lds + 8 * QUEUE_ENTRIES);
+    sums = reinterpret_cast<double*>(lds + 9 * QUEUE_ENTRIES);
+    tags = reinterpret_cast<unsigned*>(sums + SLOTS);
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
-    for (int i = lane; i < plan.table.slots(); i += 64) {
+    for (int i = lane; i < SLOTS; i += 64) {
       sums[i] = 0.0;
       tags[i] = SLOT_FREE;
     }
@@ -100,13 +97,14 @@ struct QueueMerge {
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const unsigned c0 = (unsigned)max(p[a] - 1, 0), c1 = (unsigned)min(p[a], S.n[a] - 1);
-        const unsigned mask = (1u << bits[a]) - 1u;
+        const int bits = ALONG == QUEUE_ACROSS || a != S.view_axis ? QUEUE_ACROSS : ALONG;
+        const unsigned mask = (1u << bits) - 1u;
         v[a][0] = c0 * stride;
         v[a][1] = c1 * stride;
         s[a][0] = (c0 & mask) << shift;
         s[a][1] = (c1 & mask) << shift;
         stride *= (unsigned)S.n[a];
-        shift += bits[a];
+        shift += bits;
       }
       // claim or find the slots: all eight exchanges in flight together
       unsigned t[8];
@@ -140,7 +138,7 @@ struct QueueMerge {
   // Write out the slots that were not touched since the last sweep (all with `every`).
   __device__ __forceinline__ void sweep(const SceneDev& S, bool every, int lane) {
     wave_lds_order();
-    const int n = Q.table.slots();
+    const int n = SLOTS;
 #pragma unroll 2
     for (int i = lane; i < n; i += 64) {
       const unsigned t = tags[i];
@@ -159,7 +157,7 @@ struct QueueMerge {
 
   // The sums of the lanes in out_m (those lanes have out) become entries, and restart.
   __device__ __forceinline__ void push(const SceneDev& S, bool out, unsigned long long out_m, int lane) {
-    if (count + 64 > Q.entries) insert(S, 64, lane);
+    if (count + 64 > QUEUE_ENTRIES) insert(S, 64, lane);
     // cells with many leaving lanes are summed first; the scan ends with the lanes left too
     // few, or after QUEUE_MISSES cells of few lanes
     unsigned long long pend = out_m, few = 0;
@@ -215,7 +213,7 @@ struct QueueMerge {
   // atomics' latency runs beside the arithmetic of a step.
   __device__ __forceinline__ void ease(const SceneDev& S, int lane) {
     if (count >= 64) insert(S, 64, lane);
-    if (claims >= Q.table.slots() / 4) sweep(S, false, lane);
+    if (claims >= SLOTS / 4) sweep(S, false, lane);
   }
 
   __device__ __forceinline__ void drain(const SceneDev& S, int lane) {
@@ -249,8 +247,7 @@ __device__ __forceinline__ void load_rows(const SceneDev& S, const f32x4* row, S
 // recorded samples (record index and fractions), then reversed, the rows and cells of a
 // step loaded one step ahead.
 template <int DT, int KS>
-__device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, int lane, float* lds,
-                                                   const QueuePlan& plan) {
+__device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, int lane, float* lds) {
   AdjRay R;
   adjoint_ray_setup(S, tile, lane, R);
   const int q = R.q, n = R.n;
@@ -261,7 +258,7 @@ __device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, 
   const int m_chunks = K / KS;
   const int nseg = wave_max_nonneg(active ? (n + K - 1) / K : 0);
   f32x4* rows = reinterpret_cast<f32x4*>(lds) + lane;
-  QueueMerge M(S, lds + KS * 3 * 64 * 4, plan, lane);
+  QueueMerge<QUEUE_ALONG> M(lds + KS * 3 * 64 * 4, lane);
 
   // The state a chunk's replay starts from and its first samples, loaded while the chunk
   // before it (the one after it on the ray) is reversed.
@@ -327,11 +324,11 @@ __device__ __forceinline__ void adjoint_tile_queue(const SceneDev& S, int tile, 
 
 template <int DT, int KS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_queue(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles) {
   extern __shared__ float lds[];
   const int gtile = xcd_remap(blockIdx.x, total_tiles);
   const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
-  adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds, plan);
+  adjoint_tile_queue<DT, KS>(S, gtile - S.tile_begin, threadIdx.x, lds);
 }
 
 // Pixel lists beyond the four-wavefront form. The list lies on the device, so the tile's
@@ -351,13 +348,13 @@ __device__ __forceinline__ bool tile_bunched(const SceneDev& S, int tile, int la
 
 template <int DT, int KS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_list(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles) {
   extern __shared__ float lds[];
   const int gtile = xcd_remap(blockIdx.x, total_tiles);
   const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
   const int tile = gtile - S.tile_begin, lane = threadIdx.x;
   if (!S.pixel_ids || !tile_bunched(S, tile, lane))
-    adjoint_tile_queue<DT, KS>(S, tile, lane, lds, plan);
+    adjoint_tile_queue<DT, KS>(S, tile, lane, lds);
   else if constexpr (KS == 3)
     adjoint_tile<DT, Replay::SEGMENT, 3>(S, tile, lane, lds);
   else if constexpr (KS == 4)
@@ -408,8 +405,7 @@ constexpr int pipe_rows() { return KS * 3 * 64; }  // samples of a chunk
 constexpr int PIPE_SUMS = 2;  // wavefronts that sum
 
 template <int DT, int KS>
-__device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, int wave, int lane, float* lds,
-                                                  const QueuePlan& plan) {
+__device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, int wave, int lane, float* lds) {
   constexpr int ROWS = pipe_rows<KS>();
   f32x4* const samples = reinterpret_cast<f32x4*>(lds) + lane;  // ring of 3 chunks
   f32x4* const terms = samples + 3 * ROWS;                      // ring of 2 chunks
@@ -495,7 +491,7 @@ __device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, i
   }
   // sum chunk nch + 1 - r in round r
   const int share = wave - 2;  // 0: the chunk's first steps
-  QueueMerge M(S, queues + (size_t)share * (plan.bytes() / 4), plan, lane);
+  QueueMerge<PIPE_ALONG> M(queues + (size_t)share * (QueueMerge<PIPE_ALONG>::BYTES / 4), lane);
   const int i0 = KS * share / PIPE_SUMS, i1 = KS * (share + 1) / PIPE_SUMS;
   lds_barrier();
   lds_barrier();
@@ -539,11 +535,11 @@ __device__ __forceinline__ void adjoint_tile_pipe(const SceneDev& S, int tile, i
 
 template <int DT, int KS>
 __global__ __launch_bounds__(64 * (2 + PIPE_SUMS)) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_trace_adj_pipe(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, QueuePlan plan) {
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles) {
   extern __shared__ float lds[];
   const int gtile = xcd_remap(blockIdx.x, total_tiles);
   const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
-  adjoint_tile_pipe<DT, KS>(S, gtile - S.tile_begin, wave_uniform(threadIdx.x >> 6), threadIdx.x & 63, lds, plan);
+  adjoint_tile_pipe<DT, KS>(S, gtile - S.tile_begin, wave_uniform(threadIdx.x >> 6), threadIdx.x & 63, lds);
 }
 
 // Quasi-linear tracer: the line points j = 0 .. 2n are independent of each other, so a
@@ -551,7 +547,7 @@ __global__ __launch_bounds__(64 * (2 + PIPE_SUMS)) __attribute__((amdgpu_waves_p
 // the adjoint of the entry velocity: each part adds its own share.
 template <int DT>
 __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int tile, int part, int parts, int lane,
-                                                      float* lds, const QueuePlan& plan) {
+                                                      float* lds) {
   AdjRay R;
   adjoint_ray_setup(S, tile, lane, R);
   const int n = R.n;
@@ -560,7 +556,7 @@ __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int til
   const int npts = wave_max_nonneg(active ? 2 * n + 1 : 0);
   const int j0 = (int)((long long)npts * part / parts), j1 = (int)((long long)npts * (part + 1) / parts);
   const float h = S.hf, h_6 = S.h_6;
-  QueueMerge M(S, lds, plan, lane);
+  QueueMerge<QUEUE_ALONG> M(lds, lane);
   float pv[3] = {0.0f, 0.0f, 0.0f};  // dL/dv0 through the stage points (grid units)
   auto sample_point_j = [&](int j, Sample& P) {
     const float jf = (float)j;
@@ -613,11 +609,11 @@ __device__ __forceinline__ void adjoint_tile_ql_queue(const SceneDev& S, int til
 
 template <int DT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_trace_adj_ql_queue(
-    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int parts, QueuePlan plan) {
+    const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int parts) {
   extern __shared__ float lds[];
   const int gtile = xcd_remap(blockIdx.x, total_tiles);
   const SceneDev& S = scenes[find_scene(scenes, n_scenes, gtile)];
-  adjoint_tile_ql_queue<DT>(S, gtile - S.tile_begin, blockIdx.y, parts, threadIdx.x, lds, plan);
+  adjoint_tile_ql_queue<DT>(S, gtile - S.tile_begin, blockIdx.y, parts, threadIdx.x, lds);
 }
 
 // Steps per recorded chunk for a checkpoint stride.
@@ -625,13 +621,8 @@ static int queue_chunk(const LaunchPlan& P) {
   return P.ckpt_k == 3 || P.ckpt_k == 4 || P.ckpt_k == 6 ? P.ckpt_k : 8;
 }
 
-// 8 slots per axis hold a tile's cells across the view down to one ray per cell; along the
-// view, 16: the slots the bundle has left wait there for the sweep (8: 1776 against 1223 us
-// on the 128^3 room with 256 x 256 rays).
-constexpr QueuePlan QUEUE_PLAN{128, VoxelTable{4, 3}};
-
 static size_t queue_lds(const LaunchPlan& P) {
-  return (P.tracer == 1 ? 0 : (size_t)queue_chunk(P) * 3 * 64 * 16) + QUEUE_PLAN.bytes();
+  return (P.tracer == 1 ? 0 : (size_t)queue_chunk(P) * 3 * 64 * 16) + QueueMerge<QUEUE_ALONG>::BYTES;
 }
 
 // With every wavefront resident at once (4 per compute unit by registers, fewer by LDS), the
@@ -720,20 +711,18 @@ Form adjoint_form(const LaunchPlan& P) {
 
 template <int DT, int KS>
 static hipError_t launch_pipe_t(const LaunchPlan& P, hipStream_t stream) {
-  QueuePlan plan = QUEUE_PLAN;
-  plan.table.along = 3;  // half a chunk's steps each; 16 slots along the view gain nothing (538, 517 us)
-  const size_t lds = (size_t)pipe_rows<KS>() * 5 * 16 + 3 * 64 * 4 + PIPE_SUMS * plan.bytes();
+  const size_t lds = (size_t)pipe_rows<KS>() * 5 * 16 + 3 * 64 * 4 + PIPE_SUMS * QueueMerge<PIPE_ALONG>::BYTES;
   hipLaunchKernelGGL((k_trace_adj_pipe<DT, KS>), dim3(P.total_tiles), dim3(64 * (2 + PIPE_SUMS)), lds, stream, P.scenes,
-                     P.n_scenes, P.total_tiles, plan);
+                     P.n_scenes, P.total_tiles);
   return hipGetLastError();
 }
 
 template <int DT, int KS>
 static hipError_t launch_queue_t(const LaunchPlan& P, hipStream_t stream) {
-  static_assert(adj_floats_per_wave<KS == 3 ? 3 : 4>() <= KS * 3 * 64 * 4 + 128 * 9, "the coherent sweep's LDS");
+  static_assert(adj_floats_per_wave<KS == 3 ? 3 : 4>() <= KS * 3 * 64 * 4 + QUEUE_ENTRIES * 9, "the coherent sweep's LDS");
   auto* kernel = P.lists ? &k_trace_adj_list<DT, KS> : &k_trace_adj_queue<DT, KS>;
   hipLaunchKernelGGL(kernel, dim3(P.total_tiles), dim3(64), queue_lds(P), stream, P.scenes, P.n_scenes,
-                     P.total_tiles, QUEUE_PLAN);
+                     P.total_tiles);
   return hipGetLastError();
 }
 
@@ -742,7 +731,7 @@ static hipError_t launch_queue_dt(const LaunchPlan& P, hipStream_t stream) {
   if (P.tracer == 1) {
     const int parts = std::max(1, std::min(16, 8 * P.n_cus / P.total_tiles));
     hipLaunchKernelGGL(k_trace_adj_ql_queue<DT>, dim3(P.total_tiles, parts), dim3(64), queue_lds(P), stream, P.scenes,
-                       P.n_scenes, P.total_tiles, parts, QUEUE_PLAN);
+                       P.n_scenes, P.total_tiles, parts);
     return hipGetLastError();
   }
   if (adjoint_form(P) == FORM_PIPE)
