@@ -245,40 +245,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
   }
 }
 
-// Few wavefronts leave a step's gathers exposed: up to 9 tiles per compute unit the kernel
-// that issues them ahead runs, one wavefront per block so that they spread over the chip.
-// 192^3 room, stride 16, 160 x 160 rays: 628 -> 378 us, 384 x 384 (9 tiles per unit) 668 ->
-// 511; 128^3, 160 x 160: 388 -> 261 us, 768 x 768 895 -> 1038. The quasi-linear gathers do
-// not wait for each other; more registers alone let two run together: 192^3, 160 x 160 rays
-// 504 -> 354 us, 512 x 512 (16 per unit) 621 -> 561.
-//
-// They are exposed where they miss the caches: beyond one tile per compute unit, several
-// wavefronts of a unit cover what hits, and the instructions that issue gathers ahead only cost.
-// Each XCD's eighth of the tiles sees about an eighth of the field, so the line lies at field
-// sizes. Ahead over at use, strides 3 and 16, 192 x 192, 256 x 256 and 320 x 320 rays:
-// - FP32 80^3 1.11 1.06, 1.16 1.10, 1.08 1.04; 96^3 1.07 1.03, 1.08 1.04, 0.99 0.95; 112^3 0.91 0.85,
-//   0.94 0.88, 0.92 0.86; 192^3 0.77 0.70, 0.82 0.75, 0.84 0.78;
-// - FP32 x-pairs 112^3 1.09 1.07, 1.05 1.04, 1.03 1.02; 128^3 1.07 1.06, 1.05 1.05, 0.98 0.98; 160^3 0.98
-//   0.93, 0.98 0.98, 0.95 0.91;
-// - BF16 112^3 1.11 1.08, 1.15 1.14, 1.02 1.01; 128^3 1.03 1.02, 1.09 1.10, 0.97 0.95; 160^3 0.92 0.87,
-//   0.97 0.95, 0.92 0.89; x-pairs 128^3 1.03 0.97, 1.04 0.98, 1.02 0.98; 160^3 1.02 0.96, 1.02 0.96, 0.97
-//   0.95; 192^3 0.93 0.88, 0.97 0.92, 0.92 0.88;
-// - FP16 costs more to decode still: 256 x 256 rays, 64^3 179 / 212 us, 128^3 353 / 425, 192^3 643 / 690;
-//   x-pairs 128^3 362 / 466; 64 x 64 rays, 192^3 737 / 734.
-// Quasi-linear, us: FP32 24^3 58 / 50, 96^3 177 / 149, FP16 64^3 138 / 113 and so on, but BF16 128^3 209
-// / 218, 192^3 367 / 360. Up to one tile per unit, 64 x 64 rays: FP32 32^3 77 / 75, 128^3 389 / 246;
-// BF16 64^3 169 / 162, 192^3 678 / 503.
+// Few wavefronts leave a step's gathers exposed: the kernel that issues them ahead runs, one
+// wavefront per block so that they spread over the chip. The quasi-linear gathers do not wait
+// for each other; more registers alone let two run together. Many wavefronts cover each
+// other's gathers, the sooner the more of the field the caches hold, and the instructions
+// that issue them ahead only cost. Each forward after its field's encoding, as a fit runs
+// them, at use / ahead, us, 140 x 140 rays (1.3 tiles per compute unit), 256 x 256 (4) and
+// 384 x 384 (9), stride 3:
+// - FP32 24^3 78 / 76, 74 / 80, 93 / 98; 64^3 182 / 162, 167 / 174, 205 / 201; 96^3 277 / 231, 255 / 244,
+//   296 / 290; 192^3 583 / 437, 546 / 461, 608 / 547; stride 16, 64^3 169 / 147, 151 / 144, 185 / 183;
+// - x-pairs of FP32 32^3 104 / 104, 99 / 105, 126 / 131; 96^3 291 / 266, 258 / 274, 320 / 327; 192^3 617 /
+//   528, 542 / 537, 645 / 633; of BF16 96^3 306 / 269, 265 / 282, 325 / 342; 192^3 646 / 532, 567 / 543, 657 / 657;
+// - BF16 32^3 100 / 101, 98 / 108, 126 / 129; 96^3 279 / 260, 253 / 267, 312 / 315; 192^3 599 / 515, 548 / 525,
+//   636 / 617;
+// - FP16 costs more to decode still: 64^3 206 / 232, 190 / 217, 237 / 255; 192^3 652 / 743, 599 / 712, 689 /
+//   758; x-pairs likewise.
+// Up to two tiles per unit the next adjoint gains as well, where the checkpoints of a tile are
+// in the L2 that its wavefront reads them through: 32^3, 140 x 140 rays 212 -> 202 us.
+// Quasi-linear: FP32 24^3 68 / 58, 69 / 55, 85 / 78; 192^3 510 / 352, 475 / 354, 532 / 399, 512 x 512 rays
+// (16) 604 / 536; FP16 64^3 166 / 133, 151 / 126, 195 / 172, 248 / 222; but BF16 64^3 131 / 124, 125 /
+// 120, 167 / 160; 96^3 187 / 180, 176 / 191, 235 / 229, 306 / 331; 192^3 376 / 372, 362 / 380, 467 / 459, 606 / 635.
 Form forward_form(const LaunchPlan& P) {
-  const bool ql = P.tracer == 1;
-  double voxels = 0.0;  // of the smallest field that AHEAD is taken for
-  switch (P.dtype) {
-    case DT_F32: voxels = ql ? 0.0 : 1e6; break;
-    case DT_BF16: voxels = ql ? 4e6 : 3e6; break;
-    default: voxels = ql ? 0.0 : 3e6; break;
+  int ahead;  // tiles per compute unit up to which gathers are issued ahead
+  if (P.tracer == 1) {
+    ahead = P.dtype != DT_BF16 ? 16 : P.voxels <= 3e5 ? 4 : 2;
+  } else if (code_type(P.dtype) == DT_F16) {
+    ahead = 0;
+  } else {
+    ahead = P.voxels >= (P.dtype == DT_F32 ? 5e5 : 3e6) ? 9 : 2;
   }
-  const bool ahead = ql || code_type(P.dtype) != DT_F16;
-  if (ahead && P.total_tiles <= (ql ? 16 : 9) * P.n_cus && (P.total_tiles <= P.n_cus || P.voxels >= voxels))
-    return FORM_AHEAD;
+  if (P.total_tiles <= ahead * P.n_cus) return FORM_AHEAD;
   return P.persistent ? FORM_PERSISTENT : FORM_GRID;
 }
 

@@ -127,16 +127,17 @@ def test_second_round_of_four_wavefront_blocks():
     assert adjoint(32, 184) == "queue"  # 529 tiles
 
 
-@pytest.mark.parametrize("dtype,least", [(0, 100), (3, 145), (2, 145), (5, 145), (1, None), (4, None)])
+@pytest.mark.parametrize("dtype,least", [(0, 80), (3, 145), (2, 145), (5, 145), (1, None), (4, None)])
 def test_gathers_ahead_by_field_size_and_type(dtype, least):
-    """Nonlinear forwards between one and nine tiles per compute unit: gathers ahead from `least`
-    voxels per axis on; FP16 codes never; up to one tile per unit whatever the size."""
+    """Nonlinear forwards: gathers ahead up to two tiles per compute unit, from `least` voxels per axis
+    on up to nine; FP16 codes never. Quasi-linear ones up to 16, BF16 up to 4 and, from 67^3 on, 2."""
     def forward(n, side, **kw):
         return forms(room((n, n, n), side, side, dtype=dtype, **kw))[0]
-    for n in (32, 64, 99, 100, 144, 145, 158, 159, 224):
+    for n in (24, 64, 79, 80, 144, 145, 224):
         few = "grid" if least is None else "ahead"
-        assert forward(n, 64) == forward(n, 128) == few
-        assert forward(n, 129) == forward(n, 384) == (few if least is not None and n >= least else "grid")
+        assert forward(n, 64) == forward(n, 176) == few
+        assert forward(n, 184) == forward(n, 384) == (few if least is not None and n >= least else "grid")
         assert forward(n, 392) == "grid"
-        assert forward(n, 129, tracer=1) == ("grid" if dtype == 2 and n < 159 else "ahead")
-        assert forward(n, 512, tracer=1) == ("grid" if dtype == 2 and n < 159 else "ahead") and forward(n, 520, tracer=1) == "grid"
+    for n, last in ((24, 512), (66, 512), (67, 512), (224, 512)) if dtype != 2 else ((24, 256), (66, 256), (67, 176), (224, 176)):
+        assert forward(n, 64, tracer=1) == forward(n, last, tracer=1) == "ahead"
+        assert forward(n, last + 8, tracer=1) == "grid"
