@@ -683,13 +683,16 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
 // once, twice as many in turn. Adjoint, one wavefront per tile / four, us: 128^3 room, stride 3, 36
 // tiles 1106 / 540, 256 tiles 1080 / 538, 900 tiles 1225 / 1817; stride 16, 144 tiles 1184 / 522;
 // 64^3, stride 4, 256 tiles 510 / 288. Between one tile per unit and two, a second round gains
-// - on fields of up to about 50^3 voxels (stride 3): 32^3, 484 tiles 244 / 213; 48^3, 289 tiles 386 /
-//   338, 361 392 / 376, 484 383 / 356; x-pairs, 484 tiles 424 / 377; but 52^3, 400 tiles 428 / 474,
-//   x-pairs, 324 tiles 460 / 495, 56^3, 484 456 / 510;
-// - else while it is short and the rays share few cells: 192^3, 484 tiles (1.6 rays per cell) 1730 /
-//   1547; 160^3, 361 (1.6) 1412 / 1266, 484 (2.2) 1399 / 1421; 128^3, 361 (2.5) 1106 / 1065, 484 (3.5)
-//   1106 / 1218; 96^3, 289 (3.4) 820 / 756, 324 (3.9) 820 / 823, 361 (4.5) 827 / 861, 484 (6.2) 817 /
-//   1056; 72^3, 289 (6) 595 / 563, 324 (7) 614 / 646; 64^3, 361 (10) 539 / 713, 484 (14) 539 / 862.
+// - on fields of up to about 50^3 voxels: stride 3, 32^3, 484 tiles 244 / 213; 48^3, 289 tiles 386 / 338,
+//   361 392 / 376, 484 383 / 356; but 52^3, 400 tiles 428 / 474, x-pairs, 324 tiles 460 / 495;
+// - else while it is short and the rays share few cells (in brackets, rays per cell). FP32, stride 3:
+//   192^3, 289 tiles (1) 1745 / 1363, 484 (1.6) 1730 / 1577; 160^3, 484 (2.2) 1425 / 1419; 128^3, 289 (2)
+//   1132 / 1013, 400 (2.8) 1140 / 1082, 484 (3.4) 1119 / 1213; 96^3, 289 (3.5) 836 / 819, 361 (4.5) 838 /
+//   899; 80^3, 289 (5) 683 / 709; 64^3, 289 (8) 544 / 639. The samples of longer strides and other
+//   types cost the one wavefront more: stride 16, 128^3, 484 tiles 1177 / 1177; 96^3, 324 (4) 867 /
+//   842; 80^3, 289 708 / 702, 324 (6) 719 / 708; 64^3, 289 564 / 660; FP16, 128^3, 400 tiles 1327 / 1170;
+//   96^3, 324 962 / 914; 80^3, 289 807 / 778, 361 (6.5) 825 / 824; 64^3, 289 637 / 699; BF16 and x-pairs
+//   of FP32 128^3, 400 tiles 1236 / 1112, 1252 / 1105; 80^3, 289 742 / 757, 750 / 751.
 // Pixel lists take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera (452 tiles)
 // 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 / 2172; 256
 // tiles 1039 / 1292, 637 / 299 and 1070 / 1152. So do strides beyond 16, whose walk is one
@@ -700,7 +703,8 @@ static bool adjoint_by_pipe(const LaunchPlan& P) {
   const float second_round = (float)P.total_tiles / (float)P.n_cus - 1.0f;
   if (second_round <= 0.0f) return true;
   if (P.lists || P.ckpt_k > 16) return false;
-  return P.voxels <= 125000.0 || P.rays_per_cell * second_round <= 1.4f;
+  const float rays_per_cell = P.dtype == DT_F32 && P.ckpt_k <= 4 ? 4.0f : 7.0f;
+  return P.voxels <= 125000.0 || (P.rays_per_cell <= rays_per_cell && P.rays_per_cell * second_round <= 2.1f);
 }
 
 Form adjoint_form(const LaunchPlan& P) {

@@ -117,10 +117,13 @@ def test_second_round_of_four_wavefront_blocks():
     round."""
     def adjoint(n, side, dtype=0, scenes=1, **kw):
         return forms(*[room((n, n, n), side, side, dtype=dtype, **kw)] * scenes)[1]
-    assert adjoint(96, 128) == "pipe"  # 256 tiles
-    assert adjoint(96, 132) == "pipe"  # 289 tiles, 3.5 rays per cell
-    assert adjoint(96, 150) == adjoint(96, 176) == adjoint(64, 150) == adjoint(64, 176) == "queue"
-    assert adjoint(192, 176) == "pipe"  # 484, 1.6
+    assert adjoint(64, 128) == "pipe"  # 256 tiles
+    assert adjoint(96, 136) == "pipe"  # 289 tiles, 3.5 rays per cell
+    assert adjoint(96, 150) == adjoint(96, 176) == adjoint(64, 136) == adjoint(64, 176) == "queue"
+    assert adjoint(80, 136) == "queue" and adjoint(80, 136, stride=16) == adjoint(80, 136, dtype=1) == "pipe"  # 5
+    assert adjoint(64, 136, stride=16) == adjoint(64, 136, dtype=1) == adjoint(64, 136, dtype=3) == "queue"  # 8
+    assert adjoint(128, 160) == "pipe" and adjoint(128, 176) == "queue"  # 400 tiles, 2.8; 484, 3.4
+    assert adjoint(192, 176) == adjoint(160, 176) == "pipe"  # 484, 1.6 and 2.2
     assert adjoint(50, 176) == adjoint(32, 176) == "pipe"
     assert adjoint(51, 176) == adjoint(51, 176, dtype=3) == "queue"
     assert adjoint(48, 120) == "pipe" and adjoint(48, 120, scenes=2) == "queue"  # 225 tiles; 450 on two fields
