@@ -71,22 +71,19 @@ __host__ __device__ constexpr int fused_lds_floats(int depth) {
 
 __global__ __launch_bounds__(256) void k_mlp_forward_fused(MlpDev M, float* __restrict__ act, float* __restrict__ xh,
                                                            float* __restrict__ wt, float* __restrict__ out,
-                                                           float* __restrict__ T, float T0, float dT) {
+                                                           float* __restrict__ T, float T0, float dT, int nblk) {
   extern __shared__ float lds[];
   const int D = M.depth;
-  // The last D - 1 blocks take no points: each leaves a hidden layer's W_l^T for the backward
-  // pass. In the blocks with points it was in the way of a small call (512 points, depth 4: 25.0
-  // us against 22.6 so).
-  const int nblk = (int)gridDim.x - (D - 1);
-  if ((int)blockIdx.x >= nblk) {
-    const int l = 1 + (int)blockIdx.x - nblk;
-    float* dst = wt + (size_t)(l - 1) * MLP_WIDTH * MLP_WIDTH;
-#pragma unroll
-    for (int i = 0; i < MLP_WIDTH * MLP_WIDTH / 256; ++i) {
-      const int e = threadIdx.x + 256 * i;
-      dst[e] = M.params[M.off_w[l] + (e & (MLP_WIDTH - 1)) * MLP_WIDTH + (e / MLP_WIDTH)];
-    }
-    return;
+  // W_l^T of the hidden layers for the backward pass, a layer per block. Blocks past the first
+  // nblk, if the grid has any, take no points.
+  const bool spare = nblk < (int)gridDim.x;
+  if (!spare || (int)blockIdx.x >= nblk) {
+    const int step = spare ? (int)gridDim.x - nblk : nblk;
+    for (int l = 1 + (spare ? (int)blockIdx.x - nblk : (int)blockIdx.x); l < D; l += step)
+      for (int e = threadIdx.x; e < MLP_WIDTH * MLP_WIDTH; e += 256)
+        wt[(l - 1) * MLP_WIDTH * MLP_WIDTH + e] =
+            M.params[M.off_w[l] + (e & (MLP_WIDTH - 1)) * MLP_WIDTH + (e / MLP_WIDTH)];
+    if (spare) return;
   }
   float* Wh = lds;                                         // W_1 .. W_{D-1}, rows padded
   float* bh = Wh + (D - 1) * MLP_WIDTH * FUSED_PITCH;      // b_0 .. b_{D-1}
@@ -1028,9 +1025,12 @@ hipError_t launch_mlp_forward(const MlpDev& M, const MlpWork& w, float* out, flo
   }
   const long long groups = (M.n + 31) / 32;
   const long long blocks = (groups + 3) / 4;
-  const int grid = (int)(blocks < 2048 ? blocks : 2048) + M.depth - 1;
+  const int nblk = (int)(blocks < 2048 ? blocks : 2048);
+  // The transposed weights by blocks of their own while compute units are idle: 512 points, depth
+  // 4, 25.0 -> 22.6 us. More blocks than units would run them last: 64^3 points, depth 8, 846 -> 863.
+  const int grid = nblk + M.depth - 1 <= 256 ? nblk + M.depth - 1 : nblk;
   hipLaunchKernelGGL(k_mlp_forward_fused, dim3(grid), dim3(256), lds, stream, M, w.act, w.xh, w.wt, out, T,
-                     T0, dT);
+                     T0, dT, nblk);
   return hipGetLastError();
 }
 
