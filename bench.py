@@ -132,7 +132,8 @@ def launches(args):
 # requests and HBM bytes per launch. Used only while the kernels' sources hash to the value
 # recorded with the counters and the configuration matches.
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "tracer_room1m_counters.md")
-KERNEL_SOURCES = ("trace_fwd.hip", "trace_adj.hip", "trace_adj_queue.hip", "rbos_adjoint.hpp", "rbos_device.hpp",
+KERNEL_SOURCES = ("trace_fwd.hip", "trace_adj.hip", "trace_adj_queue.hip", "rbos_adjoint.hpp",
+                  "rbos_coherent.hpp", "rbos_device.hpp",
                   "rbos_launch.hpp", "abi.hip",
                   "field_pack.hip", "ceilings.hip")
 COPY_BYTES = 256 << 20
