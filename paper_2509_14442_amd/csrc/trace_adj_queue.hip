@@ -693,18 +693,22 @@ static bool adjoint_by_queue(const LaunchPlan& P) {
 //   842; 80^3, 289 708 / 702, 324 (6) 719 / 708; 64^3, 289 564 / 660; FP16, 128^3, 400 tiles 1327 / 1170;
 //   96^3, 324 962 / 914; 80^3, 289 807 / 778, 361 (6.5) 825 / 824; 64^3, 289 637 / 699; BF16 and x-pairs
 //   of FP32 128^3, 400 tiles 1236 / 1112, 1252 / 1105; 80^3, 289 742 / 757, 750 / 751.
-// Pixel lists take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera (452 tiles)
-// 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 / 2172; 256
-// tiles 1039 / 1292, 637 / 299 and 1070 / 1152. So do strides beyond 16, whose walk is one
-// wavefront's: stride 64, 192^3, 400 tiles 2872 / 3085, 96^3, 484 tiles 1315 / 1560, 144 tiles 1279 /
-// 769; stride 256, 144 tiles 2944 / 2380, coherent 4472.
+// Pixel lists on larger fields take it up to one tile per unit: 170 x 170 pixels of a 512 x 512 camera
+// (452 tiles) 1209 / 2069, of 2048 x 1536 (see k_trace_adj_list) 733 / 814, 30000 random ones 1408 /
+// 2172; 256 tiles 1039 / 1292, 637 / 299 and 1070 / 1152. On small fields regions gain and random
+// pixels lose: 32^3, 176 x 176 of 512 x 384 258 / 197, 30000 random ones 536 / 746; 50^3 478 / 319 and
+// 669 / 957. A list may be a small part of a call, and the line there is that of images. Strides
+// beyond 16 stop at one tile per unit on every field, their walk is one wavefront's: stride 64,
+// 192^3, 400 tiles 2872 / 3085, 96^3, 484 tiles 1315 / 1560, 144 tiles 1279 / 769; stride 256, 144 tiles
+// 2944 / 2380, coherent 4472.
 static bool adjoint_by_pipe(const LaunchPlan& P) {
   if (P.tracer == 1 || P.total_tiles > 2 * P.n_cus) return false;
   const float second_round = (float)P.total_tiles / (float)P.n_cus - 1.0f;
   if (second_round <= 0.0f) return true;
-  if (P.lists || P.ckpt_k > 16) return false;
+  if (P.ckpt_k > 16) return false;
+  if (P.voxels <= 125000.0) return true;
   const float rays_per_cell = P.dtype == DT_F32 && P.ckpt_k <= 4 ? 4.0f : 7.0f;
-  return P.voxels <= 125000.0 || (P.rays_per_cell <= rays_per_cell && P.rays_per_cell * second_round <= 2.1f);
+  return !P.lists && P.rays_per_cell <= rays_per_cell && P.rays_per_cell * second_round <= 2.1f;
 }
 
 Form adjoint_form(const LaunchPlan& P) {

@@ -149,13 +149,13 @@ def test_coherent_adjoint_with_every_lane_in_its_own_cell(tracer, ckpt, persiste
 
 
 def _lists(w):
-    """Pixel lists of 257 tiles and more: a region, the same in random order, random pixels of the
+    """Pixel lists of more than 512 tiles: a region, the same in random order, random pixels of the
     whole image, and a list that turns from one into the other, with a ragged last tile."""
     W, H = w.scene.width, w.scene.height
-    region = (np.arange(H // 2 - 70, H // 2 + 70)[:, None] * W + np.arange(W // 2 - 65, W // 2 + 65)[None]).ravel()
-    spread = np.sort(np.random.default_rng(1).choice(W * H, 17000, replace=False))
+    region = (np.arange(H // 2 - 100, H // 2 + 100)[:, None] * W + np.arange(W // 2 - 85, W // 2 + 85)[None]).ravel()
+    spread = np.sort(np.random.default_rng(1).choice(W * H, 34000, replace=False))
     return {"region": region, "shuffled": np.random.default_rng(2).permutation(region), "random": spread,
-            "both": np.concatenate([region[:9003], spread[::2]])}
+            "both": np.concatenate([region[:17003], spread[::2]])}
 
 
 @pytest.mark.parametrize("name", ["region", "shuffled", "random", "both"])
@@ -172,7 +172,7 @@ def test_pixel_list_forward_equals_the_image_bitwise(name):
 @pytest.mark.parametrize("name,ckpt", [("region", k) for k in (1, 3, 4, 6, 8, 40)] +
                          [("both", k) for k in (1, 3, 4, 6, 8)] + [("shuffled", 3), ("random", 3)])
 def test_pixel_list_adjoint(name, ckpt):
-    """Lists between one tile per compute unit and one residency: tiles of few cells go coherent,
+    """Lists between two tiles per compute unit and one residency: tiles of few cells go coherent,
     the others by queue, within one launch. 1600 x 1200 pixels: the region's tiles lie in 1 or 2 cells."""
     w = room_workload((20, 24, 16), 1600, 1200, seed=4, ckpt=ckpt, pat=256)
     ids = _lists(w)[name]

@@ -128,6 +128,8 @@ def test_second_round_of_four_wavefront_blocks():
     assert adjoint(51, 176) == adjoint(51, 176, dtype=3) == "queue"
     assert adjoint(48, 120) == "pipe" and adjoint(48, 120, scenes=2) == "queue"  # 225 tiles; 450 on two fields
     assert adjoint(32, 184) == "queue"  # 529 tiles
+    assert adjoint(50, 2048, pixels=64 * 512) == "pipe" and adjoint(50, 2048, pixels=64 * 513) == "queue"
+    assert adjoint(51, 2048, pixels=64 * 257) == "queue"
 
 
 @pytest.mark.parametrize("dtype,least", [(0, 80), (3, 145), (2, 145), (5, 145), (1, None), (4, None)])
