@@ -678,8 +678,9 @@ def main():
             r = out[key]
             r["fma_ceiling_tflops"] = ceil["fma_fp32_tflops"]
             r["frac_of_fma_ceiling"] = r["achieved"] / ceil["fma_fp32_tflops"]
-            # field values delivered to the lanes (algorithmic gather bytes) against the
-            # coherent-gather ceiling measured on the same record layout and ray pattern
+            # field values delivered to the lanes (algorithmic gather bytes: three samples per step,
+            # of which the kernels gather two and carry the third over) against the coherent-gather
+            # ceiling measured on the same record layout and ray pattern
             if args.tracer == "nonlinear" or key == "roofline_fwd":
                 per_step = (vals if not ql else 16) * vb
                 got = per_step * ray_steps / t / 1e12
