@@ -430,6 +430,7 @@ rbos::LaunchPlan plan_of(const Prepared& P, const rbos_scene* scenes, int n_cus)
   for (size_t i = 0; i < P.table.size(); ++i) {
     if (P.table[i].n_tiles == 0) continue;
     plan.lists = plan.lists || scenes[i].pixel_ids;
+    plan.checkpoints = plan.checkpoints || scenes[i].ckpt_stride > 0;
     plan.voxels += (double)scenes[i].nx * scenes[i].ny * scenes[i].nz;
     weight += P.table[i].n_tiles;
     logs += P.table[i].n_tiles * std::log(rays_per_cell(scenes[i]));

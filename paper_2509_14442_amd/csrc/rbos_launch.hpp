@@ -28,6 +28,7 @@ struct LaunchPlan {
   int order_shift;          // cost >> order_shift is the sort key (< 1024)
   float rays_per_cell;      // rays of one tile that share a cell, estimated from the geometry
   bool lists;               // a scene has a pixel list
+  bool checkpoints;         // a scene keeps checkpoints
   double voxels;            // of all scenes
 };
 

@@ -192,18 +192,21 @@ constexpr int LIST_CELLS = 16;
 
 // Wavefronts per SIMD the registers are held to. The Sharma step carries a sample between steps
 // and takes 75 to 77 registers; held to 64 for 8 wavefronts it spills 11 to 18 of them. That pays
-// for FP32 records beyond 9 tiles per compute unit alone (8 / 6 wavefronts, us: 900 x 900 rays,
-// 192^3, stride 3 1730 / 1760; 1024 x 1024, 128^3, stride 16 1306 / 1340), and costs where wavefronts
-// are few (384 x 384, 88^3 276 / 261) or samples are decoded or gathered in parts: BF16, 1024 x 1024,
-// 128^3, stride 1 2123 / 1992, stride 3 1660 / 1643, 256 x 256, 64^3 170 / 161; FP16 256 x 256,
-// 128^3 389 / 353, 1024 x 1024, stride 1 2177 / 2059; x-pairs 1894 / 1718, stride 1 2730 / 2114.
-template <int DT, bool QL, Gathers MODE>
+// for FP32 records beyond 9 tiles per compute unit (8 / 6 wavefronts, us: 900 x 900 rays, 192^3,
+// stride 3 1730 / 1760; 1024 x 1024, 128^3, stride 16 1306 / 1340), and costs where wavefronts are few
+// (384 x 384, 88^3 276 / 261) or samples that are decoded or gathered in parts meet checkpoint stores:
+// BF16, 1024 x 1024, 128^3, stride 1 2123 / 1992, stride 3 1660 / 1643, 256 x 256, 64^3 170 / 161;
+// FP16 256 x 256, 128^3 389 / 353, 1024 x 1024, stride 1 2177 / 2059; x-pairs 1894 / 1718, stride 1
+// 2730 / 2114. Without checkpoints it pays for all types, 1024 x 1024, 128^3: BF16 1363 / 1373, FP16
+// 1447 / 1470, x-pairs of FP32 1383 / 1416; 192^3 2005 / 2040, 2141 / 2190, 2063 / 2119; 512 x 512 (16 tiles
+// per unit) alike.
+template <Gathers MODE>
 constexpr int fwd_waves_per_simd() {
-  return MODE == Gathers::AHEAD || MODE == Gathers::BY_WAVE ? 2 : MODE == Gathers::AT_USE && (QL || DT == DT_F32) ? 8 : 6;
+  return MODE == Gathers::AHEAD || MODE == Gathers::BY_WAVE ? 2 : MODE == Gathers::AT_USE ? 8 : 6;
 }
 
 template <int DT, bool QL, Gathers MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<DT, QL, MODE>()))) void k_trace_fwd(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<MODE>()))) void k_trace_fwd(
     const SceneDev* __restrict__ scenes, int n_scenes, int total_tiles, int wpb, int nblocks) {
   const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int gtile = xcd_remap(blockIdx.x, nblocks) * wpb + wave;
@@ -301,8 +304,9 @@ static hipError_t launch_fwd_t(const LaunchPlan& P, hipStream_t stream) {
   } else {
     const int nblocks = (P.total_tiles + P.wpb - 1) / P.wpb;
     auto* kernel = &k_trace_fwd<DT, QL, Gathers::AT_USE>;
-    if constexpr (!QL && DT == DT_F32) {
-      if (P.total_tiles <= 9 * P.n_cus) kernel = &k_trace_fwd<DT, QL, Gathers::AT_USE_FEW>;
+    if constexpr (!QL) {  // see fwd_waves_per_simd
+      const bool many = DT == DT_F32 ? P.total_tiles > 9 * P.n_cus : !P.checkpoints && P.total_tiles > 16 * P.n_cus;
+      if (!many) kernel = &k_trace_fwd<DT, QL, Gathers::AT_USE_FEW>;
     }
     hipLaunchKernelGGL(kernel, dim3(nblocks), block, 0, stream, P.scenes, P.n_scenes, P.total_tiles, P.wpb, nblocks);
   }

@@ -84,6 +84,20 @@ def test_forward_forms_agree_bitwise(tracer, dtype):
         _same_rays(grid, i, _forward([scenes[i]], None, "grid" if dtype == "f16" and not tracer else "ahead"), 0)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "f32-xpair", "f16-xpair", "bf16-xpair"])
+@pytest.mark.parametrize("height", [512, 517])
+def test_forward_without_checkpoints_agrees_bitwise(dtype, height):
+    """4096 and 4160 tiles: beyond 16 per compute unit a call without checkpoints is compiled for 8
+    wavefronts per SIMD, one with them for 6 (FP32 for 8)."""
+    w = room_workload((31, 28, 36), 512, height, seed=6, ckpt=3, pat=256)
+    kept = _scene(w, dtype)
+    a = _forward([kept], GRID, "grid")
+    b = api.Tracer([kept], GRID, checkpoints=False).forward()
+    assert b.ckpt == [None] and b.forms()[0] == "grid"
+    for x, y in ((a.uv, b.uv), (a.duv, b.duv), (a.n_steps, b.n_steps), (a.status, b.status)):
+        assert torch.equal(x[0].view(torch.uint8), y[0].view(torch.uint8))
+
+
 @pytest.mark.parametrize("ckpt", [1, 3, 4, 6, 8, 16, 40])
 def test_adjoint_coherent_grid_and_persistent(ckpt):
     """1444 tiles: 6 per compute unit, so strides from 8 on take chunks of 4."""
